@@ -18,26 +18,28 @@
 //           workgroup.
 //   edge    one workgroup per edge: the edge's partials summed in fp64 in a
 //           fixed order; A^T H_e A and A^T g_e.
-//   assemble one workgroup per block row of the reduced 7(N-1) system
-//           (keyframe 0 holds the gauge): the edges' blocks summed in LDS in
-//           edge order, one writer per entry, rows written out whole.
-//   solve   one workgroup: the block-sparse Cholesky of the system in
-//           keyframe order over its fill pattern (found once per call), in
-//           LDS, the forward substitution folded into the factorization;
-//           when the fill exceeds LDS, the dense blocked right-looking
-//           Cholesky in fp64 with 32 x 32 tiles instead (the diagonal tile
-//           factored one column group per barrier, the panel kept in LDS, the
-//           backward substitution blocked);
-//           T_WC[k] <- Exp(tau_k) o T_WC[k] (Eq. 1).  A system that is not positive definite, or a step norm
-//           below step_tol, ends the loop: later launches of the call return
-//           at once.
+//   solve   one launch.  Usually one workgroup works: the block-sparse Cholesky
+//           of the reduced 7(N-1) system (keyframe 0 holds the gauge) in a
+//           fill-reducing order, level by level, in LDS (in the workspace when
+//           the factor exceeds LDS), with the edges' blocks gathered straight
+//           from the edge kernel's output.  For a graph so dense that its
+//           factor has no sparsity to use, one workgroup per block row
+//           assembles the dense system and the last one to finish factors it:
+//           blocked right-looking Cholesky in fp64 with 32 x 32 tiles (the
+//           diagonal tile factored one column group per barrier, the panel
+//           kept in LDS, the backward substitution blocked).
+//           T_WC[k] <- Exp(tau_k) o T_WC[k] (Eq. 1).  A system that is not
+//           positive definite, or a step norm below step_tol, ends the loop:
+//           later launches of the call return at once.
 //
-// Kernel boundaries order every hand-off, so no workgroup needs a
-// device-scope fence.  A final accumulation at the last poses gives the cost
+// Kernel boundaries order every hand-off but the dense assembly's, so no other
+// workgroup needs a device-scope fence.  A final accumulation at the last poses gives the cost
 // and match count.  Launches are stream-ordered with no host synchronisation.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <climits>
 
 #include "m3s.h"
 #include "m3s_internal.h"
@@ -52,7 +54,31 @@ constexpr int kSolveThreads = 512;
 constexpr int kVals = kPoseVals;
 constexpr int kStride = 40;         // floats per block partial, doubles per edge system
 constexpr int kMaxDim = 7 * (M3S_MAX_KEYFRAMES - 1);  // largest reduced system
-constexpr int kPatWords = (M3S_MAX_KEYFRAMES + 31) / 32;  // bit words per block row of the pattern
+constexpr int kPatWords = (M3S_MAX_KEYFRAMES + 31) / 32;  // bit words of a set of keyframes
+
+// The factor's block structure (backend_pattern_kernel), in elimination order:
+// position k holds keyframe node perm[k] + 1.  Blocks of L are stored by
+// column, the diagonal first, so that a level's blocks are consecutive slots.
+constexpr int kLdsBlocks = 320;      // blocks of L in LDS: 320 x 392 B = 122.5 KB
+constexpr int kMaxBlocks = 2048;     // blocks of L in the workspace
+// Block products of the whole factorization.  A factor of at most 320 blocks
+// needs at most 320 + 0.4714 * 320^1.5 = 3019 (edges plus triangles of its
+// graph, Kruskal-Katona), which the LDS list holds.
+constexpr int kLdsUpdates = 3072;
+constexpr int kMaxUpdates = 8192;
+// How the call's systems are solved (state[2]).
+enum { kSolveLds = 0, kSolveGlobal = 1, kSolveDense = 2 };
+struct PatternBuf {
+    int32_t nblk, nlev, nupd, pad;
+    uint8_t perm[M3S_MAX_KEYFRAMES];          // position -> keyframe - 1
+    uint8_t pos[M3S_MAX_KEYFRAMES];           // keyframe - 1 -> position
+    uint16_t colstart[M3S_MAX_KEYFRAMES + 2]; // first slot of each column
+    uint16_t lvl[M3S_MAX_KEYFRAMES + 2];      // first position of each level
+    uint8_t si[kMaxBlocks], sj[kMaxBlocks];   // row and column position of each slot
+    uint16_t ustart[kMaxBlocks + 2];          // products of slot s: upd[ustart[s]] ..
+    int32_t estart[kMaxBlocks + 2];           // edges of slot s: elist[estart[s]] ..
+    uint32_t upd[kMaxUpdates];                // slot of L_xv | slot of L_zv << 16
+};
 
 struct BackendArgs {
     int N, HW, E, blocks_per_edge;
@@ -71,13 +97,13 @@ struct BackendArgs {
     double* edge_sys;         // [E*kStride] fp64 relative normal equations per edge
     double* edge_blk;         // [E*kBlk] A^T H_e A (49) and A^T g_e (7) per edge
     float* partials;          // [E*blocks_per_edge*kStride]
-    int32_t* state;           // [0] done flag, [1] applied steps, [2] the factor's fill exceeds the sparse solve
+    int32_t* state;           // [0] done flag, [1] applied steps, [2] kSolve*, [3] dense assembly ticket
     double* stat;             // [0] last step norm
-    double* M;                // [np*np] reduced Hessian, factored in place (lower triangle)
+    double* M;                // [np*np] dense reduced Hessian, factored in place, or the sparse factor's blocks
     double* rhs;              // [np]
     double* dinv;             // [nt*kTile*kTile] inverses of the diagonal tiles
-    uint32_t* pat;            // [(N-1)*kPatWords] block pattern of the factor L (lower, after fill), bit j of row i
-    int32_t* row_start;       // [N] first slot of each block row of L in row-major block order; [N-1] = blocks
+    PatternBuf* pat;          // block structure of the factor
+    uint32_t* elist;          // [3*E] edges of every slot: e | flags
     float* T_out;             // [N*12]
     float* info;              // [4] or null
 };
@@ -94,7 +120,7 @@ __global__ void __launch_bounds__(256) backend_init_kernel(const float* __restri
                                                            double* __restrict__ stat) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t < 12 * N) T64[t] = (double)T_in[t];
-    if (t < 3) state[t] = 0;
+    if (t < 4) state[t] = 0;
     if (t < 2) stat[t] = 0.0;
 }
 
@@ -228,33 +254,33 @@ __global__ void __launch_bounds__(kThreads) backend_edge_kernel(BackendArgs A, i
     }
 }
 
-// Assembly of the reduced system: one workgroup per block row (keyframe
-// p = blockIdx.x + 1, rows 7(p-1) .. 7(p-1)+6) and one for the padding rows.
-// The row block is summed in LDS from the edges' blocks in edge order (thread
-// (a, b) owns the entries at offset (a, b) of the diagonal block, thread
-// 64 + (a, b) those of the off-diagonal blocks, so every entry has one writer,
-// which visits the edges in order) and written out whole, zeros included,
-// with its right-hand side -g.
-constexpr int kAsmThreads = 128;
+// Dense assembly of one block row of the reduced system (keyframe
+// p = row + 1, rows 7(p-1) .. 7(p-1)+6; row N-1 is the padding rows).  The row
+// block is summed in LDS from the edges' blocks in edge order (thread (a, b)
+// owns the entries at offset (a, b) of the diagonal block, thread 64 + (a, b)
+// those of the off-diagonal blocks, so every entry has one writer, which
+// visits the edges in order) and written out whole, zeros included, with its
+// right-hand side -g.
 constexpr int kMaxNp = (kMaxDim + kTile - 1) / kTile * kTile;
+struct AssembleLds {
+    double rows[7 * kMaxNp];
+    double rr[7];
+};
 
-__global__ void __launch_bounds__(kAsmThreads) backend_assemble_kernel(BackendArgs A) {
-    __shared__ double rows[7 * kMaxNp];
-    __shared__ double rr[7];
-    if (A.state[0]) return;
+__device__ __forceinline__ void assemble_row(const BackendArgs& A, int row, AssembleLds& S) {
     const int np = A.np, n = A.n, tid = threadIdx.x;
-    if ((int)blockIdx.x == A.N - 1) {
+    if (row == A.N - 1) {
         for (int r = n; r < np; ++r)
-            for (int c = tid; c < np; c += kAsmThreads) A.M[(long)r * np + c] = r == c ? 1.0 : 0.0;
-        for (int r = n + tid; r < np; r += kAsmThreads) A.rhs[r] = 0.0;
+            for (int c = tid; c < np; c += kSolveThreads) A.M[(long)r * np + c] = r == c ? 1.0 : 0.0;
+        for (int r = n + tid; r < np; r += kSolveThreads) A.rhs[r] = 0.0;
         return;
     }
-    for (int i = tid; i < 7 * np; i += kAsmThreads) rows[i] = 0.0;
-    if (tid < 7) rr[tid] = 0.0;
+    for (int i = tid; i < 7 * np; i += kSolveThreads) S.rows[i] = 0.0;
+    if (tid < 7) S.rr[tid] = 0.0;
     __syncthreads();
-    const int P = (int)blockIdx.x + 1, I = 7 * (P - 1);
+    const int P = row + 1, I = 7 * (P - 1);
     const int a = (tid & 63) / 7, b = (tid & 63) % 7;
-    for (int e = 0; e < A.E; ++e) {
+    for (int e = 0; tid < 128 && e < A.E; ++e) {
         const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
         // A self edge has T_ij = I whatever the poses: its blocks cancel.
         if (!edge_in_range(ei, ej, A.N) || ei == ej) continue;
@@ -264,22 +290,22 @@ __global__ void __launch_bounds__(kAsmThreads) backend_assemble_kernel(BackendAr
         const int other = own_i ? ej : ei;
         if (tid < 49) {
             // H_ii += A^T H_e A (own_i), H_jj += A^T H_e A (own_j)
-            rows[a * np + I + b] += blk[7 * a + b];
+            S.rows[a * np + I + b] += blk[7 * a + b];
         } else if (tid >= 64 && tid < 64 + 49) {
             // H_ij -= A^T H_e A, H_ji -= (A^T H_e A)^T; keyframe 0 holds the gauge
-            if (other > 0) rows[a * np + 7 * (other - 1) + b] -= own_i ? blk[7 * a + b] : blk[7 * b + a];
+            if (other > 0) S.rows[a * np + 7 * (other - 1) + b] -= own_i ? blk[7 * a + b] : blk[7 * b + a];
         } else if (tid >= 49 && tid < 56) {
             // right-hand side -g: g_i -= A^T g_e, g_j += A^T g_e
             const int o = tid - 49;
-            rr[o] += own_i ? blk[49 + o] : -blk[49 + o];
+            S.rr[o] += own_i ? blk[49 + o] : -blk[49 + o];
         }
     }
     __syncthreads();
-    for (int i = tid; i < 7 * np; i += kAsmThreads) {
+    for (int i = tid; i < 7 * np; i += kSolveThreads) {
         const int r = i / np, c = i - r * np;
-        A.M[(long)(I + r) * np + c] = rows[i];
+        A.M[(long)(I + r) * np + c] = S.rows[i];
     }
-    if (tid < 7) A.rhs[I + tid] = rr[tid];
+    if (tid < 7) A.rhs[I + tid] = S.rr[tid];
 }
 
 // Tile (ti, tj) of M as kTile x kTile, row-major with leading dimension np.
@@ -329,15 +355,16 @@ __device__ __forceinline__ void trailing_tile(const BackendArgs& A, PanelPtr P, 
 }
 
 // The end of a solve: pose updates T_WC[k] <- Exp(tau_k) o T_WC[k] for
-// keyframes 1..N-1 from the solution x (LDS), the relative pose of every edge
+// keyframes 1..N-1 from the solution x (LDS; keyframe k's step at
+// 7 pos(k - 1)), the relative pose of every edge
 // at the new poses (for the next accumulation), and the step norm, which ends
 // the loop below step_tol.  All NT lanes of the workgroup call this.
-template <int NT>
-__device__ __forceinline__ void apply_step(const BackendArgs& A, const double* x, double* red) {
+template <int NT, class Pos>
+__device__ __forceinline__ void apply_step(const BackendArgs& A, const double* x, double* red, Pos pos) {
     const int tid = threadIdx.x;
     for (int k = 1 + tid; k < A.N; k += NT) {
         double E[12], Tn[12];
-        sim3_exp(x + 7 * (k - 1), E);
+        sim3_exp(x + 7 * pos(k - 1), E);
         sim3_mul(E, A.T64 + 12 * k, Tn);
         for (int j = 0; j < 12; ++j) A.T64[12 * k + j] = Tn[j];
     }
@@ -358,21 +385,28 @@ __device__ __forceinline__ void apply_step(const BackendArgs& A, const double* x
     }
 }
 
-// One workgroup: factor the assembled reduced system (blocked Cholesky),
-// solve and update the poses.  Runs when the block-sparse factor does not fit
-// (state[2]); otherwise backend_sparse_solve_kernel has solved the system.
-__global__ void __launch_bounds__(kSolveThreads) backend_solve_kernel(BackendArgs A) {
-    __shared__ double D[kTile][kTile + 1];        // diagonal tile being factored
-    __shared__ double Dinv[kTile][kTile + 1];     // its inverse
-    __shared__ double V[kTile][kTile + 1];        // the inverse's rows before scaling
-    __shared__ double panel[kPanelRows * kPanelStride];  // the factored panel below it
-    __shared__ double x[kMaxDim + kTile];          // right-hand side, then the solution
-    __shared__ double red[kSolveThreads / 64];
-    __shared__ double part[kTile];
-    __shared__ double stage[kStageRows * kPanelStride];  // raw panel rows
-    if (A.state[0] || !A.state[2]) return;
+struct DenseLds {
+    double D[kTile][kTile + 1];                // diagonal tile being factored
+    double Dinv[kTile][kTile + 1];             // its inverse
+    double V[kTile][kTile + 1];                // the inverse's rows before scaling
+    double panel[kPanelRows * kPanelStride];   // the factored panel below it
+    double x[kMaxDim + kTile];                 // right-hand side, then the solution
+    double red[kSolveThreads / 64];
+    double stage[kStageRows * kPanelStride];   // raw panel rows
+};
+
+// One workgroup: factor the assembled dense system (blocked Cholesky), solve
+// and update the poses.
+__device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
+    auto& D = S.D;
+    auto& Dinv = S.Dinv;
+    auto& V = S.V;
+    auto& panel = S.panel;
+    auto& x = S.x;
+    auto& stage = S.stage;
     const int tid = threadIdx.x;
     const int n = A.n, np = A.np, nt = np / kTile;
+    (void)n;
 
     for (int k = tid; k < np; k += kSolveThreads) x[k] = A.rhs[k];
 
@@ -630,304 +664,575 @@ __global__ void __launch_bounds__(kSolveThreads) backend_solve_kernel(BackendArg
         __syncthreads();
     }
 
-    apply_step<kSolveThreads>(A, x, red);
+    apply_step<kSolveThreads>(A, x, S.red, [](int k) { return k; });
 }
 
 // ---------------------------------------------------------------- block-sparse solve
 //
 // The reduced system has one 7 x 7 block row per keyframe 1..N-1, and block
-// (i, j) is non-zero only where an edge joins keyframes i and j.  In the
-// natural (keyframe) order, Cholesky fills exactly the pairs of later
-// neighbours of every eliminated block (a chain with a few loop closures fills
-// little: the 32-keyframe benchmark graph's factor has 115 blocks of the 496
-// in a dense lower triangle).  backend_pattern_kernel finds that pattern once
-// per call; backend_sparse_solve_kernel factors only those blocks, in LDS,
-// every iteration.  A pattern with more than kSpBlocks blocks takes the dense
-// blocked solve instead (state[2]).
+// (i, j) is non-zero only where an edge joins keyframes i and j.  Its Cholesky
+// factor is as sparse, and as parallel, as the elimination order lets it be.
+// backend_pattern_kernel picks the order once per call: level by level, each
+// level an independent set of keyframes of nearly the least degree in the
+// graph that the earlier levels leave (the chain of a sequence halves at every
+// level).  The columns of one level depend on earlier levels only, so a level
+// costs the latency of one column.  Eliminated one column at a time in keyframe
+// order, a 31-column system (a 32-keyframe sequence with 3 closures) took 31
+// steps of about 2.3 us and its factor had 115 blocks: 101 us; here it is 6
+// levels, 89 blocks and 37 us.  A 96-keyframe sequence with 8 closures had
+// 791 blocks, more than LDS holds, and took the dense solve, 3,578 us; here it
+// is 10 levels, 286 blocks and 81 us.
 
-constexpr int kSpThreads = 256;
-constexpr int kSpBlocks = 320;   // blocks of L in LDS: 320 x 392 B = 122.5 KB
+constexpr int kPatThreads = 512;
 
-// Bits j of word w (of a row's kPatWords words) with lo < j < hi.
-__device__ __forceinline__ uint32_t bits_between(int w, int lo, int hi) {
-    const long b0 = 32L * w;
-    const uint64_t below_hi = hi <= b0 ? 0ull : (hi >= b0 + 32 ? 0xffffffffull : ((1ull << (hi - b0)) - 1ull));
-    const uint64_t above_lo = lo < b0 ? 0xffffffffull : (lo >= b0 + 31 ? 0ull : (0xffffffffull << (lo - b0 + 1)));
-    return (uint32_t)(below_hi & above_lo & 0xffffffffull);
+// Edges of a slot: the edge and how its block enters (PatternBuf, elist).
+constexpr uint32_t kEdgeMask = 0xffffu;   // M3S_MAX_EDGES fits 16 bits
+constexpr uint32_t kEdgeTransposed = 1u << 16, kEdgeOwnI = 1u << 17;
+static_assert(M3S_MAX_EDGES <= 0x10000, "edge index in 16 bits");
+static_assert(M3S_MAX_KEYFRAMES <= 128, "two keyframes per lane, positions in a byte");
+
+// Exclusive sums over the workgroup of every thread's v; total in *all.
+__device__ __forceinline__ int block_exclusive(int v, int* tmp, int* all) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int inc = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += u;
+    }
+    __syncthreads();  // earlier readers of tmp are done
+    if (lane == 63) tmp[wave] = inc;
+    __syncthreads();
+    int before = 0, sum = 0;
+    for (int w = 0; w < kPatThreads / 64; ++w) {
+        if (w < wave) before += tmp[w];
+        sum += tmp[w];
+    }
+    *all = sum;
+    return before + inc - v;
 }
 
-// One workgroup, once per call: the lower block pattern of L after symbolic
-// elimination in keyframe order (diagonal, every in-range edge between
-// keyframes 1..N-1, then for each block column k every pair of its later
-// non-zero rows), the slot of each block row's first block, and whether the
-// factor fits the sparse solve.
-__global__ void __launch_bounds__(kSpThreads) backend_pattern_kernel(BackendArgs A) {
-    __shared__ uint32_t rows[M3S_MAX_KEYFRAMES * kPatWords];
-    __shared__ uint32_t colm[kPatWords];
-    __shared__ int32_t cnt[M3S_MAX_KEYFRAMES];
-    const int nb = A.N - 1, tid = threadIdx.x;
-    for (int i = tid; i < nb * kPatWords; i += kSpThreads) rows[i] = 0u;
+// One workgroup, once per call: elimination order, levels, the factor's blocks,
+// and for every block the edges that enter it and the products it takes.
+__global__ void __launch_bounds__(kPatThreads) backend_pattern_kernel(BackendArgs A) {
+    __shared__ uint32_t adj[M3S_MAX_KEYFRAMES][kPatWords];
+    __shared__ uint32_t col[M3S_MAX_KEYFRAMES][kPatWords];  // by position: later keyframes of the column
+    __shared__ uint8_t perm[M3S_MAX_KEYFRAMES], pos[M3S_MAX_KEYFRAMES];
+    __shared__ int32_t cstart[M3S_MAX_KEYFRAMES + 1];
+    __shared__ uint16_t lvl[M3S_MAX_KEYFRAMES + 2];
+    __shared__ uint8_t si[kMaxBlocks], sj[kMaxBlocks];
+    __shared__ int32_t chunk[2 * kPatThreads];
+    __shared__ int tmp[kPatThreads / 64];
+    __shared__ int nlev_s;
+    const int nb = A.N - 1, tid = threadIdx.x, lane = tid & 63;
+    PatternBuf& P = *A.pat;
+    for (int i = tid; i < nb * kPatWords; i += kPatThreads) (&adj[0][0])[i] = 0u;
     __syncthreads();
-    for (int i = tid; i < nb; i += kSpThreads) atomicOr(&rows[i * kPatWords + (i >> 5)], 1u << (i & 31));
-    for (int e = tid; e < A.E; e += kSpThreads) {
+    for (int e = tid; e < A.E; e += kPatThreads) {
         const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
         if (!edge_in_range(ei, ej, A.N) || ei == ej || ei == 0 || ej == 0) continue;
-        const int a = max(ei, ej) - 1, b = min(ei, ej) - 1;
-        atomicOr(&rows[a * kPatWords + (b >> 5)], 1u << (b & 31));
+        atomicOr(&adj[ei - 1][(ej - 1) >> 5], 1u << ((ej - 1) & 31));
+        atomicOr(&adj[ej - 1][(ei - 1) >> 5], 1u << ((ei - 1) & 31));
     }
     __syncthreads();
-    for (int k = 0; k < nb; ++k) {
-        if (tid < kPatWords) colm[tid] = 0u;
-        __syncthreads();
-        for (int i = k + 1 + tid; i < nb; i += kSpThreads)
-            if ((rows[i * kPatWords + (k >> 5)] >> (k & 31)) & 1u) atomicOr(&colm[i >> 5], 1u << (i & 31));
-        __syncthreads();
-        // Row x of the column takes every other row z of the column, k < z < x
-        // (one writer per row).
-        for (int x = k + 1 + tid; x < nb; x += kSpThreads) {
-            if (!((colm[x >> 5] >> (x & 31)) & 1u)) continue;
-            for (int w = 0; w < kPatWords; ++w) rows[x * kPatWords + w] |= colm[w] & bits_between(w, k, x);
+    // The elimination in one wave, without barriers: lane l holds the rows of
+    // keyframes l and l + 64 of the remaining graph.  A level takes, in order of
+    // degree then index, every keyframe of degree at most max(least + 1, 2) that
+    // no earlier one of the level neighbours; eliminating it joins its
+    // neighbours, which leave the level.
+    if (tid < 64) {
+        uint32_t r[2][kPatWords];
+        bool alive[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int x = lane + 64 * h;
+            alive[h] = x < nb;
+#pragma unroll
+            for (int w = 0; w < kPatWords; ++w) r[h][w] = alive[h] ? adj[x][w] : 0u;
         }
-        __syncthreads();
-    }
-    for (int i = tid; i < nb; i += kSpThreads) {
-        int c = 0;
-        for (int w = 0; w < kPatWords; ++w) {
-            A.pat[i * kPatWords + w] = rows[i * kPatWords + w];
-            c += __popc(rows[i * kPatWords + w]);
-        }
-        cnt[i] = c;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int t = 0;
-        for (int i = 0; i < nb; ++i) {
-            A.row_start[i] = t;
-            t += cnt[i];
-        }
-        A.row_start[nb] = t;
-        A.state[2] = t > kSpBlocks ? 1 : 0;
-    }
-}
-
-// One workgroup per iteration: the block-sparse Cholesky of the assembled
-// system over the pattern, the forward substitution folded in, the backward
-// substitution, and the pose updates.  Per block column k, three barriers:
-//   1. every lane factors L_kk = chol(A_kk) and forms L_kk^-1 in registers
-//      (the same operations in every lane, so a block that is not positive
-//      definite stops every lane alike), and y_k <- L_kk^-1 y_k; the later
-//      rows of the column are listed in ascending order;
-//   2. one lane per row a of each listed block: L_xk[a] <- A_xk[a] L_kk^-T,
-//      then y_x[a] -= L_xk[a] . y_k;
-//   3. one lane per entry of each listed pair x >= z: L_xz -= L_xk L_zk^T.
-// L_kk^-1 replaces L_kk for the backward substitution L^T x = y, which one
-// wave runs from the last block row up (x_k = L_kk^-T (y_k - sum_i L_ik^T x_i)).
-__global__ void __launch_bounds__(kSpThreads) backend_sparse_solve_kernel(BackendArgs A) {
-    __shared__ double Lb[kSpBlocks * 49];
-    __shared__ double xs[kMaxDim];
-    __shared__ uint32_t rows[M3S_MAX_KEYFRAMES * kPatWords];
-    __shared__ int32_t rstart[M3S_MAX_KEYFRAMES];
-    __shared__ uint8_t si[kSpBlocks], sj[kSpBlocks];
-    __shared__ int32_t col[M3S_MAX_KEYFRAMES];
-    __shared__ int32_t cslot[M3S_MAX_KEYFRAMES];  // slot of block (col[p], k)
-    __shared__ uint64_t wb[kSpThreads / 64];
-    __shared__ double red[kSpThreads / 64];
-    if (A.state[0] || A.state[2]) return;
-    const int nb = A.N - 1, np = A.np, tid = threadIdx.x;
-    for (int i = tid; i < nb * kPatWords; i += kSpThreads) rows[i] = A.pat[i];
-    for (int i = tid; i <= nb; i += kSpThreads) rstart[i] = A.row_start[i];
-    for (int i = tid; i < A.n; i += kSpThreads) xs[i] = A.rhs[i];
-    __syncthreads();
-    const int nblk = rstart[nb];
-    // Block (si[s], sj[s]) of every slot s, row-major.
-    for (int i = tid; i < nb; i += kSpThreads) {
-        int sl = rstart[i];
-        for (int w = 0; w < kPatWords; ++w) {
-            uint32_t m = rows[i * kPatWords + w];
-            while (m) {
-                const int j = 32 * w + __builtin_ctz(m);
-                m &= m - 1u;
-                si[sl] = (uint8_t)i;
-                sj[sl] = (uint8_t)j;
-                ++sl;
+        auto degree = [&](int h) {
+            int d = 0;
+#pragma unroll
+            for (int w = 0; w < kPatWords; ++w) d += __popc(r[h][w]);
+            return d;
+        };
+        auto least = [&](int v) {
+            for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+            return __builtin_amdgcn_readfirstlane(v);
+        };
+        int k = 0, nlev = 0;
+        while (k < nb) {
+            if (lane == 0) lvl[nlev] = (uint16_t)k;
+            ++nlev;
+            const int d0 = least(min(alive[0] ? degree(0) : INT_MAX, alive[1] ? degree(1) : INT_MAX));
+            const int top = max(d0 + 1, 2);
+            bool cand[2] = {alive[0] && degree(0) <= top, alive[1] && degree(1) <= top};
+            for (;;) {
+                const int key = least(min(cand[0] ? degree(0) * 128 + lane : INT_MAX,
+                                          cand[1] ? degree(1) * 128 + lane + 64 : INT_MAX));
+                if (key == INT_MAX) break;
+                const int v = key & 127;
+                uint32_t rv[kPatWords];
+#pragma unroll
+                for (int w = 0; w < kPatWords; ++w)
+                    rv[w] = (uint32_t)__builtin_amdgcn_readlane(v < 64 ? (int)r[0][w] : (int)r[1][w], v & 63);
+                if (lane == 0) {
+                    perm[k] = (uint8_t)v;
+                    pos[v] = (uint8_t)k;
+                }
+#pragma unroll
+                for (int w = 0; w < kPatWords; ++w)
+                    if (lane == w) col[k][w] = rv[w];
+                ++k;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int x = lane + 64 * h;
+                    if (x == v) alive[h] = cand[h] = false;
+                    bool nbr = false;
+#pragma unroll
+                    for (int w = 0; w < kPatWords; ++w) nbr = nbr || ((x >> 5) == w && ((rv[w] >> (x & 31)) & 1u));
+                    if (nbr) {
+                        cand[h] = false;
+#pragma unroll
+                        for (int w = 0; w < kPatWords; ++w) {
+                            uint32_t t = r[h][w] | rv[w];
+                            if ((x >> 5) == w) t &= ~(1u << (x & 31));
+                            if ((v >> 5) == w) t &= ~(1u << (v & 31));
+                            r[h][w] = t;
+                        }
+                    }
+                }
             }
+        }
+        if (lane == 0) {
+            lvl[nlev] = (uint16_t)nb;
+            nlev_s = nlev;
         }
     }
     __syncthreads();
-    for (int q = tid; q < nblk * 49; q += kSpThreads) {
-        const int sl = q / 49, e = q - 49 * (q / 49), a = e / 7, b = e - 7 * (e / 7);
-        Lb[q] = A.M[(long)(7 * si[sl] + a) * np + 7 * sj[sl] + b];
-    }
-    __syncthreads();
-    // Slot of block (i, j), j <= i, present in the pattern.
-    auto slot = [&](int i, int j) -> int {
-        int sl = rstart[i];
-        for (int w = 0; w < (j >> 5); ++w) sl += __popc(rows[i * kPatWords + w]);
-        return sl + __popc(rows[i * kPatWords + (j >> 5)] & ((1u << (j & 31)) - 1u));
-    };
-    const int wave = tid >> 6, lane = tid & 63;
-    bool failed = false;
-    for (int k = 0; k < nb; ++k) {
-        // 1. L_kk and its inverse in registers (lower triangles), y_k.
-        const double* Dk = Lb + 49 * (rstart[k + 1] - 1);  // the diagonal is row k's last block
-        double L[7][7], Li[7][7], yk[7], isd[7];
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < 7; ++j) {
-            double d = Dk[7 * j + j];
-#pragma unroll
-            for (int m = 0; m < j; ++m) d -= L[j][m] * L[j][m];
-            bad = bad || !(d > 0.0) || !isfinite(d);
-            // 1/sqrt(d): hardware estimate and two Newton steps (no fp64
-            // division or square root in the chain).
-            double is = __builtin_amdgcn_rsq(d);
-            is = is * fma(-0.5 * d * is, is, 1.5);
-            is = is * fma(-0.5 * d * is, is, 1.5);
-            L[j][j] = d * is;
-            isd[j] = is;
-#pragma unroll
-            for (int i = j + 1; i < 7; ++i) {
-                double v = Dk[7 * i + j];
-#pragma unroll
-                for (int m = 0; m < j; ++m) v -= L[i][m] * L[j][m];
-                L[i][j] = v * is;
-            }
-        }
-        if (bad) {
-            failed = true;
-            break;
-        }
-#pragma unroll
-        for (int i = 0; i < 7; ++i) {
-            Li[i][i] = isd[i];
-#pragma unroll
-            for (int j = 0; j < i; ++j) {
-                double v = 0.0;
-#pragma unroll
-                for (int m = j; m < i; ++m) v += L[i][m] * Li[m][j];
-                Li[i][j] = -v * Li[i][i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 7; ++i) {
-            double v = 0.0;
-#pragma unroll
-            for (int m = 0; m <= i; ++m) v += Li[i][m] * xs[7 * k + m];
-            yk[i] = v;
-        }
-        // Later rows x of column k, ascending: one ballot per wave.
-        const int xr = tid;
-        const bool in_col = xr > k && xr < nb && ((rows[xr * kPatWords + (k >> 5)] >> (k & 31)) & 1u);
-        const uint64_t bal = __ballot(in_col);
-        if (lane == 0) wb[wave] = bal;
-        __syncthreads();
-        int ncol = 0, before = 0;
-#pragma unroll
-        for (int w = 0; w < kSpThreads / 64; ++w) {
-            const int c = __popcll(wb[w]);
-            if (w < wave) before += c;
-            ncol += c;
-        }
-        if (in_col) {
-            const int pos = before + __popcll(bal & ((1ull << lane) - 1ull));
-            col[pos] = xr;
-            cslot[pos] = slot(xr, k);
-        }
-        // The diagonal slot keeps L_kk^-1 (its lower triangle, the only part
-        // the backward substitution reads) and y_k is final: one lane writes
-        // both from registers with fixed offsets.
-        if (tid == 0) {
-            double* dk = Lb + 49 * (rstart[k + 1] - 1);
-#pragma unroll
-            for (int i = 0; i < 7; ++i) {
-#pragma unroll
-                for (int j = 0; j <= i; ++j) dk[7 * i + j] = Li[i][j];
-                xs[7 * k + i] = yk[i];
-            }
-        }
-        __syncthreads();
-        // 2. Panel rows and the forward substitution.
-        for (int q = tid; q < 7 * ncol; q += kSpThreads) {
-            const int x = col[q / 7], a = q - 7 * (q / 7);
-            double* row = Lb + 49 * cslot[q / 7] + 7 * a;
-            double r[7], out[7];
-#pragma unroll
-            for (int c = 0; c < 7; ++c) r[c] = row[c];
-            double acc = 0.0;
-#pragma unroll
-            for (int b = 0; b < 7; ++b) {
-                double v = 0.0;
-#pragma unroll
-                for (int c = 0; c <= b; ++c) v += r[c] * Li[b][c];
-                out[b] = v;
-                acc += v * yk[b];
-            }
-#pragma unroll
-            for (int b = 0; b < 7; ++b) row[b] = out[b];
-            xs[7 * x + a] -= acc;
-        }
-        __syncthreads();
-        // 3. Trailing update of every listed pair x >= z.
-        const int npair = ncol * (ncol + 1) / 2;
-        for (int q = tid; q < 49 * npair; q += kSpThreads) {
-            const int p = q / 49, e = q - 49 * (q / 49), a = e / 7, b = e - 7 * (e / 7);
-            int xi = 0;
-            while ((xi + 1) * (xi + 2) / 2 <= p) ++xi;
-            const int zi = p - xi * (xi + 1) / 2;
-            const int x = col[xi], z = col[zi];
-            const double* lx = Lb + 49 * cslot[xi] + 7 * a;
-            const double* lz = Lb + 49 * cslot[zi] + 7 * b;
-            double v = 0.0;
-#pragma unroll
-            for (int c = 0; c < 7; ++c) v += lx[c] * lz[c];
-            Lb[49 * slot(x, z) + e] -= v;
-        }
-        __syncthreads();
-    }
-    if (failed) {
-        if (tid == 0) A.state[0] = 1;
-        return;
-    }
-    // Backward substitution in wave 0, from the last block row up: every lane
-    // forms x_k = L_kk^-T y_k (y_k has taken every later row's share), then
-    // one lane per off-diagonal block (k, j) of row k (its slots are
-    // consecutive) takes y_j -= L_kj^T x_k.  Row k is the only writer of those
-    // y_j in its step, and the wave's LDS accesses complete in order.
-    if (wave == 0) {
-        for (int k = nb - 1; k >= 0; --k) {
-            const int s0 = rstart[k], sd = rstart[k + 1] - 1;  // first and diagonal slot of row k
-            const double* inv = Lb + 49 * sd;
-            double yv[7], xk[7];
-#pragma unroll
-            for (int c = 0; c < 7; ++c) yv[c] = xs[7 * k + c];
-#pragma unroll
-            for (int b = 0; b < 7; ++b) {
-                double v = 0.0;
-#pragma unroll
-                for (int c = b; c < 7; ++c) v += inv[7 * c + b] * yv[c];
-                xk[b] = v;
-            }
-            if (lane < 7) {
-                double v = 0.0;
-#pragma unroll
-                for (int b = 0; b < 7; ++b) if (b == lane) v = xk[b];
-                xs[7 * k + lane] = v;
-            }
-            for (int sl = s0 + lane; sl < sd; sl += 64) {
-                const int j = sj[sl];
-                const double* blk = Lb + 49 * sl;
-#pragma unroll
-                for (int c = 0; c < 7; ++c) {
-                    double v = 0.0;
-#pragma unroll
-                    for (int a = 0; a < 7; ++a) v += blk[7 * a + c] * xk[a];
-                    xs[7 * j + c] -= v;
+    // Column starts and the row and column of every slot.
+    int nblk, c = 0;
+    if (tid < nb)
+        for (int w = 0; w < kPatWords; ++w) c += __popc(col[tid][w]);
+    const int c0 = block_exclusive(tid < nb ? c + 1 : 0, tmp, &nblk);
+    const bool fits = nblk <= kMaxBlocks;
+    if (tid < nb) {
+        cstart[tid] = c0;
+        if (fits) {
+            int s = c0;
+            si[s] = sj[s] = (uint8_t)tid;
+            ++s;
+            for (int w = 0; w < kPatWords; ++w) {
+                uint32_t m = col[tid][w];
+                while (m) {
+                    si[s] = pos[32 * w + __builtin_ctz(m)];
+                    sj[s] = (uint8_t)tid;
+                    ++s;
+                    m &= m - 1u;
                 }
             }
         }
     }
     __syncthreads();
-    apply_step<kSpThreads>(A, xs, red);
+    if (!fits) {
+        if (tid == 0) A.state[2] = kSolveDense;
+        return;
+    }
+    // Each thread's consecutive slots: products with every earlier column that
+    // holds both the slot's row and its column.
+    constexpr int kOwn = kMaxBlocks / kPatThreads;
+    const int own_n = (nblk + kPatThreads - 1) / kPatThreads;
+    auto own_slot = [&](int j) { return j < own_n ? tid * own_n + j : nblk; };
+    auto in_col = [&](int v, int x) { return ((col[v][x >> 5] >> (x & 31)) & 1u) != 0u; };
+    auto slot_in = [&](int v, int x) {  // slot of (keyframe x, column v)
+        int s = cstart[v] + 1;
+        for (int w = 0; w < (x >> 5); ++w) s += __popc(col[v][w]);
+        return s + __popc(col[v][x >> 5] & ((1u << (x & 31)) - 1u));
+    };
+    int ucnt[kOwn], usum = 0;
+    for (int j = 0; j < kOwn; ++j) {
+        const int s = own_slot(j);
+        ucnt[j] = 0;
+        if (s < nblk) {
+            const int x = perm[si[s]], z = perm[sj[s]];
+            for (int v = 0; v < sj[s]; ++v)
+                if (in_col(v, x) && in_col(v, z)) ++ucnt[j];
+        }
+        usum += ucnt[j];
+    }
+    int nupd;
+    int u0 = block_exclusive(usum, tmp, &nupd);
+    if (nupd > kMaxUpdates) {
+        if (tid == 0) A.state[2] = kSolveDense;
+        return;
+    }
+    for (int j = 0; j < kOwn; ++j) {
+        const int s = own_slot(j);
+        if (s >= nblk) break;
+        P.ustart[s] = (uint16_t)u0;
+        const int x = perm[si[s]], z = perm[sj[s]];
+        for (int v = 0; v < sj[s] && ucnt[j] > 0; ++v)
+            if (in_col(v, x) && in_col(v, z)) {
+                P.upd[u0++] = (uint32_t)slot_in(v, x) | ((uint32_t)slot_in(v, z) << 16);
+                --ucnt[j];
+            }
+    }
+    // Edges of every slot, in edge order: first counted, then listed.
+    int ecnt[kOwn], e0[kOwn];
+    for (int j = 0; j < kOwn; ++j) ecnt[j] = e0[j] = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int b = 0; b < A.E; b += kPatThreads) {
+            __syncthreads();
+            const int m = min(kPatThreads, A.E - b);
+            if (tid < m) {
+                const int ei = A.edges[2 * (b + tid)], ej = A.edges[2 * (b + tid) + 1];
+                const bool use = edge_in_range(ei, ej, A.N) && ei != ej;
+                chunk[2 * tid] = use ? ei - 1 : -1;
+                chunk[2 * tid + 1] = use ? ej - 1 : -1;
+            }
+            __syncthreads();
+            for (int j = 0; j < kOwn; ++j) {
+                const int s = own_slot(j);
+                if (s >= nblk) break;
+                const int x = perm[si[s]], z = perm[sj[s]];
+                for (int t = 0; t < m; ++t) {
+                    const int i = chunk[2 * t], k = chunk[2 * t + 1];
+                    const bool own = i == x, hit = x == z ? (own || k == x) : (own ? k == z : (i == z && k == x));
+                    if (!hit) continue;
+                    // H_ii, H_jj += blk; H_ij -= blk, H_ji -= blk^T: a row owned by j reads it transposed.
+                    if (pass)
+                        A.elist[e0[j]++] = (uint32_t)(b + t) | (own ? kEdgeOwnI : 0u) |
+                                           (x != z && !own ? kEdgeTransposed : 0u);
+                    else
+                        ++ecnt[j];
+                }
+            }
+        }
+        if (pass) break;
+        int esum = 0, nedge;
+        for (int j = 0; j < kOwn; ++j) esum += ecnt[j];
+        int base = block_exclusive(esum, tmp, &nedge);
+        for (int j = 0; j < kOwn; ++j) {
+            const int s = own_slot(j);
+            e0[j] = base;
+            if (s < nblk) P.estart[s] = base;
+            base += ecnt[j];
+        }
+        if (tid == 0) P.estart[nblk] = nedge;
+    }
+    for (int i = tid; i < nb; i += kPatThreads) {
+        P.perm[i] = perm[i];
+        P.pos[i] = pos[i];
+        P.colstart[i] = (uint16_t)cstart[i];
+    }
+    for (int i = tid; i <= nlev_s; i += kPatThreads) P.lvl[i] = lvl[i];
+    for (int i = tid; i < nblk; i += kPatThreads) {
+        P.si[i] = si[i];
+        P.sj[i] = sj[i];
+    }
+    if (tid == 0) {
+        P.nblk = nblk;
+        P.nlev = nlev_s;
+        P.nupd = nupd;
+        P.colstart[nb] = (uint16_t)nblk;
+        P.ustart[nblk] = (uint16_t)nupd;
+        A.state[2] = nblk <= kLdsBlocks && nupd <= kLdsUpdates ? kSolveLds : kSolveGlobal;
+    }
+}
+
+// LDS of the sparse solve.  In LDS mode the blocks take most of it; in global
+// mode the longer lists do.
+template <bool LDS>
+struct SparseLds {
+    static constexpr int kBlocks = LDS ? kLdsBlocks : kMaxBlocks;
+    static constexpr int kUpdates = LDS ? kLdsUpdates : kMaxUpdates;
+    static constexpr int kEntries = LDS ? 1024 : 8192;  // edge entries; the rest are read from memory
+    double Lb[LDS ? kLdsBlocks * 49 : 1];
+    double xs[kMaxDim];                        // right-hand side, then y, then the solution, by position
+    double red[kSolveThreads / 64];
+    uint32_t upd[kUpdates];
+    uint32_t elist[kEntries];
+    int32_t estart[kBlocks + 1];
+    uint16_t ustart[kBlocks + 2];
+    uint16_t colstart[M3S_MAX_KEYFRAMES + 2], lvl[M3S_MAX_KEYFRAMES + 2];
+    uint8_t pos[M3S_MAX_KEYFRAMES];
+    uint8_t si[kBlocks], sj[kBlocks];
+    int bad;
+};
+
+// One workgroup: the block-sparse Cholesky over the pattern, left looking and
+// level by level, the forward substitution folded in, the backward substitution
+// (levels in reverse), and the pose updates.  Per level:
+//   1. one lane per entry of the level's blocks: A_xz -= sum_v L_xv L_zv^T over
+//      the listed products, and b_z -= sum_v L_zv y_v (ascending v: one writer
+//      per entry in a fixed order);
+//   2. sixteen lanes per column: every lane factors L_zz = chol(A_zz) and forms
+//      L_zz^-1 in registers, y_z <- L_zz^-1 b_z, then one lane per row a of the
+//      column's blocks: L_xz[a] <- A_xz[a] L_zz^-T.  L_zz^-1 replaces L_zz.
+// LDS: the blocks are in LDS (Lb = S.Lb), else in the workspace.
+template <bool LDS>
+__device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS>& S, double* __restrict__ Lb) {
+    const PatternBuf& P = *A.pat;
+    const int nb = A.N - 1, tid = threadIdx.x;
+    const int nblk = P.nblk, nlev = P.nlev, nupd = P.nupd;
+    const int nent = P.estart[nblk];
+    for (int i = tid; i < nblk; i += kSolveThreads) {
+        S.si[i] = P.si[i];
+        S.sj[i] = P.sj[i];
+    }
+    for (int i = tid; i <= nblk; i += kSolveThreads) {
+        S.ustart[i] = P.ustart[i];
+        S.estart[i] = P.estart[i];
+    }
+    for (int i = tid; i <= nb; i += kSolveThreads) {
+        S.colstart[i] = P.colstart[i];
+        if (i < nb) S.pos[i] = P.pos[i];
+        if (i <= nlev) S.lvl[i] = P.lvl[i];
+    }
+    for (int i = tid; i < nupd; i += kSolveThreads) S.upd[i] = P.upd[i];
+    for (int i = tid; i < min(nent, (int)S.kEntries); i += kSolveThreads) S.elist[i] = A.elist[i];
+    if (tid == 0) S.bad = 0;
+    __syncthreads();
+    auto entry = [&](int l) { return l < S.kEntries ? S.elist[l] : A.elist[l]; };
+    // The system's blocks, gathered from the edges' blocks in edge order: kQ
+    // entries per lane and step, the reads of each one's first kE edges (two per
+    // block and four per diagonal in a sequence) in flight together.
+    constexpr int kQ = 4, kE = 4;
+    for (int q0 = tid; q0 < nblk * 49; q0 += kQ * kSolveThreads) {
+        double t[kQ][kE];
+        int l0[kQ], l1[kQ];
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            const int q = q0 + i * kSolveThreads;
+            const int s = q / 49, e = q - 49 * s, a = e / 7, b = e - 7 * a;
+            const bool in = q < nblk * 49;
+            l0[i] = in ? S.estart[s] : 0;
+            l1[i] = in ? S.estart[s + 1] : 0;
+#pragma unroll
+            for (int j = 0; j < kE; ++j) {
+                t[i][j] = 0.0;
+                if (l0[i] + j < l1[i]) {
+                    const uint32_t f = entry(l0[i] + j);
+                    t[i][j] = A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + ((f & kEdgeTransposed) ? 7 * b + a : e)];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            const int q = q0 + i * kSolveThreads;
+            if (q >= nblk * 49) break;
+            const int s = q / 49, e = q - 49 * s, a = e / 7, b = e - 7 * a;
+            double v = 0.0;
+#pragma unroll
+            for (int j = 0; j < kE; ++j) v += t[i][j];
+            for (int l = l0[i] + kE; l < l1[i]; ++l) {
+                const uint32_t f = entry(l);
+                v += A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + ((f & kEdgeTransposed) ? 7 * b + a : e)];
+            }
+            Lb[q] = S.si[s] == S.sj[s] ? v : -v;
+        }
+    }
+    // Right-hand side -g: g_i -= A^T g_e, g_j += A^T g_e.
+    for (int q = tid; q < 7 * nb; q += kSolveThreads) {
+        const int k = q / 7, a = q - 7 * k, s = S.colstart[k];
+        double v = 0.0;
+#pragma unroll 4
+        for (int l = S.estart[s]; l < S.estart[s + 1]; ++l) {
+            const uint32_t f = entry(l);
+            const double t = A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + 49 + a];
+            v += (f & kEdgeOwnI) ? t : -t;
+        }
+        S.xs[q] = v;
+    }
+    __syncthreads();
+    const int grp = tid >> 4, gl = tid & 15;
+    constexpr int kGroups = kSolveThreads / 16;
+    for (int lv = 0; lv < nlev; ++lv) {
+        const int k0 = S.lvl[lv], k1 = S.lvl[lv + 1];
+        const int s0 = S.colstart[k0], s1 = S.colstart[k1];
+        // 1. Products of earlier levels (the first level has none).
+        if (lv > 0) {
+            const int nb49 = 49 * (s1 - s0), nall = nb49 + 7 * (k1 - k0);
+            for (int q = tid; q < nall; q += kSolveThreads) {
+                if (q < nb49) {
+                    const int s = s0 + q / 49, e = q % 49, a = e / 7, b = e - 7 * a;
+                    const int u1 = S.ustart[s + 1];
+                    int u = S.ustart[s];
+                    if (u == u1) continue;
+                    double v = Lb[49 * s + e];
+                    for (; u < u1; ++u) {
+                        const uint32_t f = S.upd[u];
+                        const double* lx = Lb + 49 * (f & 0xffffu) + 7 * a;
+                        const double* lz = Lb + 49 * (f >> 16) + 7 * b;
+                        double t = 0.0;
+#pragma unroll
+                        for (int c = 0; c < 7; ++c) t += lx[c] * lz[c];
+                        v -= t;
+                    }
+                    Lb[49 * s + e] = v;
+                } else {
+                    const int k = k0 + (q - nb49) / 7, a = (q - nb49) % 7, s = S.colstart[k];
+                    const int u1 = S.ustart[s + 1];
+                    double v = S.xs[7 * k + a];
+                    for (int u = S.ustart[s]; u < u1; ++u) {
+                        const int sz = (int)(S.upd[u] & 0xffffu);
+                        const double* lz = Lb + 49 * sz + 7 * a;
+                        const double* y = S.xs + 7 * S.sj[sz];
+                        double t = 0.0;
+#pragma unroll
+                        for (int c = 0; c < 7; ++c) t += lz[c] * y[c];
+                        v -= t;
+                    }
+                    S.xs[7 * k + a] = v;
+                }
+            }
+            __syncthreads();
+        }
+        // 2. The level's columns.
+        for (int k = k0 + grp; k < k1; k += kGroups) {
+            double* Dk = Lb + 49 * S.colstart[k];
+            double L[7][7], Li[7][7], yk[7], isd[7];
+            bool bad = false;
+#pragma unroll
+            for (int j = 0; j < 7; ++j) {
+                double d = Dk[7 * j + j];
+#pragma unroll
+                for (int m = 0; m < j; ++m) d -= L[j][m] * L[j][m];
+                bad = bad || !(d > 0.0) || !isfinite(d);
+                // 1/sqrt(d): hardware estimate and two Newton steps (no fp64
+                // division or square root in the chain).
+                double is = __builtin_amdgcn_rsq(d);
+                is = is * fma(-0.5 * d * is, is, 1.5);
+                is = is * fma(-0.5 * d * is, is, 1.5);
+                L[j][j] = d * is;
+                isd[j] = is;
+#pragma unroll
+                for (int i = j + 1; i < 7; ++i) {
+                    double v = Dk[7 * i + j];
+#pragma unroll
+                    for (int m = 0; m < j; ++m) v -= L[i][m] * L[j][m];
+                    L[i][j] = v * is;
+                }
+            }
+            if (bad) {
+                S.bad = 1;
+                break;
+            }
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                Li[i][i] = isd[i];
+#pragma unroll
+                for (int j = 0; j < i; ++j) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int m = j; m < i; ++m) v += L[i][m] * Li[m][j];
+                    Li[i][j] = -v * Li[i][i];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 7; ++i) {
+                double v = 0.0;
+#pragma unroll
+                for (int m = 0; m <= i; ++m) v += Li[i][m] * S.xs[7 * k + m];
+                yk[i] = v;
+            }
+            // Panel rows: each lane reads its row before it writes it.
+            const int nrow = 7 * (S.colstart[k + 1] - S.colstart[k] - 1);
+            for (int q = gl; q < nrow; q += 16) {
+                double* row = Dk + 49 + 7 * q;  // the column's blocks follow its diagonal
+                double r[7], out[7];
+#pragma unroll
+                for (int c = 0; c < 7; ++c) r[c] = row[c];
+#pragma unroll
+                for (int b = 0; b < 7; ++b) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int c = 0; c <= b; ++c) v += r[c] * Li[b][c];
+                    out[b] = v;
+                }
+#pragma unroll
+                for (int b = 0; b < 7; ++b) row[b] = out[b];
+            }
+            // Every lane of the column (one wave holds it) has read the
+            // diagonal block and b_k by now.
+            if (gl == 0) {
+#pragma unroll
+                for (int i = 0; i < 7; ++i) {
+#pragma unroll
+                    for (int j = 0; j <= i; ++j) Dk[7 * i + j] = Li[i][j];
+                    S.xs[7 * k + i] = yk[i];
+                }
+            }
+        }
+        __syncthreads();
+        if (S.bad) {
+            if (tid == 0) A.state[0] = 1;
+            return;
+        }
+    }
+    // Backward substitution x_z = L_zz^-T (y_z - sum_x L_xz^T x_x): sixteen
+    // lanes per column, lane 8 h + c summing component c over every other block.
+    for (int lv = nlev - 1; lv >= 0; --lv) {
+        const int k0 = S.lvl[lv], k1 = S.lvl[lv + 1];
+        for (int kb = k0; kb < k1; kb += kGroups) {
+            const int k = kb + grp;
+            const bool on = k < k1;
+            const int c = gl & 7, h = gl >> 3;
+            const int sd = on ? S.colstart[k] : 0, n = on ? S.colstart[k + 1] - sd - 1 : 0;
+            double t = 0.0;
+            if (c < 7) {
+                for (int j = h; j < n; j += 2) {
+                    const double* blk = Lb + 49 * (sd + 1 + j) + c;
+                    const double* xx = S.xs + 7 * S.si[sd + 1 + j];
+#pragma unroll
+                    for (int a = 0; a < 7; ++a) t += blk[7 * a] * xx[a];
+                }
+            }
+            t += __shfl_xor(t, 8, 64);
+            const double w = on && c < 7 ? S.xs[7 * k + c] - t : 0.0;
+            double x = 0.0;
+#pragma unroll
+            for (int b = 0; b < 7; ++b) {
+                const double wb = __shfl(w, (tid & 48) + b, 64);
+                if (on && c <= b) x += Lb[49 * sd + 7 * b + min(c, 6)] * wb;
+            }
+            if (on && h == 0 && c < 7) S.xs[7 * k + c] = x;
+        }
+        __syncthreads();
+    }
+    apply_step<kSolveThreads>(A, S.xs, S.red, [&](int k) { return (int)S.pos[k]; });
+}
+
+// One launch per iteration, N workgroups.  Sparse: workgroup 0 solves and the
+// others return.  Dense: every workgroup assembles its block row, and the last
+// one to finish solves (its ticket tells; it resets the ticket for the next
+// iteration).
+__global__ void __launch_bounds__(kSolveThreads) backend_solve_kernel(BackendArgs A) {
+    constexpr size_t kSparse = sizeof(SparseLds<true>) > sizeof(SparseLds<false>) ? sizeof(SparseLds<true>) : sizeof(SparseLds<false>);
+    constexpr size_t kBytes = sizeof(DenseLds) > kSparse ? sizeof(DenseLds) : kSparse;
+    static_assert(sizeof(AssembleLds) <= kBytes && kBytes <= 163328, "LDS of a CU");
+    __shared__ __align__(16) char lds[kBytes];
+    __shared__ int last;
+    if (A.state[0]) return;
+    const int mode = A.state[2];
+    if (mode != kSolveDense) {
+        if (blockIdx.x != 0) return;
+        if (mode == kSolveLds) {
+            SparseLds<true>& S = *reinterpret_cast<SparseLds<true>*>(lds);
+            sparse_solve<true>(A, S, S.Lb);
+        } else {
+            sparse_solve<false>(A, *reinterpret_cast<SparseLds<false>*>(lds), A.M);
+        }
+        return;
+    }
+    assemble_row(A, (int)blockIdx.x, *reinterpret_cast<AssembleLds*>(lds));
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(A.state + 3, 1) == (int)gridDim.x - 1 ? 1 : 0;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    if (threadIdx.x == 0) A.state[3] = 0;
+    dense_solve(A, *reinterpret_cast<DenseLds*>(lds));
 }
 
 __global__ void __launch_bounds__(256) backend_finish_kernel(BackendArgs A) {
@@ -949,7 +1254,7 @@ __global__ void __launch_bounds__(256) backend_finish_kernel(BackendArgs A) {
 
 // Workspace layout.
 struct BackendLayout {
-    size_t T64, Trel, edge_sys, edge_blk, partials, state, stat, M, rhs, dinv, pat, row_start, total;
+    size_t T64, Trel, edge_sys, edge_blk, partials, state, stat, M, rhs, dinv, pat, elist, total;
 };
 
 int padded_dim(int N) { return (7 * (N - 1) + kTile - 1) / kTile * kTile; }
@@ -965,13 +1270,13 @@ BackendLayout backend_layout(int N, int HW, int E) {
     L.edge_sys = o; o = al(o + sizeof(double) * kStride * E);
     L.edge_blk = o; o = al(o + sizeof(double) * kBlk * E);
     L.partials = o; o = al(o + sizeof(float) * kStride * (size_t)bpe * E);
-    L.state = o;    o = al(o + sizeof(int32_t) * 3);
+    L.state = o;    o = al(o + sizeof(int32_t) * 4);
     L.stat = o;     o = al(o + sizeof(double) * 2);
     L.M = o;        o = al(o + sizeof(double) * np * np);
     L.rhs = o;      o = al(o + sizeof(double) * np);
     L.dinv = o;     o = al(o + sizeof(double) * np * kTile);
-    L.pat = o;      o = al(o + sizeof(uint32_t) * kPatWords * (size_t)N);
-    L.row_start = o; o = al(o + sizeof(int32_t) * (size_t)N);
+    L.pat = o;      o = al(o + sizeof(PatternBuf));
+    L.elist = o;    o = al(o + sizeof(uint32_t) * 3 * (size_t)E);
     L.total = o;
     return L;
 }
@@ -1010,14 +1315,14 @@ hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q,
     A.M = reinterpret_cast<double*>(w + L.M);
     A.rhs = reinterpret_cast<double*>(w + L.rhs);
     A.dinv = reinterpret_cast<double*>(w + L.dinv);
-    A.pat = reinterpret_cast<uint32_t*>(w + L.pat);
-    A.row_start = reinterpret_cast<int32_t*>(w + L.row_start);
+    A.pat = reinterpret_cast<PatternBuf*>(w + L.pat);
+    A.elist = reinterpret_cast<uint32_t*>(w + L.elist);
     A.T_out = T;
     A.info = info;
     const dim3 grid(A.blocks_per_edge, E);
     backend_init_kernel<<<(12 * N + 255) / 256, 256, 0, s>>>(T, A.T64, N, A.state, A.stat);
     backend_relpose_kernel<<<(E + 255) / 256, 256, 0, s>>>(A);
-    backend_pattern_kernel<<<1, kSpThreads, 0, s>>>(A);
+    backend_pattern_kernel<<<1, kPatThreads, 0, s>>>(A);
     for (int it = 0; it <= iters; ++it) {
         const int final_pass = it == iters ? 1 : 0;
         timer_begin("backend_accum", s);
@@ -1028,9 +1333,7 @@ hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q,
         timer_end(s);
         if (final_pass) break;
         timer_begin("backend_solve", s);
-        backend_assemble_kernel<<<N, kAsmThreads, 0, s>>>(A);
-        backend_sparse_solve_kernel<<<1, kSpThreads, 0, s>>>(A);
-        backend_solve_kernel<<<1, kSolveThreads, 0, s>>>(A);
+        backend_solve_kernel<<<N, kSolveThreads, 0, s>>>(A);
         timer_end(s);
     }
     backend_finish_kernel<<<(12 * N + 255) / 256, 256, 0, s>>>(A);
