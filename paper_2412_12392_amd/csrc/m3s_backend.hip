@@ -52,7 +52,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kSolveThreads = 512;
 constexpr int kVals = kPoseVals;
-constexpr int kStride = 40;         // floats per block partial, doubles per edge system
+constexpr int kStride = 40;         // doubles per edge system
 constexpr int kMaxDim = 7 * (M3S_MAX_KEYFRAMES - 1);  // largest reduced system
 constexpr int kPatWords = (M3S_MAX_KEYFRAMES + 31) / 32;  // bit words of a set of keyframes
 
@@ -88,15 +88,14 @@ struct BackendArgs {
     const int32_t* edges;     // [E*2] (i, j)
     const int32_t* idx;       // [E*HW]
     const uint8_t* valid;     // [E*HW]
-    double q_min;
-    float q_minf;
+    ConfGate gate;
     RobustWeights rw;
     double step_tol;
     double* T64;              // [N*12] world poses
     float* Trel;              // [E*12] T_ij = T_WC[i]^-1 T_WC[j] per edge at the current poses (zero out of range)
     double* edge_sys;         // [E*kStride] fp64 relative normal equations per edge
     double* edge_blk;         // [E*kBlk] A^T H_e A (49) and A^T g_e (7) per edge
-    float* partials;          // [E*blocks_per_edge*kStride]
+    float* partials;          // [E*blocks_per_edge*kMomentStride]
     int32_t* state;           // [0] done flag, [1] applied steps, [2] kSolve*, [3] dense assembly ticket
     double* stat;             // [0] last step norm
     double* M;                // [np*np] dense reduced Hessian, factored in place, or the sparse factor's blocks
@@ -109,7 +108,7 @@ struct BackendArgs {
 };
 
 constexpr int kBlk = 56;      // 49 + 7 doubles per edge
-constexpr int kMatchesPerLane = 16;  // amortises the workgroup reduction of the 37 sums
+constexpr int kMatchesPerLane = 16;  // amortises the workgroup reduction
 constexpr int kTile = 32;     // tile of the blocked Cholesky
 constexpr int kPanelRows = 416;  // panel rows kept in LDS (larger systems read the panel from memory)
 constexpr int kStageRows = 64;   // raw panel rows staged per step of the panel product
@@ -149,7 +148,7 @@ __global__ void __launch_bounds__(256) backend_relpose_kernel(BackendArgs A) {
 
 // final: 0 = an iteration's accumulation (skipped once the loop has ended), 1 = the final one.
 __global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A, int final_pass) {
-    __shared__ float red[kThreads / 64][kVals];
+    __shared__ float red[kThreads / 64][kMomentStride];
     if (!final_pass && A.state[0]) return;
     const int e = blockIdx.y;
     const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
@@ -157,9 +156,9 @@ __global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A, 
     float T[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k) T[k] = A.Trel[12 * e + k];
-    float acc[kVals];
+    float acc[kMoments];
 #pragma unroll
-    for (int k = 0; k < kVals; ++k) acc[k] = 0.f;
+    for (int k = 0; k < kMoments; ++k) acc[k] = 0.f;
 
     const long ebase = (long)e * A.HW;
     const float* Xi = A.Xc + (long)(edge_ok ? ei : 0) * A.HW * 3;
@@ -197,35 +196,23 @@ __global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A, 
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             float q;
-            if (ok[u] && confidence_gate(qi[u], qj[u], A.q_min, A.q_minf, q))
+            if (ok[u] && confidence_gate(qi[u], qj[u], A.gate, q))
                 accumulate_match(T, xj[u][0], xj[u][1], xj[u][2], xi[u][0], xi[u][1], xi[u][2], q, A.rw, acc);
         }
     }
 
-#pragma unroll
-    for (int k = 0; k < kVals; ++k) acc[k] = wave_sum(acc[k]);
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int k = 0; k < kVals; ++k) red[threadIdx.x >> 6][k] = acc[k];
-    }
-    __syncthreads();
-    if (threadIdx.x < kVals) {
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) v += red[w][threadIdx.x];
-        A.partials[((size_t)e * A.blocks_per_edge + blockIdx.x) * kStride + threadIdx.x] = v;
-    }
+    block_moments<kThreads>(acc, red, A.partials + ((size_t)e * A.blocks_per_edge + blockIdx.x) * kMomentStride);
 }
 
 // One workgroup per edge: fixed-order fp64 sum of the edge's partials; then
 // (iterations only) A = Ad(T_WC[i]^-1), A^T H_e A and A^T g_e.
 __global__ void __launch_bounds__(kThreads) backend_edge_kernel(BackendArgs A, int final_pass) {
     __shared__ double sys[kStride];
-    __shared__ double part[kThreads / kVals * kVals];
+    __shared__ SumLds<kThreads> part;
     __shared__ double Ad[49];
     if (!final_pass && A.state[0]) return;
     const int e = blockIdx.x;
-    sum_partials<kThreads>(A.partials + (size_t)e * A.blocks_per_edge * kStride, A.blocks_per_edge, kStride, part, sys);
+    sum_partials<kThreads>(A.partials + (size_t)e * A.blocks_per_edge * kMomentStride, A.blocks_per_edge, part, sys);
     if (threadIdx.x < kVals) A.edge_sys[(size_t)e * kStride + threadIdx.x] = sys[threadIdx.x];
     if (final_pass) return;
     const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
@@ -1269,7 +1256,7 @@ BackendLayout backend_layout(int N, int HW, int E) {
     L.Trel = o;     o = al(o + sizeof(float) * 12 * E);
     L.edge_sys = o; o = al(o + sizeof(double) * kStride * E);
     L.edge_blk = o; o = al(o + sizeof(double) * kBlk * E);
-    L.partials = o; o = al(o + sizeof(float) * kStride * (size_t)bpe * E);
+    L.partials = o; o = al(o + sizeof(float) * kMomentStride * (size_t)bpe * E);
     L.state = o;    o = al(o + sizeof(int32_t) * 4);
     L.stat = o;     o = al(o + sizeof(double) * 2);
     L.M = o;        o = al(o + sizeof(double) * np * np);
@@ -1301,8 +1288,7 @@ hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q,
     A.n = 7 * (N - 1);
     A.np = padded_dim(N);
     A.Xc = Xc; A.Q = Q; A.edges = edges; A.idx = idx; A.valid = valid;
-    A.q_min = (double)q_min;
-    A.q_minf = q_min;
+    A.gate = conf_gate(q_min);
     A.rw = robust_weights(sigma_ray, sigma_dist, huber);
     A.step_tol = step_tol;
     A.T64 = reinterpret_cast<double*>(w + L.T64);

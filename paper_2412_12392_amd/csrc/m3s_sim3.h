@@ -9,46 +9,72 @@
 
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stdint.h>
 
 namespace m3s {
 
-// Number of accumulated values per match set: the upper triangle of the 7x7
+// Number of normal-equation values of a match set: the upper triangle of the 7x7
 // J^T W J (28, rows of 7, 6, ..., 1), J^T W r (7), robust cost, match count.
 constexpr int kPoseVals = 28 + 7 + 2;
+// What the matches are summed into: 30 moments that determine those values
+// (accumulate_match), kept in rows of 32 floats.
+constexpr int kMoments = 30;
+constexpr int kMomentStride = 32;
 
 __device__ __forceinline__ constexpr int upper_index(int a, int b) { return a * 7 - a * (a - 1) / 2 + (b - a); }
 
-// Huber weight and cost of a whitened norm a with the given width.
-__device__ __forceinline__ float huber_weight(float a, float width) { return a <= width ? 1.f : width / a; }
-__device__ __forceinline__ float huber_cost(float a, float width) {
-    return a <= width ? 0.5f * a * a : width * (a - 0.5f * width);
-}
-
-// Weights of the two residual blocks: 1 / sigma^2 and 1 / sigma (0 drops the
-// residual), and the Huber width.
+// Weights of the two residual blocks: 1 / sigma^2 (0 drops the residual), and
+// the Huber width.
 struct RobustWeights {
-    float w_ray, w_dist, is_ray, is_dist, huber;
+    float w_ray, w_dist, huber;
 };
 
 inline RobustWeights robust_weights(float sigma_ray, float sigma_dist, float huber) {
     RobustWeights w;
     w.w_ray = isinf(sigma_ray) ? 0.f : 1.f / (sigma_ray * sigma_ray);
     w.w_dist = isinf(sigma_dist) ? 0.f : 1.f / (sigma_dist * sigma_dist);
-    w.is_ray = isinf(sigma_ray) ? 0.f : 1.f / sigma_ray;
-    w.is_dist = isinf(sigma_dist) ? 0.f : 1.f / sigma_dist;
     w.huber = huber;
     return w;
 }
 
 // Confidence gate of a match (Sec. 3.3): q = sqrt(Qa Qb) > q_min, decided
 // exactly as in fp64 (the product of two fp32 values is exact there).  The
-// fp32 root is within 2 ulp of the exact one, so outside a relative band of
-// 1e-5 around q_min its comparison gives the fp64 answer; inside the band the
-// fp64 root decides.  Writes the fp32 confidence to q.
-__device__ __forceinline__ bool confidence_gate(float Qa, float Qb, double q_min, float q_minf, float& q) {
-    q = sqrtf(Qa * Qb);
-    if (fabsf(q - q_minf) > 1e-5f * q_minf) return q > q_minf;
-    return sqrt((double)Qa * (double)Qb) > q_min;
+// fp32 product is within 2^-24 of the exact one, so outside the relative band
+// [lo, hi] = q_min^2 (1 -+ 1e-5) it gives the fp64 answer; inside the band the
+// fp64 root decides.  A q_min whose square leaves the normal fp32 range by a
+// wide margin, or is not positive, has an unbounded band.
+struct ConfGate {
+    double q_min;
+    float lo, hi;
+};
+
+inline ConfGate conf_gate(float q_min) {
+    ConfGate g;
+    g.q_min = (double)q_min;
+    const bool banded = q_min > 1e-15f && q_min < 1e15f;
+    g.lo = banded ? (float)(g.q_min * g.q_min * (1.0 - 1e-5)) : -INFINITY;
+    g.hi = banded ? (float)(g.q_min * g.q_min * (1.0 + 1e-5)) : INFINITY;
+    return g;
+}
+
+// Writes the fp32 confidence to q.
+__device__ __forceinline__ bool confidence_gate(float Qa, float Qb, const ConfGate& g, float& q) {
+    const float p = Qa * Qb;
+    q = __builtin_amdgcn_sqrtf(p);
+    if (p > g.hi) return true;
+    if (p < g.lo) return false;
+    const double e = sqrt((double)Qa * (double)Qb);
+    q = (float)e;
+    return e > g.q_min;
+}
+
+// 1 / |x| and |x| from n2 = |x|^2 (positive, finite, not subnormal): the
+// hardware reciprocal root, and one Newton step on n2 / |x| that makes |x| as
+// good as a rounded root.
+__device__ __forceinline__ void norm_of(float n2, float& id, float& d) {
+    id = __builtin_amdgcn_rsqf(n2);
+    d = n2 * id;
+    d = fmaf(0.5f * id, fmaf(-d, d, n2), d);
 }
 
 // One match: x = T X (X the point that moves with the pose), Y the measured
@@ -63,116 +89,170 @@ __device__ __forceinline__ bool confidence_gate(float Qa, float Qb, double q_min
 //   H_vv = ar I + (wd - ar) u u^T   H_vw = -ar [x]_x   H_vs = wd d u
 //   H_ww = wr P                     H_ws = 0           H_ss = wd d^2
 //   g_v  = wr P e / d + wd rd u     g_w = wr u x e     g_s  = wd rd d
-// which is what is added to acc (upper triangle of H by rows, then g, the
-// robust cost and the count).  Returns false, adding nothing, for a point at
-// the origin or non-finite.
-__device__ __forceinline__ bool accumulate_match(const float* T, float X0, float X1, float X2, float Y0, float Y1,
-                                                 float Y2, float q, const RobustWeights& rw, float* acc) {
-    const float x0 = T[0] * X0 + T[1] * X1 + T[2] * X2 + T[3];
-    const float x1 = T[4] * X0 + T[5] * X1 + T[6] * X2 + T[7];
-    const float x2 = T[8] * X0 + T[9] * X1 + T[10] * X2 + T[11];
-    const float d = sqrtf(x0 * x0 + x1 * x1 + x2 * x2);
-    const float dy = sqrtf(Y0 * Y0 + Y1 * Y1 + Y2 * Y2);
-    if (!(d > 0.f) || !(dy > 0.f) || !isfinite(d) || !isfinite(dy)) return false;
-    const float id = __builtin_amdgcn_rcpf(d), idy = __builtin_amdgcn_rcpf(dy);
+// so 30 moments hold all of it, and expand_moments forms the 37 values once
+// the sums are in fp64:
+//   0 ar   1-6 (wd - ar) u u^T (upper)   7-9 ar x   10-12 wd d u   13 wr
+//   14-19 wr u u^T (upper)   20 wd d^2   21-27 g   28 robust cost   29 count
+// A pose solve is bound by vector issue here (its operands come from L2): the
+// 37 sums with correctly rounded roots took about 240 instructions a match and
+// 89 us for 65 edges at 512 x 384, this about 140 and 68 us.
+// Adds nothing for a point at the origin or non-finite.
+__device__ __forceinline__ void accumulate_match(const float* T, float X0, float X1, float X2, float Y0, float Y1,
+                                                 float Y2, float q, const RobustWeights& rw, float* m) {
+    const float x0 = fmaf(T[0], X0, fmaf(T[1], X1, fmaf(T[2], X2, T[3])));
+    const float x1 = fmaf(T[4], X0, fmaf(T[5], X1, fmaf(T[6], X2, T[7])));
+    const float x2 = fmaf(T[8], X0, fmaf(T[9], X1, fmaf(T[10], X2, T[11])));
+    const float n2 = fmaf(x0, x0, fmaf(x1, x1, x2 * x2)), ny2 = fmaf(Y0, Y0, fmaf(Y1, Y1, Y2 * Y2));
+    if (!(n2 > 0.f && n2 < INFINITY && ny2 > 0.f && ny2 < INFINITY)) return;
+    float id, d, idy, dy;
+    norm_of(n2, id, d);
+    norm_of(ny2, idy, dy);
+    // The hardware flushes a subnormal square (a norm below 1.1e-19).
+    if (__builtin_expect(fminf(n2, ny2) < 1.17549435e-38f, 0)) {
+        d = sqrtf(n2);
+        dy = sqrtf(ny2);
+        id = 1.0f / d;
+        idy = 1.0f / dy;
+    }
     const float u0 = x0 * id, u1 = x1 * id, u2 = x2 * id;
-    const float e0 = u0 - Y0 * idy, e1 = u1 - Y1 * idy, e2 = u2 - Y2 * idy, rd = d - dy;
-    const float sq = sqrtf(q);
-    const float a_ray = sqrtf(e0 * e0 + e1 * e1 + e2 * e2) * sq * rw.is_ray;
-    const float a_dist = fabsf(rd) * sq * rw.is_dist;
-    const float hr = a_ray <= rw.huber ? 1.f : rw.huber * __builtin_amdgcn_rcpf(a_ray);
-    const float hd = a_dist <= rw.huber ? 1.f : rw.huber * __builtin_amdgcn_rcpf(a_dist);
-    const float wr = q * rw.w_ray * hr;
-    const float wd = q * rw.w_dist * hd;
-    const float ar = wr * id * id;
-    const float cv = wd - ar;
-    const float wdd = wd * d;
-    // H_vv, H_vw, H_vs (rows 0..2)
-    acc[upper_index(0, 0)] += ar + cv * u0 * u0;
-    acc[upper_index(0, 1)] += cv * u0 * u1;
-    acc[upper_index(0, 2)] += cv * u0 * u2;
-    acc[upper_index(0, 4)] += ar * x2;
-    acc[upper_index(0, 5)] -= ar * x1;
-    acc[upper_index(0, 6)] += wdd * u0;
-    acc[upper_index(1, 1)] += ar + cv * u1 * u1;
-    acc[upper_index(1, 2)] += cv * u1 * u2;
-    acc[upper_index(1, 3)] -= ar * x2;
-    acc[upper_index(1, 5)] += ar * x0;
-    acc[upper_index(1, 6)] += wdd * u1;
-    acc[upper_index(2, 2)] += ar + cv * u2 * u2;
-    acc[upper_index(2, 3)] += ar * x1;
-    acc[upper_index(2, 4)] -= ar * x0;
-    acc[upper_index(2, 6)] += wdd * u2;
-    // H_ww (rows 3..5), H_ss
-    acc[upper_index(3, 3)] += wr - wr * u0 * u0;
-    acc[upper_index(3, 4)] -= wr * u0 * u1;
-    acc[upper_index(3, 5)] -= wr * u0 * u2;
-    acc[upper_index(4, 4)] += wr - wr * u1 * u1;
-    acc[upper_index(4, 5)] -= wr * u1 * u2;
-    acc[upper_index(5, 5)] += wr - wr * u2 * u2;
-    acc[upper_index(6, 6)] += wdd * d;
-    // g
-    const float ue = u0 * e0 + u1 * e1 + u2 * e2;
-    const float wri = wr * id, wdr = wd * rd;
-    acc[28] += wri * (e0 - u0 * ue) + wdr * u0;
-    acc[29] += wri * (e1 - u1 * ue) + wdr * u1;
-    acc[30] += wri * (e2 - u2 * ue) + wdr * u2;
-    acc[31] += wr * (u1 * e2 - u2 * e1);
-    acc[32] += wr * (u2 * e0 - u0 * e2);
-    acc[33] += wr * (u0 * e1 - u1 * e0);
-    acc[34] += wdr * d;
-    acc[35] += huber_cost(a_ray, rw.huber) + huber_cost(a_dist, rw.huber);
-    acc[36] += 1.f;
-    return true;
+    const float e0 = fmaf(-Y0, idy, u0), e1 = fmaf(-Y1, idy, u1), e2 = fmaf(-Y2, idy, u2), rd = d - dy;
+    // Whitened norms a, Huber weights min(1, width / a), and Huber costs
+    // c (a - c / 2) with c = min(a, width).
+    const float qr = q * rw.w_ray, qd = q * rw.w_dist;
+    const float a_ray = __builtin_amdgcn_sqrtf(fmaf(e0, e0, fmaf(e1, e1, e2 * e2)) * qr);
+    const float a_dist = fabsf(rd) * __builtin_amdgcn_sqrtf(qd);
+    const float wr = qr * fminf(1.f, rw.huber * __builtin_amdgcn_rcpf(a_ray));
+    const float wd = qd * fminf(1.f, rw.huber * __builtin_amdgcn_rcpf(a_dist));
+    const float c_ray = fminf(a_ray, rw.huber), c_dist = fminf(a_dist, rw.huber);
+    const float wri = wr * id, ar = wri * id, cv = wd - ar, wdd = wd * d, wdr = wd * rd;
+    m[0] += ar;
+    const float cu0 = cv * u0, cu1 = cv * u1, cu2 = cv * u2;
+    m[1] = fmaf(cu0, u0, m[1]);
+    m[2] = fmaf(cu0, u1, m[2]);
+    m[3] = fmaf(cu0, u2, m[3]);
+    m[4] = fmaf(cu1, u1, m[4]);
+    m[5] = fmaf(cu1, u2, m[5]);
+    m[6] = fmaf(cu2, u2, m[6]);
+    m[7] = fmaf(ar, x0, m[7]);
+    m[8] = fmaf(ar, x1, m[8]);
+    m[9] = fmaf(ar, x2, m[9]);
+    m[10] = fmaf(wdd, u0, m[10]);
+    m[11] = fmaf(wdd, u1, m[11]);
+    m[12] = fmaf(wdd, u2, m[12]);
+    m[13] += wr;
+    const float wu0 = wr * u0, wu1 = wr * u1, wu2 = wr * u2;
+    m[14] = fmaf(wu0, u0, m[14]);
+    m[15] = fmaf(wu0, u1, m[15]);
+    m[16] = fmaf(wu0, u2, m[16]);
+    m[17] = fmaf(wu1, u1, m[17]);
+    m[18] = fmaf(wu1, u2, m[18]);
+    m[19] = fmaf(wu2, u2, m[19]);
+    m[20] = fmaf(wdd, d, m[20]);
+    const float ue = fmaf(u0, e0, fmaf(u1, e1, u2 * e2));
+    m[21] = fmaf(wri, fmaf(-u0, ue, e0), fmaf(wdr, u0, m[21]));
+    m[22] = fmaf(wri, fmaf(-u1, ue, e1), fmaf(wdr, u1, m[22]));
+    m[23] = fmaf(wri, fmaf(-u2, ue, e2), fmaf(wdr, u2, m[23]));
+    m[24] = fmaf(wu1, e2, fmaf(-wu2, e1, m[24]));
+    m[25] = fmaf(wu2, e0, fmaf(-wu0, e2, m[25]));
+    m[26] = fmaf(wu0, e1, fmaf(-wu1, e0, m[26]));
+    m[27] = fmaf(wdr, d, m[27]);
+    m[28] = fmaf(c_ray, fmaf(-0.5f, c_ray, a_ray), fmaf(c_dist, fmaf(-0.5f, c_dist, a_dist), m[28]));
+    m[29] += 1.f;
 }
 
-// Fixed-order fp64 sum of nparts fp32 partials of kPoseVals values each
-// (stride `stride` floats) by a workgroup of NT threads: G = NT / kPoseVals
-// groups of kPoseVals threads, thread (g, v) adding value v of the partials
-// g, g + G, g + 2G, ... in that order (a group's reads of one partial are
-// contiguous, and every group's reads are in flight together); then thread v
-// adds the G group sums in group order.  `part` is LDS of G * kPoseVals
-// doubles; the sums land in out[0 .. kPoseVals) (LDS), visible to the whole
-// workgroup on return.
+// Value v of the normal equations (kPoseVals) from the summed moments.
+__device__ __forceinline__ double pose_value(const double* m, int v) {
+    // Per value: moment of a (or -1), moment of b (or -1), a + sign b.
+    constexpr int8_t kA[kPoseVals] = {0, 2, 3, -1, 9, -1, 10,  0, 5, -1, -1, 7, 11,  0, 8, -1, -1, 12,
+                                      13, -1, -1, -1,  13, -1, -1,  13, -1,  20,
+                                      21, 22, 23, 24, 25, 26, 27, 28, 29};
+    constexpr int8_t kB[kPoseVals] = {1, -1, -1, -1, -1, 8, -1,  4, -1, 9, -1, -1, -1,  6, -1, 7, -1, -1,
+                                      14, 15, 16, -1,  17, 18, -1,  19, -1,  -1,
+                                      -1, -1, -1, -1, -1, -1, -1, -1, -1};
+    // H_vv adds its second moment; H_vw and H_ww subtract it.
+    const bool plus = v == upper_index(0, 0) || v == upper_index(1, 1) || v == upper_index(2, 2);
+    const double a = kA[v] >= 0 ? m[kA[v]] : 0.0, b = kB[v] >= 0 ? m[kB[v]] : 0.0;
+    return plus ? a + b : a - b;
+}
+
+// Fixed-order fp64 sum of nparts fp32 rows of kMoments values (kMomentStride
+// floats each) by a workgroup of NT threads, and the normal equations they
+// give: G = NT / 32 groups of 32 threads, thread (g, v) adding value v of the
+// rows g, g + G, g + 2G, ... in that order (a group reads whole rows, and
+// every group's reads are in flight together); then thread v adds the G group
+// sums in group order.  The kPoseVals values land in out (LDS), visible to the
+// whole workgroup on return.
 template <int NT>
-__device__ void sum_partials(const float* __restrict__ parts, int nparts, int stride, double* part, double* out) {
-    constexpr int G = NT / kPoseVals;
-    static_assert(G >= 1, "one thread per value at least");
-    const int t = threadIdx.x, g = t / kPoseVals, v = t - g * kPoseVals;
-    if (g < G) {
-        double acc = 0.0;
+struct SumLds {
+    double part[NT];
+    double mom[kMomentStride];
+};
+
+template <int NT>
+__device__ void sum_partials(const float* __restrict__ parts, int nparts, SumLds<NT>& S, double* out) {
+    constexpr int G = NT / kMomentStride;
+    const int t = threadIdx.x, g = t / kMomentStride, v = t % kMomentStride;
+    double acc = 0.0;
 #pragma unroll 8
-        for (int b = g; b < nparts; b += G) acc += (double)parts[(size_t)b * stride + v];
-        part[g * kPoseVals + v] = acc;
-    }
+    for (int b = g; b < nparts; b += G) acc += (double)parts[(size_t)b * kMomentStride + v];
+    S.part[t] = acc;
     __syncthreads();
-    if (t < kPoseVals) {
+    if (t < kMomentStride) {
         double s = 0.0;
 #pragma unroll
-        for (int k = 0; k < G; ++k) s += part[k * kPoseVals + t];
-        out[t] = s;
+        for (int k = 0; k < G; ++k) s += S.part[k * kMomentStride + t];
+        S.mom[t] = s;
     }
+    __syncthreads();
+    if (t < kPoseVals) out[t] = pose_value(S.mom, t);
     __syncthreads();
 }
 
-// Sum over the 64 lanes of a wave (every lane active), in every lane: DPP quad
-// swaps, half-row and row mirrors give each row's sum in its lanes, then the
-// four row sums are added in a fixed order.
 template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+__device__ __forceinline__ float dpp_add(float x) {
+    return x + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-    v += dpp_move<0xB1>(v);   // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);   // quad_perm [2,3,0,1]
-    v += dpp_move<0x141>(v);  // row_half_mirror
-    v += dpp_move<0x140>(v);  // row_mirror
-    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0));
-    const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 16));
-    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32));
-    const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 48));
-    return (r0 + r1) + (r2 + r3);
+// Sums of a workgroup's moments (m, every lane active) to row[0 .. 32), in a
+// fixed order.  Two swaps across the wave's halves and rows leave each of the
+// four 16-lane rows with a quarter of the moments, so the sums within a row
+// are formed for four moments at once (80 instructions a wave; 37 full
+// wave sums took about 400).  red: LDS of NT / 64 rows.
+template <int NT>
+__device__ __forceinline__ void block_moments(const float* m, float (*red)[kMomentStride], float* __restrict__ row) {
+    float h[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const uint32_t a = __builtin_bit_cast(uint32_t, m[i]);
+        const uint32_t b = i + 16 < kMoments ? __builtin_bit_cast(uint32_t, m[i + 16]) : 0u;
+        const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        h[i] = __builtin_bit_cast(float, (uint32_t)s[0]) + __builtin_bit_cast(float, (uint32_t)s[1]);
+    }
+    // h[i]: moment i in the lower half wave, i + 16 in the upper one.
+    float r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, h[i]),
+                                                        __builtin_bit_cast(uint32_t, h[i + 8]), false, false);
+        r[i] = __builtin_bit_cast(float, (uint32_t)s[0]) + __builtin_bit_cast(float, (uint32_t)s[1]);
+    }
+    // r[i]: moment i + 8 j in row j of the wave.
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        r[i] = dpp_add<0xB1>(r[i]);   // quad_perm [1,0,3,2]
+        r[i] = dpp_add<0x4E>(r[i]);   // quad_perm [2,3,0,1]
+        r[i] = dpp_add<0x141>(r[i]);  // row_half_mirror
+        r[i] = dpp_add<0x140>(r[i]);  // row_mirror
+        if ((lane & 15) == 0) red[wave][i + 8 * (lane >> 4)] = r[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < kMomentStride) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) v += red[w][threadIdx.x];
+        row[threadIdx.x] = v;
+    }
 }
 
 // Scale of a similarity [sR | t]: the cube root of det(sR).

@@ -16,8 +16,8 @@
 //           (the small-weight distance term); Jacobians w.r.t. a left
 //           perturbation (Supp. A); weights q / sigma^2 (match confidence q =
 //           sqrt(Qf[m] Qk[n]) gated at q_min, Sec. 3.3) times the Huber weight
-//           of the whitened block norm; one fp32 partial of J^T W J (upper
-//           triangle), J^T W r, robust cost and count per workgroup.
+//           of the whitened block norm; one fp32 row of the moments that give
+//           J^T W J, J^T W r, robust cost and count per workgroup.
 //   final   one workgroup: the last partials summed (cost and count at the
 //           final pose), the fp32 pose and the statistics written.
 //
@@ -40,14 +40,13 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kVals = kPoseVals;
-constexpr int kStride = 40;         // floats per block partial
 constexpr int kMaxBlocks = 2048;
 
 // Workspace layout (bytes): poses, statistics, counters, then the partials.
 constexpr size_t kOffT = 0;         // double[2][12]: pose by iteration parity
 constexpr size_t kOffStat = 192;    // double[2]: last step norm, reserved
 constexpr size_t kOffCnt = 224;     // int32[2]: reserved, solved iterations
-constexpr size_t kOffPart = 256;    // float[2][nblocks * kStride]: partials by iteration parity
+constexpr size_t kOffPart = 256;    // float[2][nblocks * kMomentStride]: partials by iteration parity
 
 struct TrackArgs {
     int N;
@@ -57,14 +56,13 @@ struct TrackArgs {
     const uint8_t* valid;
     const float* Qf;
     const float* Qk;
-    double q_min;
-    float q_minf;
+    ConfGate gate;
     RobustWeights rw;
     double* T64;            // [2][12]
     double* stat;
     int32_t* counter;       // [0] reserved, [1] solved iterations
     int32_t* solved;
-    float* partials;        // [2][nb * kStride]
+    float* partials;        // [2][nb * kMomentStride]
     int nb;
     float* T_out;
     float* info;
@@ -123,15 +121,15 @@ __device__ bool solve_and_update(const double* sum, double* T, double* step_norm
 }
 
 // Normal equations of the matches of this workgroup at the current pose: one
-// fp32 partial of kVals values per workgroup.
+// fp32 row of moments per workgroup.
 // Matches per lane and step of the accumulation: their reads are issued
 // together before the arithmetic.
 constexpr int kMatchesPerLane = 4;
 
 __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int it) {
-    __shared__ float red[kThreads / 64][kVals];
+    __shared__ float red[kThreads / 64][kMomentStride];
     __shared__ double sum[kVals];
-    __shared__ double part[kThreads / kVals * kVals];
+    __shared__ SumLds<kThreads> part;
     __shared__ double Tn[12];
     // Pose of the previous iteration (parity buffer); iteration 0 starts from
     // the initial pose in buffer 0.
@@ -139,7 +137,7 @@ __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int i
     if (it > 0) {
         // Iteration it - 1's system: the same fixed-order sum and solve in
         // every workgroup.
-        sum_partials<kThreads>(A.partials + (size_t)((it + 1) & 1) * A.nb * kStride, A.nb, kStride, part, sum);
+        sum_partials<kThreads>(A.partials + (size_t)((it + 1) & 1) * A.nb * kMomentStride, A.nb, part, sum);
         if (threadIdx.x == 0) {
             double Tl[12], step;
             for (int j = 0; j < 12; ++j) Tl[j] = Tprev[j];
@@ -161,9 +159,9 @@ __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int i
     float T[12];
 #pragma unroll
     for (int i = 0; i < 12; ++i) T[i] = (float)Tn[i];
-    float acc[kVals];
+    float acc[kMoments];
 #pragma unroll
-    for (int i = 0; i < kVals; ++i) acc[i] = 0.f;
+    for (int i = 0; i < kMoments; ++i) acc[i] = 0.f;
 
     constexpr int kStep = kThreads * kMatchesPerLane;
     for (int base = blockIdx.x * kStep + threadIdx.x; base < A.N; base += gridDim.x * kStep) {
@@ -187,33 +185,20 @@ __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int i
 #pragma unroll
         for (int u = 0; u < kMatchesPerLane; ++u) {
             float q;
-            if (ok[u] && confidence_gate(qf[u], qk[u], A.q_min, A.q_minf, q))
+            if (ok[u] && confidence_gate(qf[u], qk[u], A.gate, q))
                 accumulate_match(T, xf[u][0], xf[u][1], xf[u][2], xk[u][0], xk[u][1], xk[u][2], q, A.rw, acc);
         }
     }
 
-    // Block partial: wave sums, then the four waves through LDS.
-#pragma unroll
-    for (int i = 0; i < kVals; ++i) acc[i] = wave_sum(acc[i]);
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int i = 0; i < kVals; ++i) red[threadIdx.x >> 6][i] = acc[i];
-    }
-    __syncthreads();
-    if (threadIdx.x < kVals) {
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) v += red[w][threadIdx.x];
-        A.partials[((size_t)(it & 1) * A.nb + blockIdx.x) * kStride + threadIdx.x] = v;
-    }
+    block_moments<kThreads>(acc, red, A.partials + ((size_t)(it & 1) * A.nb + blockIdx.x) * kMomentStride);
 }
 
 // One workgroup: the last iteration's partials summed (cost and count at the
 // final pose), the fp32 pose and the statistics written.
 __global__ void __launch_bounds__(kThreads) track_final_kernel(TrackArgs A, int it) {
     __shared__ double sum[kVals];
-    __shared__ double part[kThreads / kVals * kVals];
-    sum_partials<kThreads>(A.partials + (size_t)(it & 1) * A.nb * kStride, A.nb, kStride, part, sum);
+    __shared__ SumLds<kThreads> part;
+    sum_partials<kThreads>(A.partials + (size_t)(it & 1) * A.nb * kMomentStride, A.nb, part, sum);
     if (threadIdx.x != 0) return;
     const double* T = A.T64 + 12 * (it & 1);
     for (int j = 0; j < 12; ++j) A.T_out[j] = (float)T[j];
@@ -286,7 +271,7 @@ int track_blocks(int N) {
     return nb < 1 ? 1 : (nb > kMaxBlocks ? kMaxBlocks : nb);
 }
 
-size_t track_workspace_bytes(int N) { return kOffPart + 2 * (size_t)track_blocks(N) * kStride * sizeof(float); }
+size_t track_workspace_bytes(int N) { return kOffPart + 2 * (size_t)track_blocks(N) * kMomentStride * sizeof(float); }
 
 hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* idx, const uint8_t* valid,
                         const float* Qf, const float* Qk, float q_min, float sigma_ray, float sigma_dist, float huber,
@@ -295,8 +280,7 @@ hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* 
     TrackArgs A;
     A.N = N;
     A.Xk = Xk; A.Xf = Xf; A.idx = idx; A.valid = valid; A.Qf = Qf; A.Qk = Qk;
-    A.q_min = (double)q_min;
-    A.q_minf = q_min;
+    A.gate = conf_gate(q_min);
     // An infinite sigma drops its residual from the system and the cost.
     A.rw = robust_weights(sigma_ray, sigma_dist, huber);
     A.T64 = reinterpret_cast<double*>(w + kOffT);
