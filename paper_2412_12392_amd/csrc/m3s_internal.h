@@ -79,7 +79,7 @@ hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* 
 hipError_t launch_fuse(int N, const float* T, float* Xc, float* Cc, const float* X, const float* C, hipStream_t s);
 
 // Backend Gauss-Newton (m3s_backend.hip).
-int backend_blocks_per_edge(int HW);
+int backend_blocks_per_edge(int HW, int E);
 size_t backend_workspace_bytes(int N, int HW, int E);
 hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q, const int32_t* edges,
                           const int32_t* idx, const uint8_t* valid, float q_min, float sigma_ray, float sigma_dist,
