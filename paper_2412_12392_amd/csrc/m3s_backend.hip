@@ -56,7 +56,7 @@ constexpr int kStride = 40;         // doubles per edge system
 constexpr int kMaxDim = 7 * (M3S_MAX_KEYFRAMES - 1);  // largest reduced system
 constexpr int kPatWords = (M3S_MAX_KEYFRAMES + 31) / 32;  // bit words of a set of keyframes
 
-// The factor's block structure (backend_pattern_kernel), in elimination order:
+// The factor's block structure (backend_start_kernel), in elimination order:
 // position k holds keyframe node perm[k] + 1.  Blocks of L are stored by
 // column, the diagonal first, so that a level's blocks are consecutive slots.
 constexpr int kLdsBlocks = 320;      // blocks of L in LDS: 320 x 392 B = 122.5 KB
@@ -115,36 +115,25 @@ constexpr int kPanelRows = 416;  // panel rows kept in LDS (larger systems read 
 constexpr int kStageRows = 64;   // raw panel rows staged per step of the panel product
 constexpr int kPanelStride = kTile + 1;  // odd stride in doubles: rows of a wave fall in different banks
 
-__global__ void __launch_bounds__(256) backend_init_kernel(const float* __restrict__ T_in, double* __restrict__ T64,
-                                                           int N, int32_t* __restrict__ state,
-                                                           double* __restrict__ stat) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < 12 * N) T64[t] = (double)T_in[t];
-    if (t < 4) state[t] = 0;
-    if (t < 2) stat[t] = 0.0;
-}
-
 __device__ __forceinline__ bool edge_in_range(int ei, int ej, int N) {
     return ei >= 0 && ei < N && ej >= 0 && ej < N;
 }
 
-// T_ij of edge e in fp32 from the fp64 world poses (zero for an edge out of range).
-__device__ __forceinline__ void write_relative_pose(const BackendArgs& A, int e) {
+// T_ij of edge e in fp32 from the fp64 world poses (zero for an edge out of
+// range); pose(k, j) is element j of keyframe k's pose.
+template <class Pose>
+__device__ __forceinline__ void write_relative_pose(const BackendArgs& A, int e, Pose pose) {
     const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
-    double Ti[12], Tij[12];
+    double Wi[12], Wj[12], Ti[12], Tij[12];
     if (edge_in_range(ei, ej, A.N)) {
-        sim3_inverse(A.T64 + 12 * ei, Ti);
-        sim3_mul(Ti, A.T64 + 12 * ej, Tij);
+        for (int k = 0; k < 12; ++k) Wi[k] = pose(ei, k);
+        for (int k = 0; k < 12; ++k) Wj[k] = pose(ej, k);
+        sim3_inverse(Wi, Ti);
+        sim3_mul(Ti, Wj, Tij);
     } else {
         for (int k = 0; k < 12; ++k) Tij[k] = 0.0;
     }
     for (int k = 0; k < 12; ++k) A.Trel[12 * e + k] = (float)Tij[k];
-}
-
-// Relative poses at the initial world poses, one thread per edge.
-__global__ void __launch_bounds__(256) backend_relpose_kernel(BackendArgs A) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < A.E) write_relative_pose(A, e);
 }
 
 // Loads of four neighbouring pixels: whole vectors at any alignment (gfx950
@@ -390,7 +379,8 @@ __device__ __forceinline__ void apply_step(const BackendArgs& A, const double* x
         for (int j = 0; j < 12; ++j) A.T64[12 * k + j] = Tn[j];
     }
     __syncthreads();
-    for (int e = tid; e < A.E; e += NT) write_relative_pose(A, e);
+    for (int e = tid; e < A.E; e += NT)
+        write_relative_pose(A, e, [&](int k, int j) { return A.T64[12 * k + j]; });
     double sq = 0.0;
     for (int k = tid; k < A.n; k += NT) sq += x[k] * x[k];
     for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
@@ -693,7 +683,7 @@ __device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
 // The reduced system has one 7 x 7 block row per keyframe 1..N-1, and block
 // (i, j) is non-zero only where an edge joins keyframes i and j.  Its Cholesky
 // factor is as sparse, and as parallel, as the elimination order lets it be.
-// backend_pattern_kernel picks the order once per call: level by level, each
+// backend_start_kernel picks the order once per call: level by level, each
 // level an independent set of keyframes of nearly the least degree in the
 // graph that the earlier levels leave (the chain of a sequence halves at every
 // level).  The columns of one level depend on earlier levels only, so a level
@@ -732,19 +722,129 @@ __device__ __forceinline__ int block_exclusive(int v, int* tmp, int* all) {
     return before + inc - v;
 }
 
-// One workgroup, once per call: elimination order, levels, the factor's blocks,
-// and for every block the edges that enter it and the products it takes.
-__global__ void __launch_bounds__(kPatThreads) backend_pattern_kernel(BackendArgs A) {
+// Smallest value of the wave (every lane active), uniform.
+__device__ __forceinline__ int wave_least(int v) {
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, false));  // row_half_mirror
+    v = min(v, __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, false));  // row_mirror
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// The elimination, in one wave without barriers: lane l holds the rows of
+// keyframes l and l + 64 (HALVES = 2) of the remaining graph.  A level takes,
+// in order of degree then index, every keyframe of degree at most
+// max(least + 1, 2) that no earlier one of the level neighbours; eliminating it
+// joins its neighbours, which leave the level.  A serial chain per keyframe:
+// one wave minimum and some register operations without branches.  Returns the
+// number of levels.
+template <int HALVES>
+__device__ __forceinline__ int eliminate(int nb, const uint32_t (*adj)[kPatWords], uint32_t (*col)[kPatWords],
+                                         uint32_t (*row)[kPatWords], uint8_t* perm, uint8_t* pos, uint16_t* lvl) {
+    constexpr int WORDS = 2 * HALVES;
+    const int lane = threadIdx.x & 63;
+    // r: neighbours left; mine: positions of the columns that hold the keyframe;
+    // self: its own bit; gone: all ones once eliminated (keys are positive).
+    uint32_t r[HALVES][WORDS], mine[HALVES][WORDS], self[HALVES][WORDS];
+    int gone[HALVES], key[HALVES], cand[HALVES];
+    auto rekey = [&](int h) {
+        int d = 0;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) d += __popc(r[h][w]);
+        key[h] = (d * 128 + lane + 64 * h) | gone[h];
+    };
+#pragma unroll
+    for (int h = 0; h < HALVES; ++h) {
+        const int x = lane + 64 * h;
+        gone[h] = x < nb ? 0 : INT_MAX;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) {
+            r[h][w] = x < nb ? adj[x][w] : 0u;
+            mine[h][w] = 0u;
+            self[h][w] = (x >> 5) == w ? 1u << (x & 31) : 0u;
+        }
+        rekey(h);
+    }
+    // By mask: a conditional here would index the register arrays in memory.
+    auto pick = [](uint32_t a, uint32_t b, uint32_t mask) { return a ^ ((a ^ b) & mask); };
+    int k = 0, nlev = 0;
+    while (k < nb) {
+        if (lane == 0) lvl[nlev] = (uint16_t)k;
+        ++nlev;
+        const int top = (max((wave_least(min(key[0], key[HALVES - 1])) >> 7) + 1, 2) + 1) * 128;
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) cand[h] = key[h] < top ? key[h] : INT_MAX;
+        for (;;) {
+            const int best = wave_least(min(cand[0], cand[HALVES - 1]));
+            if (best == INT_MAX) break;
+            const int v = best & 127;
+            uint32_t rv[WORDS];
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w)
+                rv[w] = (uint32_t)__builtin_amdgcn_readlane((int)pick(r[0][w], r[HALVES - 1][w], v >= 64 ? ~0u : 0u), v & 63);
+            if (lane == 0) {
+                perm[k] = (uint8_t)v;
+                pos[v] = (uint8_t)k;
+            }
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w)
+                if (lane == w) col[k][w] = rv[w];
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) {
+                // Keyframe lane + 64 h is on bit lane & 31 of word 2 h or 2 h + 1.
+                const uint32_t word = pick(rv[2 * h], rv[2 * h + 1], (lane & 32) ? ~0u : 0u);
+                const uint32_t nbr = 0u - ((word >> (lane & 31)) & 1u);
+                gone[h] = lane + 64 * h == v ? INT_MAX : gone[h];
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) {
+                    const uint32_t vbit = (v >> 5) == w ? 1u << (v & 31) : 0u, kbit = (k >> 5) == w ? 1u << (k & 31) : 0u;
+                    r[h][w] = (r[h][w] | (rv[w] & nbr)) & ~(self[h][w] | vbit);
+                    mine[h][w] |= kbit & nbr;
+                }
+                rekey(h);
+                cand[h] |= gone[h] | (int)(nbr & 0x7fffffffu);
+            }
+            ++k;
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+        for (int w = 0; w < kPatWords; ++w) row[lane + 64 * h][w] = w < WORDS ? mine[h][w < WORDS ? w : 0] : 0u;
+    if (HALVES == 1)
+        for (int i = lane; i < nb; i += 64)
+            for (int w = WORDS; w < kPatWords; ++w) col[i][w] = 0u;
+    return nlev;
+}
+
+// Once per call.  Workgroup 0: elimination order, levels, the factor's blocks,
+// and for every block the edges that enter it and the products it takes.  It is
+// a chain of short serial parts: 20 us for 32 keyframes and 75 us for
+// 96, from 60 and 164 us with the wave minimum through LDS permutes, each slot's
+// products found by walking every earlier column and its edges by one lane.  The
+// other workgroups: the fp64 poses and the edges' relative poses at T_in.
+__global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs A, const float* __restrict__ T_in) {
     __shared__ uint32_t adj[M3S_MAX_KEYFRAMES][kPatWords];
     __shared__ uint32_t col[M3S_MAX_KEYFRAMES][kPatWords];  // by position: later keyframes of the column
+    __shared__ uint32_t row[M3S_MAX_KEYFRAMES][kPatWords];  // by keyframe: positions of its row's columns
     __shared__ uint8_t perm[M3S_MAX_KEYFRAMES], pos[M3S_MAX_KEYFRAMES];
     __shared__ int32_t cstart[M3S_MAX_KEYFRAMES + 1];
     __shared__ uint16_t lvl[M3S_MAX_KEYFRAMES + 2];
     __shared__ uint8_t si[kMaxBlocks], sj[kMaxBlocks];
-    __shared__ int32_t chunk[2 * kPatThreads];
+    __shared__ int2 chunk[kPatThreads];
+    __shared__ int32_t cursor[kMaxBlocks];  // edges of a slot, then where its next one goes
     __shared__ int tmp[kPatThreads / 64];
     __shared__ int nlev_s;
     const int nb = A.N - 1, tid = threadIdx.x, lane = tid & 63;
+    if (blockIdx.x > 0) {
+        const int t = ((int)blockIdx.x - 1) * kPatThreads + tid;
+        if (t < 12 * A.N) A.T64[t] = (double)T_in[t];
+        if (t < A.E) write_relative_pose(A, t, [&](int k, int j) { return (double)T_in[12 * k + j]; });
+        return;
+    }
+    if (tid < 4 && tid != 2) A.state[tid] = 0;
+    if (tid < 2) A.stat[tid] = 0.0;
     PatternBuf& P = *A.pat;
     for (int i = tid; i < nb * kPatWords; i += kPatThreads) (&adj[0][0])[i] = 0u;
     __syncthreads();
@@ -755,75 +855,8 @@ __global__ void __launch_bounds__(kPatThreads) backend_pattern_kernel(BackendArg
         atomicOr(&adj[ej - 1][(ei - 1) >> 5], 1u << ((ei - 1) & 31));
     }
     __syncthreads();
-    // The elimination in one wave, without barriers: lane l holds the rows of
-    // keyframes l and l + 64 of the remaining graph.  A level takes, in order of
-    // degree then index, every keyframe of degree at most max(least + 1, 2) that
-    // no earlier one of the level neighbours; eliminating it joins its
-    // neighbours, which leave the level.
     if (tid < 64) {
-        uint32_t r[2][kPatWords];
-        bool alive[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int x = lane + 64 * h;
-            alive[h] = x < nb;
-#pragma unroll
-            for (int w = 0; w < kPatWords; ++w) r[h][w] = alive[h] ? adj[x][w] : 0u;
-        }
-        auto degree = [&](int h) {
-            int d = 0;
-#pragma unroll
-            for (int w = 0; w < kPatWords; ++w) d += __popc(r[h][w]);
-            return d;
-        };
-        auto least = [&](int v) {
-            for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-            return __builtin_amdgcn_readfirstlane(v);
-        };
-        int k = 0, nlev = 0;
-        while (k < nb) {
-            if (lane == 0) lvl[nlev] = (uint16_t)k;
-            ++nlev;
-            const int d0 = least(min(alive[0] ? degree(0) : INT_MAX, alive[1] ? degree(1) : INT_MAX));
-            const int top = max(d0 + 1, 2);
-            bool cand[2] = {alive[0] && degree(0) <= top, alive[1] && degree(1) <= top};
-            for (;;) {
-                const int key = least(min(cand[0] ? degree(0) * 128 + lane : INT_MAX,
-                                          cand[1] ? degree(1) * 128 + lane + 64 : INT_MAX));
-                if (key == INT_MAX) break;
-                const int v = key & 127;
-                uint32_t rv[kPatWords];
-#pragma unroll
-                for (int w = 0; w < kPatWords; ++w)
-                    rv[w] = (uint32_t)__builtin_amdgcn_readlane(v < 64 ? (int)r[0][w] : (int)r[1][w], v & 63);
-                if (lane == 0) {
-                    perm[k] = (uint8_t)v;
-                    pos[v] = (uint8_t)k;
-                }
-#pragma unroll
-                for (int w = 0; w < kPatWords; ++w)
-                    if (lane == w) col[k][w] = rv[w];
-                ++k;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int x = lane + 64 * h;
-                    if (x == v) alive[h] = cand[h] = false;
-                    bool nbr = false;
-#pragma unroll
-                    for (int w = 0; w < kPatWords; ++w) nbr = nbr || ((x >> 5) == w && ((rv[w] >> (x & 31)) & 1u));
-                    if (nbr) {
-                        cand[h] = false;
-#pragma unroll
-                        for (int w = 0; w < kPatWords; ++w) {
-                            uint32_t t = r[h][w] | rv[w];
-                            if ((x >> 5) == w) t &= ~(1u << (x & 31));
-                            if ((v >> 5) == w) t &= ~(1u << (v & 31));
-                            r[h][w] = t;
-                        }
-                    }
-                }
-            }
-        }
+        const int nlev = nb <= 64 ? eliminate<1>(nb, adj, col, row, perm, pos, lvl) : eliminate<2>(nb, adj, col, row, perm, pos, lvl);
         if (lane == 0) {
             lvl[nlev] = (uint16_t)nb;
             nlev_s = nlev;
@@ -863,22 +896,19 @@ __global__ void __launch_bounds__(kPatThreads) backend_pattern_kernel(BackendArg
     constexpr int kOwn = kMaxBlocks / kPatThreads;
     const int own_n = (nblk + kPatThreads - 1) / kPatThreads;
     auto own_slot = [&](int j) { return j < own_n ? tid * own_n + j : nblk; };
-    auto in_col = [&](int v, int x) { return ((col[v][x >> 5] >> (x & 31)) & 1u) != 0u; };
+    // Columns that rows x and z of the factor share, before column z itself.
+    auto shared_cols = [&](int x, int z, int w) { return row[x][w] & row[z][w]; };
     auto slot_in = [&](int v, int x) {  // slot of (keyframe x, column v)
         int s = cstart[v] + 1;
         for (int w = 0; w < (x >> 5); ++w) s += __popc(col[v][w]);
         return s + __popc(col[v][x >> 5] & ((1u << (x & 31)) - 1u));
     };
-    int ucnt[kOwn], usum = 0;
+    int usum = 0;
     for (int j = 0; j < kOwn; ++j) {
         const int s = own_slot(j);
-        ucnt[j] = 0;
-        if (s < nblk) {
-            const int x = perm[si[s]], z = perm[sj[s]];
-            for (int v = 0; v < sj[s]; ++v)
-                if (in_col(v, x) && in_col(v, z)) ++ucnt[j];
-        }
-        usum += ucnt[j];
+        if (s >= nblk) break;
+        const int x = perm[si[s]], z = perm[sj[s]];
+        for (int w = 0; w < kPatWords; ++w) usum += __popc(shared_cols(x, z, w));
     }
     int nupd;
     int u0 = block_exclusive(usum, tmp, &nupd);
@@ -891,15 +921,18 @@ __global__ void __launch_bounds__(kPatThreads) backend_pattern_kernel(BackendArg
         if (s >= nblk) break;
         P.ustart[s] = (uint16_t)u0;
         const int x = perm[si[s]], z = perm[sj[s]];
-        for (int v = 0; v < sj[s] && ucnt[j] > 0; ++v)
-            if (in_col(v, x) && in_col(v, z)) {
+        for (int w = 0; w < kPatWords; ++w) {
+            uint32_t m = shared_cols(x, z, w);
+            while (m) {
+                const int v = 32 * w + __builtin_ctz(m);
+                m &= m - 1u;
                 P.upd[u0++] = (uint32_t)slot_in(v, x) | ((uint32_t)slot_in(v, z) << 16);
-                --ucnt[j];
             }
+        }
     }
-    // Edges of every slot, in edge order: first counted, then listed.
-    int ecnt[kOwn], e0[kOwn];
-    for (int j = 0; j < kOwn; ++j) ecnt[j] = e0[j] = 0;
+    // Edges of every slot, in edge order, first counted, then listed: eight
+    // lanes per slot, each a contiguous eighth of a chunk of edges.
+    for (int i = tid; i < nblk; i += kPatThreads) cursor[i] = 0;
     for (int pass = 0; pass < 2; ++pass) {
         for (int b = 0; b < A.E; b += kPatThreads) {
             __syncthreads();
@@ -907,36 +940,51 @@ __global__ void __launch_bounds__(kPatThreads) backend_pattern_kernel(BackendArg
             if (tid < m) {
                 const int ei = A.edges[2 * (b + tid)], ej = A.edges[2 * (b + tid) + 1];
                 const bool use = edge_in_range(ei, ej, A.N) && ei != ej;
-                chunk[2 * tid] = use ? ei - 1 : -1;
-                chunk[2 * tid + 1] = use ? ej - 1 : -1;
+                chunk[tid] = use ? make_int2(ei - 1, ej - 1) : make_int2(-1, -1);
             }
             __syncthreads();
-            for (int j = 0; j < kOwn; ++j) {
-                const int s = own_slot(j);
-                if (s >= nblk) break;
+            const int sub = tid & 7, seg = (m + 7) / 8, t0 = min(sub * seg, m), t1 = min(t0 + seg, m);
+            for (int s = tid >> 3; s < nblk; s += kPatThreads / 8) {
                 const int x = perm[si[s]], z = perm[sj[s]];
-                for (int t = 0; t < m; ++t) {
-                    const int i = chunk[2 * t], k = chunk[2 * t + 1];
-                    const bool own = i == x, hit = x == z ? (own || k == x) : (own ? k == z : (i == z && k == x));
-                    if (!hit) continue;
-                    // H_ii, H_jj += blk; H_ij -= blk, H_ji -= blk^T: a row owned by j reads it transposed.
-                    if (pass)
-                        A.elist[e0[j]++] = (uint32_t)(b + t) | (own ? kEdgeOwnI : 0u) |
-                                           (x != z && !own ? kEdgeTransposed : 0u);
-                    else
-                        ++ecnt[j];
+                // H_ii, H_jj += blk; H_ij -= blk, H_ji -= blk^T: a row owned by j reads it transposed.
+                // (An edge's two keyframes differ; no branches in the test.)
+                auto hits = [&](int2 c) { return ((int)(c.x == x) | (int)(c.y == x)) & ((int)(c.x == z) | (int)(c.y == z)); };
+                int c = 0;
+#pragma unroll 4
+                for (int t = t0; t < t1; ++t) c += hits(chunk[t]);
+                int inc = c;
+                for (int o = 1; o < 8; o <<= 1) {
+                    const int u = __shfl_up(inc, o, 8);
+                    if (sub >= o) inc += u;
                 }
+                const int all = __shfl(inc, 7, 8);
+                if (pass) {
+                    int at = cursor[s] + inc - c;
+                    for (int t = t0; c > 0 && t < t1; ++t)
+                        if (hits(chunk[t])) {
+                            const bool own = chunk[t].x == x;
+                            A.elist[at++] = (uint32_t)(b + t) | (own ? kEdgeOwnI : 0u) |
+                                            (x != z && !own ? kEdgeTransposed : 0u);
+                        }
+                }
+                // The eight lanes have read the cursor (they are of one wave).
+                if (sub == 7) cursor[s] += all;
             }
         }
         if (pass) break;
+        __syncthreads();
         int esum = 0, nedge;
-        for (int j = 0; j < kOwn; ++j) esum += ecnt[j];
+        for (int j = 0; j < kOwn; ++j) {
+            const int s = own_slot(j);
+            if (s < nblk) esum += cursor[s];
+        }
         int base = block_exclusive(esum, tmp, &nedge);
         for (int j = 0; j < kOwn; ++j) {
             const int s = own_slot(j);
-            e0[j] = base;
-            if (s < nblk) P.estart[s] = base;
-            base += ecnt[j];
+            if (s >= nblk) break;
+            const int c = cursor[s];
+            P.estart[s] = cursor[s] = base;
+            base += c;
         }
         if (tid == 0) P.estart[nblk] = nedge;
     }
@@ -1013,43 +1061,49 @@ __device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS
     for (int i = tid; i < min(nent, (int)S.kEntries); i += kSolveThreads) S.elist[i] = A.elist[i];
     if (tid == 0) S.bad = 0;
     __syncthreads();
-    auto entry = [&](int l) { return l < S.kEntries ? S.elist[l] : A.elist[l]; };
-    // The system's blocks, gathered from the edges' blocks in edge order: kQ
-    // entries per lane and step, the reads of each one's first kE edges (two per
-    // block and four per diagonal in a sequence) in flight together.
-    constexpr int kQ = 4, kE = 4;
-    for (int q0 = tid; q0 < nblk * 49; q0 += kQ * kSolveThreads) {
+    // The system's blocks, gathered from the edges' blocks in edge order: one
+    // lane per entry and one wave per block, kQ blocks a step with the reads of
+    // each one's first kE edges (two per block and four per diagonal in a
+    // sequence) issued together, without branches between them: they come from
+    // memory that other XCDs wrote.  (Entry by entry with branches: 9.5 us for 89
+    // blocks and 25 us for 286; this 6.6 and 14.6 us; with the indices in scalar
+    // registers 7.4 and 17.2 us.)
+    constexpr int kQ = 8, kE = 4;
+    const int wave = tid >> 6, en = min(tid & 63, 48), et = 7 * (en % 7) + en / 7;
+    for (int sb = wave * kQ; sb < nblk; sb += kQ * (kSolveThreads / 64)) {
         double t[kQ][kE];
+        uint32_t f[kQ][kE];
         int l0[kQ], l1[kQ];
 #pragma unroll
         for (int i = 0; i < kQ; ++i) {
-            const int q = q0 + i * kSolveThreads;
-            const int s = q / 49, e = q - 49 * s, a = e / 7, b = e - 7 * a;
-            const bool in = q < nblk * 49;
-            l0[i] = in ? S.estart[s] : 0;
-            l1[i] = in ? S.estart[s + 1] : 0;
-#pragma unroll
-            for (int j = 0; j < kE; ++j) {
-                t[i][j] = 0.0;
-                if (l0[i] + j < l1[i]) {
-                    const uint32_t f = entry(l0[i] + j);
-                    t[i][j] = A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + ((f & kEdgeTransposed) ? 7 * b + a : e)];
-                }
-            }
+            const int s = min(sb + i, nblk - 1);
+            l0[i] = S.estart[s];
+            l1[i] = sb + i < nblk ? S.estart[s + 1] : l0[i];
         }
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            const int q = q0 + i * kSolveThreads;
-            if (q >= nblk * 49) break;
-            const int s = q / 49, e = q - 49 * s, a = e / 7, b = e - 7 * a;
-            double v = 0.0;
+        for (int i = 0; i < kQ; ++i)
 #pragma unroll
-            for (int j = 0; j < kE; ++j) v += t[i][j];
-            for (int l = l0[i] + kE; l < l1[i]; ++l) {
-                const uint32_t f = entry(l);
-                v += A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + ((f & kEdgeTransposed) ? 7 * b + a : e)];
+            for (int j = 0; j < kE; ++j) f[i][j] = S.elist[min(l0[i] + j, (int)S.kEntries - 1)];
+        // Past the block's edges (or beyond the listed ones): some edge's block, not used.
+#pragma unroll
+        for (int i = 0; i < kQ; ++i)
+#pragma unroll
+            for (int j = 0; j < kE; ++j) {
+                const uint32_t e = min(f[i][j] & kEdgeMask, (uint32_t)(A.E - 1));
+                t[i][j] = A.edge_blk[(size_t)e * kBlk + ((f[i][j] & kEdgeTransposed) ? et : en)];
             }
-            Lb[q] = S.si[s] == S.sj[s] ? v : -v;
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            double v = 0.0;
+            const int n0 = min(l0[i] + kE, min(l1[i], (int)S.kEntries));
+#pragma unroll
+            for (int j = 0; j < kE; ++j) v += l0[i] + j < n0 ? t[i][j] : 0.0;
+            for (int l = max(n0, l0[i]); l < l1[i]; ++l) {
+                const uint32_t g = l < S.kEntries ? S.elist[l] : A.elist[l];
+                v += A.edge_blk[(size_t)(g & kEdgeMask) * kBlk + ((g & kEdgeTransposed) ? et : en)];
+            }
+            const int s = min(sb + i, nblk - 1);
+            if ((tid & 63) < 49 && sb + i < nblk) Lb[49 * s + en] = S.si[s] == S.sj[s] ? v : -v;
         }
     }
     // Right-hand side -g: g_i -= A^T g_e, g_j += A^T g_e.
@@ -1058,7 +1112,7 @@ __device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS
         double v = 0.0;
 #pragma unroll 4
         for (int l = S.estart[s]; l < S.estart[s + 1]; ++l) {
-            const uint32_t f = entry(l);
+            const uint32_t f = l < S.kEntries ? S.elist[l] : A.elist[l];
             const double t = A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + 49 + a];
             v += (f & kEdgeOwnI) ? t : -t;
         }
@@ -1259,17 +1313,30 @@ __global__ void __launch_bounds__(kSolveThreads) backend_solve_kernel(BackendArg
 __global__ void __launch_bounds__(256) backend_finish_kernel(BackendArgs A) {
     const int t = threadIdx.x + blockIdx.x * blockDim.x;
     if (t < 12 * A.N) A.T_out[t] = (float)A.T64[t];
-    if (t == 0 && A.info) {
+    if (blockIdx.x == 0 && A.info) {
+        // Cost and count: every 256th edge per thread, then the threads in a fixed tree.
+        __shared__ double part[2][256];
         double cost = 0.0, count = 0.0;
-        for (int e = 0; e < A.E; ++e) {
+        for (int e = threadIdx.x; e < A.E; e += 256) {
             if (!edge_in_range(A.edges[2 * e], A.edges[2 * e + 1], A.N)) continue;
             cost += A.edge_sys[(size_t)e * kStride + 35];
             count += A.edge_sys[(size_t)e * kStride + 36];
         }
-        A.info[0] = (float)cost;
-        A.info[1] = (float)count;
-        A.info[2] = (float)A.state[1];
-        A.info[3] = (float)A.stat[0];
+        part[0][threadIdx.x] = cost;
+        part[1][threadIdx.x] = count;
+        for (int o = 128; o > 0; o >>= 1) {
+            __syncthreads();
+            if ((int)threadIdx.x < o) {
+                part[0][threadIdx.x] += part[0][threadIdx.x + o];
+                part[1][threadIdx.x] += part[1][threadIdx.x + o];
+            }
+        }
+        if (threadIdx.x == 0) {
+            A.info[0] = (float)part[0][0];
+            A.info[1] = (float)part[1][0];
+            A.info[2] = (float)A.state[1];
+            A.info[3] = (float)A.stat[0];
+        }
     }
 }
 
@@ -1347,9 +1414,7 @@ hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q,
     A.T_out = T;
     A.info = info;
     const dim3 grid(A.blocks_per_edge, E);
-    backend_init_kernel<<<(12 * N + 255) / 256, 256, 0, s>>>(T, A.T64, N, A.state, A.stat);
-    backend_relpose_kernel<<<(E + 255) / 256, 256, 0, s>>>(A);
-    backend_pattern_kernel<<<1, kPatThreads, 0, s>>>(A);
+    backend_start_kernel<<<1 + (max(12 * N, E) + kPatThreads - 1) / kPatThreads, kPatThreads, 0, s>>>(A, T);
     for (int it = 0; it <= iters; ++it) {
         const int final_pass = it == iters ? 1 : 0;
         timer_begin("backend_accum", s);
