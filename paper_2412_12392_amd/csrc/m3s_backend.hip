@@ -107,6 +107,7 @@ struct BackendArgs {
     float* info;              // [4] or null
 };
 
+constexpr int kGroup = 4;     // neighbouring matches a lane of the accumulation takes at a time
 constexpr int kBlk = 56;      // 49 + 7 doubles per edge
 constexpr int kMatchesMost = 8;     // matches per lane of the accumulation (amortises the workgroup reduction)
 constexpr int kAccumBlocks = 1536;   // workgroups of an accumulation, at least, where there are matches for them
@@ -135,13 +136,6 @@ __device__ __forceinline__ void write_relative_pose(const BackendArgs& A, int e,
     }
     for (int k = 0; k < 12; ++k) A.Trel[12 * e + k] = (float)Tij[k];
 }
-
-// Loads of four neighbouring pixels: whole vectors at any alignment (gfx950
-// takes 16-byte loads at a float's alignment and 4-byte loads at a byte's).
-constexpr int kGroup = 4;
-typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef int32_t i4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32_any __attribute__((aligned(1)));
 
 // A lane takes four neighbouring matches at a time: the six vector loads of the
 // pixel side replace 24 scalar ones, and only the matched points and their

@@ -69,7 +69,7 @@ hipError_t launch_bwd_batched(const BwdEdgeArgs* table, int n_edges, long max_pi
                               bool zero, hipStream_t s);
 
 // Tracking pose solve (m3s_track.hip): workgroups of one iteration launch,
-// workspace bytes, and the launch sequence (init + iters + 1 launches).
+// workspace bytes, and the launch sequence (iters + 1 steps, then the final sum).
 int track_blocks(int N);
 size_t track_workspace_bytes(int N);
 hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* idx, const uint8_t* valid,

@@ -13,6 +13,15 @@
 
 namespace m3s {
 
+// Loads of neighbouring pixels: whole vectors at any alignment (gfx950 takes
+// 16-byte loads at a float's alignment and 4-byte loads at a byte's).
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t i4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef int32_t i2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+
 // Number of normal-equation values of a match set: the upper triangle of the 7x7
 // J^T W J (28, rows of 7, 6, ..., 1), J^T W r (7), robust cost, match count.
 constexpr int kPoseVals = 28 + 7 + 2;
@@ -299,6 +308,46 @@ __device__ inline void sim3_adjoint(const double* T, double* A) {
     A[48] = 1.0;
 }
 
+// Coefficients of sim3_exp for a small tangent (theta^2 < 2.5e-3, |sigma| <
+// 0.05: every Gauss-Newton step but the first ones of a poor start), to fp64
+// rounding, without library calls or divisions.  With J_m = int s^m e^{sigma s}
+// over [0, 1]: a0 = J_0, a1 = sum (-theta^2)^n J_{2n+1} / (2n+1)! and
+// a2 = sum (-theta^2)^n J_{2n+2} / (2n+2)!; J_8 by its series and the others
+// downwards by J_{m-1} = (e^sigma - sigma J_m) / m (integration by parts),
+// which damps the error.
+__device__ inline void sim3_exp_small(double sg, double th2, double& ka, double& kb, double& es, double& a0, double& a1,
+                                      double& a2) {
+    es = 1.0 / 362880.0;
+    es = fma(es, sg, 1.0 / 40320.0);
+    es = fma(es, sg, 1.0 / 5040.0);
+    es = fma(es, sg, 1.0 / 720.0);
+    es = fma(es, sg, 1.0 / 120.0);
+    es = fma(es, sg, 1.0 / 24.0);
+    es = fma(es, sg, 1.0 / 6.0);
+    es = fma(es, sg, 0.5);
+    es = fma(es, sg, 1.0);
+    es = fma(es, sg, 1.0);
+    double J[9];
+    // sum sigma^k / (k! (k + 9))
+    J[8] = 1.0 / (40320.0 * 17.0);
+    J[8] = fma(J[8], sg, 1.0 / (5040.0 * 16.0));
+    J[8] = fma(J[8], sg, 1.0 / (720.0 * 15.0));
+    J[8] = fma(J[8], sg, 1.0 / (120.0 * 14.0));
+    J[8] = fma(J[8], sg, 1.0 / (24.0 * 13.0));
+    J[8] = fma(J[8], sg, 1.0 / (6.0 * 12.0));
+    J[8] = fma(J[8], sg, 1.0 / (2.0 * 11.0));
+    J[8] = fma(J[8], sg, 1.0 / 10.0);
+    J[8] = fma(J[8], sg, 1.0 / 9.0);
+#pragma unroll
+    for (int m = 8; m > 0; --m) J[m - 1] = fma(-sg, J[m], es) * (1.0 / m);
+    const double z = -th2;
+    ka = fma(z, fma(z, fma(z, fma(z, 1.0 / 362880.0, 1.0 / 5040.0), 1.0 / 120.0), 1.0 / 6.0), 1.0);
+    kb = fma(z, fma(z, fma(z, fma(z, 1.0 / 3628800.0, 1.0 / 40320.0), 1.0 / 720.0), 1.0 / 24.0), 0.5);
+    a0 = J[0];
+    a1 = fma(z, fma(z, fma(z, J[7] * (1.0 / 5040.0), J[5] * (1.0 / 120.0)), J[3] * (1.0 / 6.0)), J[1]);
+    a2 = fma(z, fma(z, fma(z, J[8] * (1.0 / 40320.0), J[6] * (1.0 / 720.0)), J[4] * (1.0 / 24.0)), J[2] * 0.5);
+}
+
 // Exp of sim(3): tau = (v, omega, sigma) -> [e^sigma R | V v], R by Rodrigues
 // and V = a0 I + a1 [omega]_x + a2 [omega]_x^2 with a0 = int e^{sigma s},
 // a1 = int e^{sigma s} sin(theta s) / theta and
@@ -307,34 +356,35 @@ __device__ inline void sim3_adjoint(const double* T, double* A) {
 __device__ inline void sim3_exp(const double* tau, double* E) {
     const double sg = tau[6];
     const double w0 = tau[3], w1 = tau[4], w2 = tau[5];
-    const double th2 = w0 * w0 + w1 * w1 + w2 * w2, th = sqrt(th2);
+    const double th2 = w0 * w0 + w1 * w1 + w2 * w2;
     const double S[3][3] = {{0.0, -w2, w1}, {w2, 0.0, -w0}, {-w1, w0, 0.0}};
     double S2[3][3];
     for (int i = 0; i < 3; ++i)
         for (int j = 0; j < 3; ++j) S2[i][j] = S[i][0] * S[0][j] + S[i][1] * S[1][j] + S[i][2] * S[2][j];
-    double sn, cs;
-    sincos(th, &sn, &cs);
-    const bool small = th < 1e-4;
-    const double ka = small ? 1.0 - th2 / 6.0 : sn / th;
-    const double kb = small ? 0.5 - th2 / 24.0 : (1.0 - cs) / th2;
-    const double es = exp(sg);
-    const double a0 = sg == 0.0 ? 1.0 : expm1(sg) / sg;
-    double a1, a2;
-    if (small) {
-        const double s2 = sg * sg;
-        if (fabs(sg) < 1e-3) {
-            a1 = 0.5 + sg / 3.0 + s2 / 8.0 + s2 * sg / 30.0;
-            a2 = 1.0 / 6.0 + sg / 8.0 + s2 / 20.0 + s2 * sg / 72.0;
-        } else {
+    double ka, kb, es, a0, a1, a2;
+    if (th2 < 2.5e-3 && fabs(sg) < 0.05) {
+        sim3_exp_small(sg, th2, ka, kb, es, a0, a1, a2);
+    } else {
+        const double th = sqrt(th2);
+        double sn, cs;
+        sincos(th, &sn, &cs);
+        const bool small = th < 1e-4;
+        ka = small ? 1.0 - th2 / 6.0 : sn / th;
+        kb = small ? 0.5 - th2 / 24.0 : (1.0 - cs) / th2;
+        es = exp(sg);
+        a0 = sg == 0.0 ? 1.0 : expm1(sg) / sg;
+        if (small) {
+            // |sigma| is at least 0.05 here.
+            const double s2 = sg * sg;
             a1 = (es * (sg - 1.0) + 1.0) / s2;
             a2 = (es * (s2 - 2.0 * sg + 2.0) - 2.0) / (2.0 * s2 * sg);
+        } else {
+            const double den = sg * sg + th2;
+            const double is = (es * (sg * sn - th * cs) + th) / den;
+            const double ic = (es * (sg * cs + th * sn) - sg) / den;
+            a1 = is / th;
+            a2 = (a0 - ic) / th2;
         }
-    } else {
-        const double den = sg * sg + th2;
-        const double is = (es * (sg * sn - th * cs) + th) / den;
-        const double ic = (es * (sg * cs + th * sn) - sg) / den;
-        a1 = is / th;
-        a2 = (a0 - ic) / th2;
     }
     for (int i = 0; i < 3; ++i) {
         double tv = 0.0;

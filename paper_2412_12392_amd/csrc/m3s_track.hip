@@ -42,10 +42,9 @@ constexpr int kThreads = 256;
 constexpr int kVals = kPoseVals;
 constexpr int kMaxBlocks = 2048;
 
-// Workspace layout (bytes): poses, statistics, counters, then the partials.
+// Workspace layout (bytes): poses and statistics, then the partials.
 constexpr size_t kOffT = 0;         // double[2][12]: pose by iteration parity
-constexpr size_t kOffStat = 192;    // double[2]: last step norm, reserved
-constexpr size_t kOffCnt = 224;     // int32[2]: reserved, solved iterations
+constexpr size_t kOffStat = 192;    // double[2][2]: solved iterations and last step norm by iteration parity
 constexpr size_t kOffPart = 256;    // float[2][nblocks * kMomentStride]: partials by iteration parity
 
 struct TrackArgs {
@@ -59,27 +58,18 @@ struct TrackArgs {
     ConfGate gate;
     RobustWeights rw;
     double* T64;            // [2][12]
-    double* stat;
-    int32_t* counter;       // [0] reserved, [1] solved iterations
-    int32_t* solved;
+    double* stat;           // [2][2]
     float* partials;        // [2][nb * kMomentStride]
     int nb;
-    float* T_out;
+    float* T;               // in: the initial pose (read by iteration 0), out: the final one
     float* info;
 };
-
-__global__ void __launch_bounds__(64) track_init_kernel(const float* __restrict__ T_in, double* __restrict__ T64,
-                                                        int32_t* __restrict__ cnt, double* __restrict__ stat) {
-    const int i = threadIdx.x;
-    if (i < 12) T64[i] = (double)T_in[i];
-    if (i < 2) { cnt[i] = 0; stat[i] = 0.0; }
-}
 
 // Solve H tau = -g (7x7 SPD) and apply T <- Exp(tau) o T.  Returns false
 // (pose unchanged) when H is not positive definite.
 __device__ bool solve_and_update(const double* sum, double* T, double* step_norm) {
-    // Cholesky by rows; each pivot's reciprocal serves its column and both
-    // substitutions (one fp64 division per pivot).
+    // Cholesky by rows; each pivot's reciprocal root serves its column and both
+    // substitutions.
     double L[7][7], inv[7];
     for (int r = 0; r < 7; ++r)
         for (int c = 0; c < 7; ++c) L[r][c] = 0.0;
@@ -89,8 +79,13 @@ __device__ bool solve_and_update(const double* sum, double* T, double* step_norm
             for (int q = 0; q < c; ++q) s -= L[r][q] * L[c][q];
             if (r == c) {
                 if (!(s > 0.0) || !isfinite(s)) return false;
-                L[r][r] = sqrt(s);
-                inv[r] = 1.0 / L[r][r];
+                // 1/sqrt(s): hardware estimate and two Newton steps (no fp64
+                // division or square root in the chain).
+                double is = __builtin_amdgcn_rsq(s);
+                is = is * fma(-0.5 * s * is, is, 1.5);
+                is = is * fma(-0.5 * s * is, is, 1.5);
+                L[r][r] = s * is;
+                inv[r] = is;
             } else {
                 L[r][c] = s * inv[c];
             }
@@ -120,41 +115,109 @@ __device__ bool solve_and_update(const double* sum, double* T, double* step_norm
     return true;
 }
 
-// Normal equations of the matches of this workgroup at the current pose: one
-// fp32 row of moments per workgroup.
-// Matches per lane and step of the accumulation: their reads are issued
-// together before the arithmetic.
-constexpr int kMatchesPerLane = 4;
+// The neighbouring matches of a lane (pixels n0 .. n0 + PER - 1), as loaded.
+template <int PER>
+struct MatchGroup {
+    bool ok[PER];
+    float qf[PER], qk[PER], xf[PER][3], xk[PER][3];
+};
 
+template <int PER>
+__device__ __forceinline__ void load_group(const TrackArgs& A, int n0, MatchGroup<PER>& M) {
+    static_assert(PER == 2 || PER == 4, "vector loads of 2 or 4 pixels");
+    int mm[PER];
+    if (n0 + PER <= A.N) {
+        const float* x = A.Xk + 3 * (long)n0;
+        float xs[3 * PER];
+        uint32_t v;
+        if constexpr (PER == 4) {
+            v = *reinterpret_cast<const u32_any*>(A.valid + n0);
+            const i4_any i = *reinterpret_cast<const i4_any*>(A.idx + n0);
+            const f4_any q = *reinterpret_cast<const f4_any*>(A.Qk + n0);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) { mm[u] = i[u]; M.qk[u] = q[u]; }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const f4_any t = reinterpret_cast<const f4_any*>(x)[k];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) xs[4 * k + j] = t[j];
+            }
+        } else {
+            v = *reinterpret_cast<const u16_any*>(A.valid + n0);
+            const i2_any i = *reinterpret_cast<const i2_any*>(A.idx + n0);
+            const f2_any q = *reinterpret_cast<const f2_any*>(A.Qk + n0);
+            const f4_any xa = *reinterpret_cast<const f4_any*>(x);
+            const f2_any xb = *reinterpret_cast<const f2_any*>(x + 4);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) { mm[u] = i[u]; M.qk[u] = q[u]; }
+#pragma unroll
+            for (int j = 0; j < 6; ++j) xs[j] = j < 4 ? xa[j & 3] : xb[j & 1];
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            M.ok[u] = ((v >> (8 * u)) & 0xffu) != 0u;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) M.xk[u][j] = xs[3 * u + j];
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const bool in = n0 + u < A.N;
+            const long n = in ? n0 + u : 0;
+            mm[u] = A.idx[n];
+            M.ok[u] = in && A.valid[n] != 0;
+            M.qk[u] = A.Qk[n];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) M.xk[u][j] = A.Xk[3 * n + j];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        M.ok[u] = M.ok[u] && (uint32_t)mm[u] < (uint32_t)A.N;
+        const long m = M.ok[u] ? mm[u] : 0;
+        M.qf[u] = A.Qf[m];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) M.xf[u][j] = A.Xf[3 * m + j];
+    }
+}
+
+// Normal equations of the matches of this workgroup at the current pose: one
+// fp32 row of moments per workgroup.  A step is bound by latency: the sum and
+// the solve of the previous system are a serial chain (1.7 and 1.8 us by clock
+// stamps), the matches' reads another (flag and index, then the points they
+// name), and the arithmetic of a lane's matches a third.  The reads do not
+// depend on the solve, so each lane's first matches (all of them up to 2048
+// workgroups) are read before it; the solve has no fp64 division, root or
+// library call in its usual case.  A step of 320 x 240: 9.3 us before, 7.8 now.
+template <int PER>
 __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int it) {
     __shared__ float red[kThreads / 64][kMomentStride];
     __shared__ double sum[kVals];
     __shared__ SumLds<kThreads> part;
     __shared__ double Tn[12];
-    // Pose of the previous iteration (parity buffer); iteration 0 starts from
-    // the initial pose in buffer 0.
-    const double* Tprev = A.T64 + (it > 0 ? 12 * ((it + 1) & 1) : 0);
+    constexpr int kStep = kThreads * PER;
+    int n0 = blockIdx.x * kStep + PER * threadIdx.x;
+    MatchGroup<PER> M;
+    load_group(A, n0, M);
+    // Workgroup 0 records the iteration's pose and statistics, after its
+    // partials are on their way.
+    double Tl[12], solved = 0.0, step = 0.0;
     if (it > 0) {
         // Iteration it - 1's system: the same fixed-order sum and solve in
-        // every workgroup.
-        sum_partials<kThreads>(A.partials + (size_t)((it + 1) & 1) * A.nb * kMomentStride, A.nb, part, sum);
+        // every workgroup, from the pose of the previous parity buffer.
+        const int prev = (it + 1) & 1;
+        sum_partials<kThreads>(A.partials + (size_t)prev * A.nb * kMomentStride, A.nb, part, sum);
         if (threadIdx.x == 0) {
-            double Tl[12], step;
-            for (int j = 0; j < 12; ++j) Tl[j] = Tprev[j];
-            const bool ok = solve_and_update(sum, Tl, &step);
-            for (int j = 0; j < 12; ++j) Tn[j] = Tl[j];
-            if (blockIdx.x == 0) {
-                double* Tout = A.T64 + 12 * (it & 1);
-                for (int j = 0; j < 12; ++j) Tout[j] = Tl[j];
-                if (ok) {
-                    A.solved[0] += 1;
-                    A.stat[0] = step;
-                }
-            }
+            for (int j = 0; j < 12; ++j) Tl[j] = A.T64[12 * prev + j];
+            solved = A.stat[2 * prev];
+            step = A.stat[2 * prev + 1];
+            if (solve_and_update(sum, Tl, &step)) solved += 1.0;
         }
-    } else if (threadIdx.x < 12) {
-        Tn[threadIdx.x] = Tprev[threadIdx.x];
+    } else if (threadIdx.x == 0) {
+        for (int j = 0; j < 12; ++j) Tl[j] = (double)A.T[j];
     }
+    if (threadIdx.x == 0)
+        for (int j = 0; j < 12; ++j) Tn[j] = Tl[j];
     __syncthreads();
     float T[12];
 #pragma unroll
@@ -162,35 +225,23 @@ __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int i
     float acc[kMoments];
 #pragma unroll
     for (int i = 0; i < kMoments; ++i) acc[i] = 0.f;
-
-    constexpr int kStep = kThreads * kMatchesPerLane;
-    for (int base = blockIdx.x * kStep + threadIdx.x; base < A.N; base += gridDim.x * kStep) {
-        int nn[kMatchesPerLane], mm[kMatchesPerLane];
-        bool ok[kMatchesPerLane];
+    for (;;) {
 #pragma unroll
-        for (int u = 0; u < kMatchesPerLane; ++u) {
-            nn[u] = base + u * kThreads;
-            ok[u] = nn[u] < A.N && A.valid[nn[u]];
-            mm[u] = ok[u] ? A.idx[nn[u]] : 0;
-            ok[u] = ok[u] && mm[u] >= 0 && mm[u] < A.N;
-        }
-        float qf[kMatchesPerLane], qk[kMatchesPerLane], xf[kMatchesPerLane][3], xk[kMatchesPerLane][3];
-#pragma unroll
-        for (int u = 0; u < kMatchesPerLane; ++u) {
-            const int m = ok[u] ? mm[u] : 0, n = ok[u] ? nn[u] : 0;
-            qf[u] = A.Qf[m]; qk[u] = A.Qk[n];
-#pragma unroll
-            for (int j = 0; j < 3; ++j) { xf[u][j] = A.Xf[3 * m + j]; xk[u][j] = A.Xk[3 * n + j]; }
-        }
-#pragma unroll
-        for (int u = 0; u < kMatchesPerLane; ++u) {
+        for (int u = 0; u < PER; ++u) {
             float q;
-            if (ok[u] && confidence_gate(qf[u], qk[u], A.gate, q))
-                accumulate_match(T, xf[u][0], xf[u][1], xf[u][2], xk[u][0], xk[u][1], xk[u][2], q, A.rw, acc);
+            if (M.ok[u] && confidence_gate(M.qf[u], M.qk[u], A.gate, q))
+                accumulate_match(T, M.xf[u][0], M.xf[u][1], M.xf[u][2], M.xk[u][0], M.xk[u][1], M.xk[u][2], q, A.rw, acc);
         }
+        n0 += gridDim.x * kStep;
+        if (n0 >= A.N) break;
+        load_group(A, n0, M);
     }
-
     block_moments<kThreads>(acc, red, A.partials + ((size_t)(it & 1) * A.nb + blockIdx.x) * kMomentStride);
+    if (blockIdx.x == 0 && threadIdx.x < 12) A.T64[12 * (it & 1) + threadIdx.x] = Tn[threadIdx.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        A.stat[2 * (it & 1)] = solved;
+        A.stat[2 * (it & 1) + 1] = step;
+    }
 }
 
 // One workgroup: the last iteration's partials summed (cost and count at the
@@ -201,12 +252,12 @@ __global__ void __launch_bounds__(kThreads) track_final_kernel(TrackArgs A, int 
     sum_partials<kThreads>(A.partials + (size_t)(it & 1) * A.nb * kMomentStride, A.nb, part, sum);
     if (threadIdx.x != 0) return;
     const double* T = A.T64 + 12 * (it & 1);
-    for (int j = 0; j < 12; ++j) A.T_out[j] = (float)T[j];
+    for (int j = 0; j < 12; ++j) A.T[j] = (float)T[j];
     if (A.info) {
         A.info[0] = (float)sum[35];
         A.info[1] = (float)sum[36];
-        A.info[2] = (float)A.solved[0];
-        A.info[3] = (float)A.stat[0];
+        A.info[2] = (float)A.stat[2 * (it & 1)];
+        A.info[3] = (float)A.stat[2 * (it & 1) + 1];
     }
 }
 
@@ -266,8 +317,14 @@ __global__ void __launch_bounds__(256) fuse_kernel(int N, int first, const float
 
 }  // namespace
 
+// Matches per lane at a time: 2 while that needs at most one workgroup per CU
+// (an MI355X has 256), else 4, since every workgroup sums all rows.  320 x 240 (150
+// rows): 7.7 us a step with 2, 8.4 with 4; 512 x 384: 9.0 (384 rows) and 7.9 (192).
+static int matches_per_lane(int N) { return N <= 256 * kThreads * 2 ? 2 : 4; }
+
 int track_blocks(int N) {
-    const int nb = (N + kThreads * kMatchesPerLane - 1) / (kThreads * kMatchesPerLane);
+    const int per = kThreads * matches_per_lane(N);
+    const int nb = N / per + (N % per != 0);
     return nb < 1 ? 1 : (nb > kMaxBlocks ? kMaxBlocks : nb);
 }
 
@@ -285,17 +342,15 @@ hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* 
     A.rw = robust_weights(sigma_ray, sigma_dist, huber);
     A.T64 = reinterpret_cast<double*>(w + kOffT);
     A.stat = reinterpret_cast<double*>(w + kOffStat);
-    A.counter = reinterpret_cast<int32_t*>(w + kOffCnt);
-    A.solved = A.counter + 1;
     A.partials = reinterpret_cast<float*>(w + kOffPart);
-    A.T_out = T;
+    A.T = T;
     A.info = info;
     const int nb = track_blocks(N);
     A.nb = nb;
-    track_init_kernel<<<1, 64, 0, s>>>(T, A.T64, A.counter, A.stat);
     for (int it = 0; it <= iters; ++it) {
         timer_begin("track_step", s);
-        track_step_kernel<<<nb, kThreads, 0, s>>>(A, it);
+        if (matches_per_lane(N) == 2) track_step_kernel<2><<<nb, kThreads, 0, s>>>(A, it);
+        else track_step_kernel<4><<<nb, kThreads, 0, s>>>(A, it);
         timer_end(s);
     }
     timer_begin("track_final", s);
