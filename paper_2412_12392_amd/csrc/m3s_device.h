@@ -52,8 +52,18 @@ __device__ __forceinline__ float3 f3(float x, float y, float z) { return make_fl
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
-__device__ __forceinline__ float3 load_point(const float* __restrict__ X, long m) {
-    return f3(X[3 * m + 0], X[3 * m + 1], X[3 * m + 2]);
+// Element of an array at a 32-bit byte offset: the base stays in scalar registers
+// and the address costs no 64-bit vector arithmetic.  H * W is at most 2^26 (the
+// host checks), so per-pixel arrays of up to 63 bytes a pixel qualify; the
+// descriptors do not.
+template <class T>
+__device__ __forceinline__ T* at_bytes(T* base, uint32_t byte) {
+    return (T*)((char*)base + byte);
+}
+
+__device__ __forceinline__ float3 load_point(const float* __restrict__ X, uint32_t m) {
+    const float* p = reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + 12u * m);
+    return f3(p[0], p[1], p[2]);
 }
 
 __device__ __forceinline__ bool finite3(float3 v) {

@@ -165,13 +165,13 @@ struct QState {
 // its final outputs here and returns false.
 __device__ __forceinline__ bool lm_setup(const EdgeArgs& A, int x, int y, QState& q, float3& t, LMState& st) {
     const int H = A.H, W = A.W;
-    const long n = (long)y * W + x;
+    const uint32_t n = (uint32_t)(y * W + x);
     float3 xq = load_point(A.Xji, n);
     float px0, py0;
     bool bad = false;
     if (A.p_init) {
-        px0 = A.p_init[2 * n];
-        py0 = A.p_init[2 * n + 1];
+        px0 = at_bytes(A.p_init, 8u * n)[0];
+        py0 = at_bytes(A.p_init, 8u * n)[1];
         if (!isfinite(px0) || !isfinite(py0)) { bad = true; px0 = py0 = 0.f; }
     } else {
         px0 = (float)x;
@@ -184,11 +184,14 @@ __device__ __forceinline__ bool lm_setup(const EdgeArgs& A, int x, int y, QState
     q.good = !bad;
     q.px = px; q.py = py; q.th = INFINITY;
     if (bad) {
-        reinterpret_cast<float2*>(A.p)[n] = make_float2(px, py);
-        A.idx[n] = -1;
-        A.valid[n] = 0;
-        if (A.theta) A.theta[n] = INFINITY;
-        if (A.xhat) { A.xhat[3 * n] = NAN; A.xhat[3 * n + 1] = NAN; A.xhat[3 * n + 2] = NAN; }
+        *at_bytes(reinterpret_cast<float2*>(A.p), 8u * n) = make_float2(px, py);
+        *at_bytes(A.idx, 4u * n) = -1;
+        *at_bytes(A.valid, n) = 0;
+        if (A.theta) *at_bytes(A.theta, 4u * n) = INFINITY;
+        if (A.xhat) {
+            float* o = at_bytes(A.xhat, 12u * n);
+            o[0] = NAN; o[1] = NAN; o[2] = NAN;
+        }
         return false;
     }
     float inv = rsq(n2);
@@ -201,21 +204,22 @@ __device__ __forceinline__ bool lm_setup(const EdgeArgs& A, int x, int y, QState
 // Phase 1c: outputs of the LM: p*, residual angle (Eq. 3 solved for theta), xhat.
 __device__ __forceinline__ void lm_finish(const EdgeArgs& A, int x, int y, const LMState& st, QState& q) {
     const int H = A.H, W = A.W;
-    const long n = (long)y * W + x;
+    const uint32_t n = (uint32_t)(y * W + x);
     const float px = st.px, py = st.py;
-    reinterpret_cast<float2*>(A.p)[n] = make_float2(px, py);
+    *at_bytes(reinterpret_cast<float2*>(A.p), 8u * n) = make_float2(px, py);
     float th = 2.0f * asinf(fminf(1.0f, sqrtf(st.cur.c) * 0.5f));
-    if (A.theta) A.theta[n] = th;
+    if (A.theta) *at_bytes(A.theta, 4u * n) = th;
     if (A.xhat) {
         int x0 = min((int)floorf(px), W - 2), y0 = min((int)floorf(py), H - 2);
         float a = px - (float)x0, b = py - (float)y0;
-        long m00 = (long)y0 * W + x0;
+        const uint32_t m00 = (uint32_t)(y0 * W + x0);
         float3 X00 = load_point(A.Xii, m00), X10 = load_point(A.Xii, m00 + 1);
         float3 X01 = load_point(A.Xii, m00 + W), X11 = load_point(A.Xii, m00 + W + 1);
         float w00 = (1.f - a) * (1.f - b), w10 = a * (1.f - b), w01 = (1.f - a) * b, w11 = a * b;
-        A.xhat[3 * n + 0] = w00 * X00.x + w10 * X10.x + w01 * X01.x + w11 * X11.x;
-        A.xhat[3 * n + 1] = w00 * X00.y + w10 * X10.y + w01 * X01.y + w11 * X11.y;
-        A.xhat[3 * n + 2] = w00 * X00.z + w10 * X10.z + w01 * X01.z + w11 * X11.z;
+        float* o = at_bytes(A.xhat, 12u * n);
+        o[0] = w00 * X00.x + w10 * X10.x + w01 * X01.x + w11 * X11.x;
+        o[1] = w00 * X00.y + w10 * X10.y + w01 * X01.y + w11 * X11.y;
+        o[2] = w00 * X00.z + w10 * X10.z + w01 * X01.z + w11 * X11.z;
     }
     q.px = px; q.py = py; q.th = th;
 }
@@ -318,14 +322,15 @@ __device__ __forceinline__ long refine_lds(const EdgeArgs& A, long n, const QSta
 // of Sec. 3.2) and the refined index.
 __device__ __forceinline__ void finish(const EdgeArgs& A, long n, const QState& q, long bi) {
     bool ok = bi >= 0 && q.th <= A.max_theta;
-    if (ok && A.Qii) ok = sqrtf(A.Qii[bi] * A.Qji[n]) >= A.conf_min;
+    const uint32_t m = (uint32_t)bi, nn = (uint32_t)n;
+    if (ok && A.Qii) ok = sqrtf(*at_bytes(A.Qii, 4u * m) * *at_bytes(A.Qji, 4u * nn)) >= A.conf_min;
     if (ok && A.max_dist < INFINITY) {
-        float3 xr = load_point(A.Xii, bi);
+        float3 xr = load_point(A.Xii, m);
         float d0 = xr.x - q.xq.x, d1 = xr.y - q.xq.y, d2 = xr.z - q.xq.z;
         ok = sqrtf(d0 * d0 + d1 * d1 + d2 * d2) <= A.max_dist;
     }
-    A.idx[n] = (int32_t)bi;
-    A.valid[n] = ok ? 1 : 0;
+    *at_bytes(A.idx, 4u * nn) = (int32_t)bi;
+    *at_bytes(A.valid, nn) = ok ? 1 : 0;
 }
 
 // One query end to end through global memory.
@@ -408,24 +413,24 @@ constexpr int kRayMargin = 2;
 template <int NT>
 __device__ __forceinline__ void stage_rays(const EdgeArgs& A, float4* lds, int lx, int ly, int rw, int rh) {
     const int tid = threadIdx.x;
-    const int npx = rw * rh, slots = kRecP4 * npx;
+    const int npx = rw * rh, slots = kRecP4 * npx, hw = A.H * A.W;
     const SmallDiv div_rw(rw);
     for (int c0 = tid & ~63; c0 < slots; c0 += NT) {
         const int c = c0 + (tid & 63);
         if (c < slots) {
             const int pix = c >> 1, j = c & 1;
             const int ry = div_rw(pix), rx = pix - ry * rw;
-            __builtin_amdgcn_global_load_lds(A.rays + (long)j * A.H * A.W + (long)(ly + ry) * A.W + lx + rx,
+            __builtin_amdgcn_global_load_lds(at_bytes(A.rays, 16u * (uint32_t)(j * hw + (ly + ry) * A.W + lx + rx)),
                                              (__attribute__((address_space(3))) void*)(lds + c0), 16, 0, 0);
         }
     }
-    const float* z = reinterpret_cast<const float*>(A.rays + (long)kRecP4 * A.H * A.W);
+    const float* z = reinterpret_cast<const float*>(A.rays + (long)kRecP4 * hw);
     float* ldz = reinterpret_cast<float*>(lds + slots);
     for (int c0 = tid & ~63; c0 < npx; c0 += NT) {
         const int c = c0 + (tid & 63);
         if (c < npx) {
             const int ry = div_rw(c), rx = c - ry * rw;
-            __builtin_amdgcn_global_load_lds(z + (long)(ly + ry) * A.W + lx + rx,
+            __builtin_amdgcn_global_load_lds(at_bytes(z, 4u * (uint32_t)((ly + ry) * A.W + lx + rx)),
                                              (__attribute__((address_space(3))) void*)(ldz + c0), 4, 0, 0);
         }
     }
@@ -1073,12 +1078,40 @@ __global__ void __launch_bounds__(TX * TY) fwd_lds_kernel(EdgeArgs A, int remap)
 
 // ---------------------------------------------------------------- batched
 
-// Edge of a global tile id: the last edge whose tile_begin <= tile.
-__device__ __forceinline__ int find_edge(const EdgeArgs* __restrict__ E, int n_edges, int tile) {
-    int lo = 0, hi = n_edges - 1;
+// The arguments of edge e from the table, which no kernel of the launch writes:
+// through the constant address space, so that they are scalar loads, and with
+// their pointers marked global.  Read as ordinary memory the table fills vector
+// registers, and its pointers are generic: every access is then a flat one,
+// which waits for LDS as well.  (Batched forward of 64 edges at 512 x 384 1,550 ->
+// 1,512 us with its prep, of 24 mixed edges 566 -> 550 us.)
+__device__ __forceinline__ EdgeArgs edge_args(const EdgeArgs* E, int e) {
+    static_assert(sizeof(EdgeArgs) % 4 == 0, "whole words");
+    constexpr int kWords = sizeof(EdgeArgs) / 4;
+    typedef const __attribute__((address_space(4))) uint32_t cword_t;
+    cword_t* src = (cword_t*)(uintptr_t)(E + e);
+    uint32_t w[kWords];
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) w[i] = src[i];
+    EdgeArgs A;
+    __builtin_memcpy(&A, w, sizeof A);
+    auto global = [](auto*& p) {
+        typedef typename std::remove_reference<decltype(*p)>::type T;
+        p = (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+    };
+    global(A.Xii); global(A.Xji); global(A.Dii); global(A.Dji); global(A.Qii); global(A.Qji); global(A.p_init);
+    global(A.rays); global(A.p); global(A.idx); global(A.valid); global(A.theta); global(A.xhat);
+    return A;
+}
+__device__ __forceinline__ int edge_tile_begin(const EdgeArgs* E, int e) {
+    return ((const __attribute__((address_space(4))) EdgeArgs*)(uintptr_t)E)[e].tile_begin;
+}
+
+// Edge of a global tile id at or after edge lo: the last whose tile_begin <= tile.
+__device__ __forceinline__ int find_edge(const EdgeArgs* __restrict__ E, int lo, int n_edges, int tile) {
+    int hi = n_edges - 1;
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
-        if (E[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
+        if (edge_tile_begin(E, mid) <= tile) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -1096,7 +1129,7 @@ __global__ void __launch_bounds__(256) batched_prep_kernel(const EdgeArgs* __res
         int mid = (lo + hi + 1) >> 1;
         if (prep_begin[mid] <= blk) lo = mid; else hi = mid - 1;
     }
-    const EdgeArgs& A = E[lo];
+    const EdgeArgs A = edge_args(E, lo);
     prep_tile(A.Xii, const_cast<float4*>(A.rays), A.H, A.W, blk - prep_begin[lo], S);
 }
 
@@ -1113,14 +1146,19 @@ batched_fwd_kernel(const EdgeArgs* __restrict__ E, int n_edges, int total_tiles,
     __shared__ typename std::conditional<
         MODE == 1, TileLds,
         typename std::conditional<MODE == 2, TileLds16<f16_cap<TX, TY, MULTI>()>, int>::type>::type S;
+    int e = 0;
     for (;;) {
         if (threadIdx.x == 0) s_tile = atomicAdd(counter, 1);
         __syncthreads();
-        int tile = s_tile;
+        // Read from LDS, so the compiler does not know that the tile is the same for
+        // every lane; in a scalar register it, the search and the whole argument
+        // block stay scalar.
+        const int tile = __builtin_amdgcn_readfirstlane(s_tile);
         __syncthreads();
         if (tile >= total_tiles) return;
-        int e = find_edge(E, n_edges, tile);
-        const EdgeArgs A = E[e];
+        // A workgroup's tiles ascend, so the search goes on from its last edge.
+        e = find_edge(E, e, n_edges, tile);
+        const EdgeArgs A = edge_args(E, e);
         int local = tile - A.tile_begin;
         int ty = local / A.tiles_x, tx = local - ty * A.tiles_x;
         if constexpr (MODE == 1) {
