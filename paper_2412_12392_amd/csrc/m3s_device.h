@@ -204,7 +204,7 @@ struct WindowRays {
         const int lx = x0 - rx0, ly = y0 - ry0;
         // 0 <= lx <= rw - 2 and 0 <= ly <= rh - 2 (the whole cell in the window).
         if ((uint32_t)lx < (uint32_t)(rw - 1) && (uint32_t)ly < (uint32_t)(rh - 1)) {
-            const uint32_t k = (uint32_t)(ly * rw + lx);
+            const uint32_t k = __umul24((uint32_t)ly, (uint32_t)rw) + (uint32_t)lx;  // one full-rate instruction
             const float4* a = lds + kRecP4 * k;
             const float4* c = a + kRecP4 * rw;
 #pragma unroll
@@ -225,13 +225,18 @@ struct WindowRays {
     }
 };
 
+__device__ __forceinline__ float clampf(float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); }
+
+// Cell origin of coordinate p in [0, size - 1]: min(floor(p), size - 2), formed
+// in fp32 (exact for integers), so p = size - 1 lies on the last cell's far edge.
+// (As a clamp from 0, which it is for p >= 0: one instruction.)
+__device__ __forceinline__ float cell_origin(float p, float cell) { return clampf(floorf(p), 0.f, cell); }
+
 // Ray error of Eq. 2 at pixel (px, py) (inside the domain) for target ray t.
-// The cell origin is min(floor(p), size - 2), formed in fp32 (exact for
-// integers), so p = size - 1 lies on the last cell's far edge.
 template <bool FULL = true, class Src>
 __device__ __forceinline__ void sample_ray_error(const Src& src, float xcell, float ycell, float px, float py,
                                                  float3 t, Sample& s) {
-    const float fx0 = fminf(floorf(px), xcell), fy0 = fminf(floorf(py), ycell);
+    const float fx0 = cell_origin(px, xcell), fy0 = cell_origin(py, ycell);
     const float a = px - fx0, b = py - fy0;
     float4 A[kRecP4], B[kRecP4], C[kRecP4], D[kRecP4];
     float z[4];
@@ -239,7 +244,21 @@ __device__ __forceinline__ void sample_ray_error(const Src& src, float xcell, fl
     ray_error_from<FULL>(A, B, C, D, z, a, b, t, s);
 }
 
-__device__ __forceinline__ float clampf(float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); }
+// asin(s) for 0 <= s <= 1.  Up to 1/2 (a residual angle of 60 degrees) s plus
+// s^3 times a degree-5 polynomial in s^2, fitted at Chebyshev nodes (within 0.6
+// ulp evaluated in fp32; s itself for the angles near the gate), 9 instructions
+// instead of the library's 45.
+__device__ __forceinline__ float asin01(float s) {
+    if (__builtin_expect(s > 0.5f, 0)) return asinf(s);
+    const float y = s * s;
+    float p = 0.03380575f;
+    p = fmaf(p, y, 0.01707786f);
+    p = fmaf(p, y, 0.03111616f);
+    p = fmaf(p, y, 0.04459803f);
+    p = fmaf(p, y, 0.07500099f);
+    p = fmaf(p, y, 0.16666666f);
+    return fmaf(s * y, p, s);
+}
 
 // Levenberg-Marquardt state of one query: current pixel, damping and the
 // sample at the current pixel.
@@ -257,21 +276,25 @@ __device__ __forceinline__ void lm_start(const Src& src, int H, int W, float lam
 // Damped 2x2 step of Eq. 2's normal equations at the current state; false
 // when it is not finite.  A coordinate on its bound whose step points out of
 // the image is held, and the other coordinate takes its own 1-D damped step.
+// on_bound: the pixel lies on an image bound (the test for it is kept out of
+// the iterations, which mostly reject and leave the pixel where it was).
 // Returns the clamped trial pixel.
 __device__ __forceinline__ bool lm_step(const Sample& cur, float lambda, float px, float py, float xmax, float ymax,
-                                        float& qx, float& qy) {
+                                        bool on_bound, float& qx, float& qy) {
     float a00 = cur.a00 + lambda, a01 = cur.a01, a11 = cur.a11 + lambda;
     float g0 = cur.g0, g1 = cur.g1;
     float idet = rcp(a00 * a11 - a01 * a01);
     float dx = -(a11 * g0 - a01 * g1) * idet;
     float dy = -(a00 * g1 - a01 * g0) * idet;
     if (!isfinite(dx) || !isfinite(dy)) return false;
-    bool hold_x = (px <= 0.f && dx < 0.f) || (px >= xmax && dx > 0.f);
-    bool hold_y = (py <= 0.f && dy < 0.f) || (py >= ymax && dy > 0.f);
-    if (__builtin_expect(hold_x | hold_y, 0)) {
-        float fx = -g0 * rcp(a00), fy = -g1 * rcp(a11);
-        dx = hold_x ? 0.f : fx;
-        dy = hold_y ? 0.f : fy;
+    if (__builtin_expect(on_bound, 0)) {
+        bool hold_x = (px <= 0.f && dx < 0.f) || (px >= xmax && dx > 0.f);
+        bool hold_y = (py <= 0.f && dy < 0.f) || (py >= ymax && dy > 0.f);
+        if (hold_x | hold_y) {
+            float fx = -g0 * rcp(a00), fy = -g1 * rcp(a11);
+            dx = hold_x ? 0.f : fx;
+            dy = hold_y ? 0.f : fy;
+        }
     }
     qx = clampf(px + dx, 0.f, xmax);
     qy = clampf(py + dy, 0.f, ymax);
@@ -290,15 +313,17 @@ __device__ __forceinline__ void lm_iterate(const Src& src, int H, int W, float3 
     const float xcell = (float)(W - 2), ycell = (float)(H - 2);
     float px = st.px, py = st.py, lambda = st.lambda;
     Sample cur = st.cur, nxt;
+    auto at_bound = [&](float x, float y) { return (x <= 0.f) | (x >= xmax) | (y <= 0.f) | (y >= ymax); };
+    bool on_bound = at_bound(px, py);
     const int full = final ? iters - 1 : iters;
 #pragma unroll UNROLL
     for (int it = 0; it < full; ++it) {
         float qx, qy;
-        if (!lm_step(cur, lambda, px, py, xmax, ymax, qx, qy)) { lambda *= 10.f; continue; }
+        if (!lm_step(cur, lambda, px, py, xmax, ymax, on_bound, qx, qy)) { lambda *= 10.f; continue; }
         // The trial's cost first; its Jacobian blocks only where it is accepted
         // (on strictly lower cost).  After the first few iterations most lanes
         // reject, and a wave whose lanes all reject skips that part.
-        const float fx0 = fminf(floorf(qx), xcell), fy0 = fminf(floorf(qy), ycell);
+        const float fx0 = cell_origin(qx, xcell), fy0 = cell_origin(qy, ycell);
         float4 A[kRecP4], B[kRecP4], C[kRecP4], D[kRecP4];
         float z[4];
         src.fetch((int)fx0, (int)fy0, A, B, C, D, z);
@@ -310,12 +335,13 @@ __device__ __forceinline__ void lm_iterate(const Src& src, int H, int W, float3 
             cur.c = c;
             px = qx;
             py = qy;
+            on_bound = at_bound(px, py);
         }
         lambda = acc ? lambda * 0.1f : lambda * 10.f;
     }
     if (final && iters > 0) {
         float qx, qy;
-        if (lm_step(cur, lambda, px, py, xmax, ymax, qx, qy)) {
+        if (lm_step(cur, lambda, px, py, xmax, ymax, on_bound, qx, qy)) {
             sample_ray_error<false>(src, xcell, ycell, qx, qy, t, nxt);
             const bool acc = nxt.c < cur.c;
             px = acc ? qx : px;

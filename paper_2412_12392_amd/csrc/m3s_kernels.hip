@@ -207,7 +207,7 @@ __device__ __forceinline__ void lm_finish(const EdgeArgs& A, int x, int y, const
     const uint32_t n = (uint32_t)(y * W + x);
     const float px = st.px, py = st.py;
     *at_bytes(reinterpret_cast<float2*>(A.p), 8u * n) = make_float2(px, py);
-    float th = 2.0f * asinf(fminf(1.0f, sqrtf(st.cur.c) * 0.5f));
+    float th = 2.0f * asin01(fminf(1.0f, sqrtf(st.cur.c) * 0.5f));
     if (A.theta) *at_bytes(A.theta, 4u * n) = th;
     if (A.xhat) {
         int x0 = min((int)floorf(px), W - 2), y0 = min((int)floorf(py), H - 2);
