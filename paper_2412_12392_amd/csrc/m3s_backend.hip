@@ -142,10 +142,12 @@ __device__ __forceinline__ void write_relative_pose(const BackendArgs& A, int e,
 // confidences are gathered one by one (with
 // 8 to 16 matches a lane, 68 to 60 us for 65 edges at 512 x 384 and 45 to 40 us for
 // 199 at 224 x 160).
-// final: 0 = an iteration's accumulation (skipped once the loop has ended), 1 = the final one.
-__global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A, int final_pass) {
+// COST: false = an iteration's accumulation (the system; skipped once the loop
+// has ended), true = the final one (cost and count).
+template <bool COST>
+__global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A) {
     __shared__ float red[kThreads / 64][kMomentStride];
-    if (!final_pass && A.state[0]) return;
+    if (!COST && A.state[0]) return;
     const int e = blockIdx.y;
     const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
     const bool edge_ok = edge_in_range(ei, ej, A.N);
@@ -214,7 +216,7 @@ __global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A, 
         for (int u = 0; u < kGroup; ++u) {
             float q;
             if (ok[u] && confidence_gate(qi[u], qj[u], A.gate, q))
-                accumulate_match(T, xj[u][0], xj[u][1], xj[u][2], xi[u][0], xi[u][1], xi[u][2], q, A.rw, acc);
+                accumulate_match<COST>(T, xj[u][0], xj[u][1], xj[u][2], xi[u][0], xi[u][1], xi[u][2], q, A.rw, acc);
         }
     }
 
@@ -1412,7 +1414,8 @@ hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q,
     for (int it = 0; it <= iters; ++it) {
         const int final_pass = it == iters ? 1 : 0;
         timer_begin("backend_accum", s);
-        backend_accum_kernel<<<grid, kThreads, 0, s>>>(A, final_pass);
+        if (final_pass) backend_accum_kernel<true><<<grid, kThreads, 0, s>>>(A);
+        else backend_accum_kernel<false><<<grid, kThreads, 0, s>>>(A);
         timer_end(s);
         timer_begin("backend_edge", s);
         backend_edge_kernel<<<E, kThreads, 0, s>>>(A, final_pass);

@@ -105,7 +105,10 @@ __device__ __forceinline__ void norm_of(float n2, float& id, float& d) {
 // A pose solve is bound by vector issue here (its operands come from L2): the
 // 37 sums with correctly rounded roots took about 240 instructions a match and
 // 89 us for 65 edges at 512 x 384, this about 140 and 68 us.
-// Adds nothing for a point at the origin or non-finite.
+// Adds nothing for a point at the origin or non-finite.  A pass sums either the
+// system (COST = false: moments 0 .. 27) or the cost and the count (moments 28
+// and 29), never both: the solves read the latter at the final pose only.
+template <bool COST>
 __device__ __forceinline__ void accumulate_match(const float* T, float X0, float X1, float X2, float Y0, float Y1,
                                                  float Y2, float q, const RobustWeights& rw, float* m) {
     const float x0 = fmaf(T[0], X0, fmaf(T[1], X1, fmaf(T[2], X2, T[3])));
@@ -130,9 +133,14 @@ __device__ __forceinline__ void accumulate_match(const float* T, float X0, float
     const float qr = q * rw.w_ray, qd = q * rw.w_dist;
     const float a_ray = __builtin_amdgcn_sqrtf(fmaf(e0, e0, fmaf(e1, e1, e2 * e2)) * qr);
     const float a_dist = fabsf(rd) * __builtin_amdgcn_sqrtf(qd);
+    if constexpr (COST) {
+        const float c_ray = fminf(a_ray, rw.huber), c_dist = fminf(a_dist, rw.huber);
+        m[28] = fmaf(c_ray, fmaf(-0.5f, c_ray, a_ray), fmaf(c_dist, fmaf(-0.5f, c_dist, a_dist), m[28]));
+        m[29] += 1.f;
+        return;
+    }
     const float wr = qr * fminf(1.f, rw.huber * __builtin_amdgcn_rcpf(a_ray));
     const float wd = qd * fminf(1.f, rw.huber * __builtin_amdgcn_rcpf(a_dist));
-    const float c_ray = fminf(a_ray, rw.huber), c_dist = fminf(a_dist, rw.huber);
     const float wri = wr * id, ar = wri * id, cv = wd - ar, wdd = wd * d, wdr = wd * rd;
     m[0] += ar;
     const float cu0 = cv * u0, cu1 = cv * u1, cu2 = cv * u2;
@@ -165,8 +173,6 @@ __device__ __forceinline__ void accumulate_match(const float* T, float X0, float
     m[25] = fmaf(wu2, e0, fmaf(-wu0, e2, m[25]));
     m[26] = fmaf(wu0, e1, fmaf(-wu1, e0, m[26]));
     m[27] = fmaf(wdr, d, m[27]);
-    m[28] = fmaf(c_ray, fmaf(-0.5f, c_ray, a_ray), fmaf(c_dist, fmaf(-0.5f, c_dist, a_dist), m[28]));
-    m[29] += 1.f;
 }
 
 // Value v of the normal equations (kPoseVals) from the summed moments.

@@ -31,6 +31,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "m3s_internal.h"
 #include "m3s_sim3.h"
 
@@ -124,12 +126,12 @@ struct MatchGroup {
 
 template <int PER>
 __device__ __forceinline__ void load_group(const TrackArgs& A, int n0, MatchGroup<PER>& M) {
-    static_assert(PER == 2 || PER == 4, "vector loads of 2 or 4 pixels");
+    static_assert(PER == 1 || PER == 2 || PER == 4, "vector loads of 1, 2 or 4 pixels");
     int mm[PER];
-    if (n0 + PER <= A.N) {
+    if (PER > 1 && n0 + PER <= A.N) {
         const float* x = A.Xk + 3 * (long)n0;
         float xs[3 * PER];
-        uint32_t v;
+        uint32_t v = 0u;
         if constexpr (PER == 4) {
             v = *reinterpret_cast<const u32_any*>(A.valid + n0);
             const i4_any i = *reinterpret_cast<const i4_any*>(A.idx + n0);
@@ -142,7 +144,7 @@ __device__ __forceinline__ void load_group(const TrackArgs& A, int n0, MatchGrou
 #pragma unroll
                 for (int j = 0; j < 4; ++j) xs[4 * k + j] = t[j];
             }
-        } else {
+        } else if constexpr (PER == 2) {
             v = *reinterpret_cast<const u16_any*>(A.valid + n0);
             const i2_any i = *reinterpret_cast<const i2_any*>(A.idx + n0);
             const f2_any q = *reinterpret_cast<const f2_any*>(A.Qk + n0);
@@ -188,14 +190,14 @@ __device__ __forceinline__ void load_group(const TrackArgs& A, int n0, MatchGrou
 // name), and the arithmetic of a lane's matches a third.  The reads do not
 // depend on the solve, so each lane's first matches (all of them up to 2048
 // workgroups) are read before it; the solve has no fp64 division, root or
-// library call in its usual case.  A step of 320 x 240: 9.3 us before, 7.8 now.
-template <int PER>
-__global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int it) {
-    __shared__ float red[kThreads / 64][kMomentStride];
+// library call in its usual case.  A step of 320 x 240: 9.3 us before, 7.0 now.
+template <int NT, int PER, bool COST>
+__global__ void __launch_bounds__(NT) track_step_kernel(TrackArgs A, int it) {
+    __shared__ float red[NT / 64][kMomentStride];
     __shared__ double sum[kVals];
-    __shared__ SumLds<kThreads> part;
+    __shared__ SumLds<NT> part;
     __shared__ double Tn[12];
-    constexpr int kStep = kThreads * PER;
+    constexpr int kStep = NT * PER;
     int n0 = blockIdx.x * kStep + PER * threadIdx.x;
     MatchGroup<PER> M;
     load_group(A, n0, M);
@@ -206,7 +208,7 @@ __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int i
         // Iteration it - 1's system: the same fixed-order sum and solve in
         // every workgroup, from the pose of the previous parity buffer.
         const int prev = (it + 1) & 1;
-        sum_partials<kThreads>(A.partials + (size_t)prev * A.nb * kMomentStride, A.nb, part, sum);
+        sum_partials<NT>(A.partials + (size_t)prev * A.nb * kMomentStride, A.nb, part, sum);
         if (threadIdx.x == 0) {
             for (int j = 0; j < 12; ++j) Tl[j] = A.T64[12 * prev + j];
             solved = A.stat[2 * prev];
@@ -230,13 +232,13 @@ __global__ void __launch_bounds__(kThreads) track_step_kernel(TrackArgs A, int i
         for (int u = 0; u < PER; ++u) {
             float q;
             if (M.ok[u] && confidence_gate(M.qf[u], M.qk[u], A.gate, q))
-                accumulate_match(T, M.xf[u][0], M.xf[u][1], M.xf[u][2], M.xk[u][0], M.xk[u][1], M.xk[u][2], q, A.rw, acc);
+                accumulate_match<COST>(T, M.xf[u][0], M.xf[u][1], M.xf[u][2], M.xk[u][0], M.xk[u][1], M.xk[u][2], q, A.rw, acc);
         }
         n0 += gridDim.x * kStep;
         if (n0 >= A.N) break;
         load_group(A, n0, M);
     }
-    block_moments<kThreads>(acc, red, A.partials + ((size_t)(it & 1) * A.nb + blockIdx.x) * kMomentStride);
+    block_moments<NT>(acc, red, A.partials + ((size_t)(it & 1) * A.nb + blockIdx.x) * kMomentStride);
     if (blockIdx.x == 0 && threadIdx.x < 12) A.T64[12 * (it & 1) + threadIdx.x] = Tn[threadIdx.x];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         A.stat[2 * (it & 1)] = solved;
@@ -317,13 +319,20 @@ __global__ void __launch_bounds__(256) fuse_kernel(int N, int first, const float
 
 }  // namespace
 
-// Matches per lane at a time: 2 while that needs at most one workgroup per CU
-// (an MI355X has 256), else 4, since every workgroup sums all rows.  320 x 240 (150
-// rows): 7.7 us a step with 2, 8.4 with 4; 512 x 384: 9.0 (384 rows) and 7.9 (192).
-static int matches_per_lane(int N) { return N <= 256 * kThreads * 2 ? 2 : 4; }
+// Threads and matches per lane of a workgroup: 512 x 1 while that needs at most
+// one workgroup per CU (an MI355X has 256), else 256 x 4, since every workgroup
+// sums all rows.  10-iteration solve at 320 x 240: 78.6 us with 512 x 1, 86 with
+// 256 x 2, 84.8 with 1024 x 1; tracked frame at 512 x 384: 183 us with 256 x 4 or
+// 512 x 2, 196 with 512 x 4, 189 with 1024 x 1.
+struct TrackShape { int threads, per; };
+static TrackShape track_shape(int N) {
+    if (N <= 256 * 512) return {512, 1};
+    return {256, 4};
+}
 
 int track_blocks(int N) {
-    const int per = kThreads * matches_per_lane(N);
+    const TrackShape t = track_shape(N);
+    const int per = t.threads * t.per;
     const int nb = N / per + (N % per != 0);
     return nb < 1 ? 1 : (nb > kMaxBlocks ? kMaxBlocks : nb);
 }
@@ -347,10 +356,17 @@ hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* 
     A.info = info;
     const int nb = track_blocks(N);
     A.nb = nb;
+    const bool small = N <= 256 * 512;
     for (int it = 0; it <= iters; ++it) {
         timer_begin("track_step", s);
-        if (matches_per_lane(N) == 2) track_step_kernel<2><<<nb, kThreads, 0, s>>>(A, it);
-        else track_step_kernel<4><<<nb, kThreads, 0, s>>>(A, it);
+        auto step = [&](auto cost) {
+            constexpr bool C = decltype(cost)::value;
+            if (small) track_step_kernel<512, 1, C><<<nb, 512, 0, s>>>(A, it);
+            else track_step_kernel<256, 4, C><<<nb, 256, 0, s>>>(A, it);
+        };
+        // The last launch sums the cost and the count at the final pose.
+        if (it == iters) step(std::true_type{});
+        else step(std::false_type{});
         timer_end(s);
     }
     timer_begin("track_final", s);

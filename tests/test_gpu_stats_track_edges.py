@@ -32,8 +32,8 @@ def test_stats_exact(H, W, kind):
     assert counts == [int(use.sum()), len(np.unique(idx[use]))]
 
 
-# Pixel counts that leave 0, 1 and 3 over a lane's 2 or 4 matches, on both sides of the change
-# from 2 to 4 (131,072 pixels) and beyond what one pass of the grid covers with 4 (2,097,152).
+# Pixel counts that leave 0, 1 and 3 over a lane's 4 matches, on both sides of the change from 1
+# match a lane to 4 (131,072 pixels) and beyond what one pass of the grid covers (2,097,152).
 @pytest.mark.parametrize("H,W", [(2, 2), (3, 3), (29, 53), (256, 512), (257, 511), (1449, 1449)])
 def test_track_pixel_counts(H, W):
     print("track", H, W, flush=True)
