@@ -686,9 +686,9 @@ __device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
 // costs the latency of one column.  Eliminated one column at a time in keyframe
 // order, a 31-column system (a 32-keyframe sequence with 3 closures) took 31
 // steps of about 2.3 us and its factor had 115 blocks: 101 us; here it is 6
-// levels, 89 blocks and 37 us.  A 96-keyframe sequence with 8 closures had
+// levels, 89 blocks and 35 us.  A 96-keyframe sequence with 8 closures had
 // 791 blocks, more than LDS holds, and took the dense solve, 3,578 us; here it
-// is 10 levels, 286 blocks and 81 us.
+// is 9 levels, 288 blocks and 66 us.
 
 constexpr int kPatThreads = 512;
 
@@ -728,95 +728,128 @@ __device__ __forceinline__ int wave_least(int v) {
                min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
-// The elimination, in one wave without barriers: lane l holds the rows of
-// keyframes l and l + 64 (HALVES = 2) of the remaining graph.  A level takes,
-// in order of degree then index, every keyframe of degree at most
-// max(least + 1, 2) that no earlier one of the level neighbours; eliminating it
-// joins its neighbours, which leave the level.  A serial chain per keyframe:
-// one wave minimum and some register operations without branches.  Returns the
-// number of levels.
-template <int HALVES>
-__device__ __forceinline__ int eliminate(int nb, const uint32_t (*adj)[kPatWords], uint32_t (*col)[kPatWords],
-                                         uint32_t (*row)[kPatWords], uint8_t* perm, uint8_t* pos, uint16_t* lvl) {
-    constexpr int WORDS = 2 * HALVES;
+// The elimination, in one wave without barriers: lane l holds keyframes l and
+// l + 64 of the remaining graph (rows r; adj holds them for the other lanes).  A
+// level is a maximal independent set among the keyframes of degree at most
+// max(least + 1, 2), found in rounds: a candidate that comes before all its
+// candidate neighbours is taken, and its neighbours drop out.  The order is by
+// degree, then by the parity of the index among the remaining keyframes (which
+// takes every other keyframe of a chain in one round; the parity alternates from
+// level to level), then by index.  Eliminating the level joins the neighbours of
+// each of its keyframes.  About as many rounds as levels (9 levels in 12 rounds
+// for 96 keyframes with 8 closures); taking the keyframes one at a time, least
+// degree first, gave the same fill and number of levels in a serial chain of
+// 0.27 to 0.43 us a keyframe.  Returns the number of levels.
+__device__ __forceinline__ int eliminate(int nb, uint32_t (*adj)[kPatWords], uint32_t (*col)[kPatWords],
+                                         uint32_t (*row)[kPatWords], int32_t* keys, uint8_t* perm, uint8_t* pos,
+                                         uint16_t* lvl) {
+    static_assert(kPatWords == 4, "two keyframes per lane, two words each");
     const int lane = threadIdx.x & 63;
-    // r: neighbours left; mine: positions of the columns that hold the keyframe;
-    // self: its own bit; gone: all ones once eliminated (keys are positive).
-    uint32_t r[HALVES][WORDS], mine[HALVES][WORDS], self[HALVES][WORDS];
-    int gone[HALVES], key[HALVES], cand[HALVES];
-    auto rekey = [&](int h) {
-        int d = 0;
+    uint32_t r[2][kPatWords], mine[2][kPatWords];  // neighbours left; positions of the columns that hold the keyframe
+    bool alive[2];
 #pragma unroll
-        for (int w = 0; w < WORDS; ++w) d += __popc(r[h][w]);
-        key[h] = (d * 128 + lane + 64 * h) | gone[h];
-    };
+    for (int h = 0; h < 2; ++h) {
+        alive[h] = lane + 64 * h < nb;
 #pragma unroll
-    for (int h = 0; h < HALVES; ++h) {
-        const int x = lane + 64 * h;
-        gone[h] = x < nb ? 0 : INT_MAX;
-#pragma unroll
-        for (int w = 0; w < WORDS; ++w) {
-            r[h][w] = x < nb ? adj[x][w] : 0u;
+        for (int w = 0; w < kPatWords; ++w) {
+            r[h][w] = alive[h] ? adj[lane + 64 * h][w] : 0u;
             mine[h][w] = 0u;
-            self[h][w] = (x >> 5) == w ? 1u << (x & 31) : 0u;
         }
-        rekey(h);
     }
-    // By mask: a conditional here would index the register arrays in memory.
-    auto pick = [](uint32_t a, uint32_t b, uint32_t mask) { return a ^ ((a ^ b) & mask); };
+    auto below = [&](uint64_t m) { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)); };
+    // Word w of a set held as two 64-bit masks.
+    auto word = [](const uint64_t (&m)[2], int w) { return (uint32_t)(m[w >> 1] >> (32 * (w & 1))); };
     int k = 0, nlev = 0;
     while (k < nb) {
         if (lane == 0) lvl[nlev] = (uint16_t)k;
-        ++nlev;
-        const int top = (max((wave_least(min(key[0], key[HALVES - 1])) >> 7) + 1, 2) + 1) * 128;
+        int deg[2], least = INT_MAX;
 #pragma unroll
-        for (int h = 0; h < HALVES; ++h) cand[h] = key[h] < top ? key[h] : INT_MAX;
-        for (;;) {
-            const int best = wave_least(min(cand[0], cand[HALVES - 1]));
-            if (best == INT_MAX) break;
-            const int v = best & 127;
-            uint32_t rv[WORDS];
+        for (int h = 0; h < 2; ++h) {
+            deg[h] = 0;
 #pragma unroll
-            for (int w = 0; w < WORDS; ++w)
-                rv[w] = (uint32_t)__builtin_amdgcn_readlane((int)pick(r[0][w], r[HALVES - 1][w], v >= 64 ? ~0u : 0u), v & 63);
-            if (lane == 0) {
-                perm[k] = (uint8_t)v;
-                pos[v] = (uint8_t)k;
-            }
-#pragma unroll
-            for (int w = 0; w < WORDS; ++w)
-                if (lane == w) col[k][w] = rv[w];
-#pragma unroll
-            for (int h = 0; h < HALVES; ++h) {
-                // Keyframe lane + 64 h is on bit lane & 31 of word 2 h or 2 h + 1.
-                const uint32_t word = pick(rv[2 * h], rv[2 * h + 1], (lane & 32) ? ~0u : 0u);
-                const uint32_t nbr = 0u - ((word >> (lane & 31)) & 1u);
-                gone[h] = lane + 64 * h == v ? INT_MAX : gone[h];
-#pragma unroll
-                for (int w = 0; w < WORDS; ++w) {
-                    const uint32_t vbit = (v >> 5) == w ? 1u << (v & 31) : 0u, kbit = (k >> 5) == w ? 1u << (k & 31) : 0u;
-                    r[h][w] = (r[h][w] | (rv[w] & nbr)) & ~(self[h][w] | vbit);
-                    mine[h][w] |= kbit & nbr;
-                }
-                rekey(h);
-                cand[h] |= gone[h] | (int)(nbr & 0x7fffffffu);
-            }
-            ++k;
+            for (int w = 0; w < kPatWords; ++w) deg[h] += __popc(r[h][w]);
+            if (alive[h]) least = min(least, deg[h]);
         }
+        const int top = max(wave_least(least) + 1, 2);
+        const uint64_t left[2] = {__ballot(alive[0]), __ballot(alive[1])};
+        int key[2];
+        bool cand[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int rank = (h ? (int)__popcll(left[0]) : 0) + below(left[h]);
+            key[h] = deg[h] * 256 + ((rank + nlev) & 1) * 128 + lane + 64 * h;
+            cand[h] = alive[h] && deg[h] <= top;
+            keys[lane + 64 * h] = key[h];
+        }
+        uint64_t level[2] = {0ull, 0ull};
+        for (;;) {
+            const uint64_t cm[2] = {__ballot(cand[0]), __ballot(cand[1])};
+            if ((cm[0] | cm[1]) == 0ull) break;
+            bool take[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                take[h] = cand[h];
+#pragma unroll
+                for (int w = 0; w < kPatWords; ++w) {
+                    uint32_t m = cand[h] ? r[h][w] & word(cm, w) : 0u;
+                    while (m) {
+                        take[h] = take[h] && key[h] < keys[32 * w + __builtin_ctz(m)];
+                        m &= m - 1u;
+                    }
+                }
+            }
+            const uint64_t tm[2] = {__ballot(take[0]), __ballot(take[1])};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                uint32_t near = 0u;
+#pragma unroll
+                for (int w = 0; w < kPatWords; ++w) near |= r[h][w] & word(tm, w);
+                cand[h] = cand[h] && !take[h] && near == 0u;
+                if (take[h]) {
+                    const int x = lane + 64 * h, p = k + (h ? (int)__popcll(tm[0]) : 0) + below(tm[h]);
+                    perm[p] = (uint8_t)x;
+                    pos[x] = (uint8_t)p;
+#pragma unroll
+                    for (int w = 0; w < kPatWords; ++w) col[p][w] = r[h][w];
+                    alive[h] = false;
+                }
+                level[h] |= tm[h];
+            }
+            k += (int)(__popcll(tm[0]) + __popcll(tm[1]));
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int x = lane + 64 * h;
+#pragma unroll
+            for (int w = 0; w < kPatWords; ++w) {
+                uint32_t m = alive[h] ? r[h][w] & word(level, w) : 0u;
+                while (m) {
+                    const int v = 32 * w + __builtin_ctz(m), p = pos[v];
+                    m &= m - 1u;
+#pragma unroll
+                    for (int q = 0; q < kPatWords; ++q) {
+                        r[h][q] |= col[p][q];
+                        mine[h][q] |= (p >> 5) == q ? 1u << (p & 31) : 0u;
+                    }
+                }
+            }
+#pragma unroll
+            for (int w = 0; w < kPatWords; ++w)
+                r[h][w] = alive[h] ? r[h][w] & ~(word(level, w) | ((x >> 5) == w ? 1u << (x & 31) : 0u)) : 0u;
+        }
+        ++nlev;
     }
 #pragma unroll
-    for (int h = 0; h < HALVES; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int w = 0; w < kPatWords; ++w) row[lane + 64 * h][w] = w < WORDS ? mine[h][w < WORDS ? w : 0] : 0u;
-    if (HALVES == 1)
-        for (int i = lane; i < nb; i += 64)
-            for (int w = WORDS; w < kPatWords; ++w) col[i][w] = 0u;
+        for (int w = 0; w < kPatWords; ++w) row[lane + 64 * h][w] = mine[h][w];
     return nlev;
 }
 
 // Once per call.  Workgroup 0: elimination order, levels, the factor's blocks,
 // and for every block the edges that enter it and the products it takes.  It is
-// a chain of short serial parts: 20 us for 32 keyframes and 75 us for
+// a chain of short serial parts: 18 us for 32 keyframes and 44 us for
 // 96, from 60 and 164 us with the wave minimum through LDS permutes, each slot's
 // products found by walking every earlier column and its edges by one lane.  The
 // other workgroups: the fp64 poses and the edges' relative poses at T_in.
@@ -852,7 +885,7 @@ __global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs 
     }
     __syncthreads();
     if (tid < 64) {
-        const int nlev = nb <= 64 ? eliminate<1>(nb, adj, col, row, perm, pos, lvl) : eliminate<2>(nb, adj, col, row, perm, pos, lvl);
+        const int nlev = eliminate(nb, adj, col, row, cursor, perm, pos, lvl);
         if (lane == 0) {
             lvl[nlev] = (uint16_t)nb;
             nlev_s = nlev;
@@ -945,9 +978,10 @@ __global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs 
                 // H_ii, H_jj += blk; H_ij -= blk, H_ji -= blk^T: a row owned by j reads it transposed.
                 // (An edge's two keyframes differ; no branches in the test.)
                 auto hits = [&](int2 c) { return ((int)(c.x == x) | (int)(c.y == x)) & ((int)(c.x == z) | (int)(c.y == z)); };
-                int c = 0;
+                uint64_t hit = 0ull;  // of the at most 64 edges of the lane
 #pragma unroll 4
-                for (int t = t0; t < t1; ++t) c += hits(chunk[t]);
+                for (int t = t0; t < t1; ++t) hit |= (uint64_t)hits(chunk[t]) << (t - t0);
+                const int c = (int)__popcll(hit);
                 int inc = c;
                 for (int o = 1; o < 8; o <<= 1) {
                     const int u = __shfl_up(inc, o, 8);
@@ -956,12 +990,13 @@ __global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs 
                 const int all = __shfl(inc, 7, 8);
                 if (pass) {
                     int at = cursor[s] + inc - c;
-                    for (int t = t0; c > 0 && t < t1; ++t)
-                        if (hits(chunk[t])) {
-                            const bool own = chunk[t].x == x;
-                            A.elist[at++] = (uint32_t)(b + t) | (own ? kEdgeOwnI : 0u) |
-                                            (x != z && !own ? kEdgeTransposed : 0u);
-                        }
+                    while (hit) {
+                        const int t = t0 + __builtin_ctzll(hit);
+                        hit &= hit - 1ull;
+                        const bool own = chunk[t].x == x;
+                        A.elist[at++] = (uint32_t)(b + t) | (own ? kEdgeOwnI : 0u) |
+                                        (x != z && !own ? kEdgeTransposed : 0u);
+                    }
                 }
                 // The eight lanes have read the cursor (they are of one wave).
                 if (sub == 7) cursor[s] += all;
