@@ -597,7 +597,7 @@ __device__ __forceinline__ void tile_lds(const EdgeArgs& A, int tx, int ty, Tile
 
 typedef _Float16 h2_t __attribute__((ext_vector_type(2)));
 
-constexpr int kRegionPx16 = 832;          // 832 px x 48 B = 39 KiB: four workgroups per CU
+constexpr int kRegionPx16 = 844;          // 844 px x 48 B = 39.6 KiB: four workgroups per CU
 constexpr int kRegionPx16Multi = 1088;    // the multi-level kernel: 51 KiB, three workgroups per CU
 constexpr int kRegionPx16Small = 256;     // 8 x 8 tiles: 12 KiB, twelve one-wave workgroups per CU
 
@@ -660,8 +660,22 @@ __device__ __forceinline__ float exact24(const float* __restrict__ q, const floa
     return acc;
 }
 
-// Pass 1 over a window that lies inside the image, for a radius R and a
-// candidate spacing SP fixed at compile time: the candidates of a row are unrolled (LDS addresses are the
+// Lattice steps (of spacing 2^lev) by which a window of the given reach around c
+// has to move to lie inside [0, size), for size >= 2 reach + 2^lev.
+__device__ __forceinline__ int slide_steps(int c, int reach, int lev, int size) {
+    const int up = (1 << lev) - 1, lo = reach - c, hi = c + reach - (size - 1);
+    return (max(lo, 0) + up >> lev) - (max(hi, 0) + up >> lev);
+}
+
+// Whether scan16 covers a level, with the image large enough for its windows to
+// slide inside (the same for every lane).
+__device__ __forceinline__ bool slides(int r, int lev, int H, int W) {
+    const int least = 2 * (r << lev) + (1 << lev);
+    return ((lev == 0 && r >= 2 && r <= 4) || (lev == 1 && r == 3)) && H >= least && W >= least;
+}
+
+// Pass 1 over a window, for a radius R and a candidate spacing SP fixed at
+// compile time: the candidates of a row are unrolled (LDS addresses are the
 // row base plus immediate offsets), the row's scores are kept in registers,
 // the running maximum takes the row's maximum, and each candidate of the row
 // survives if its score is within tau of that running maximum.  A candidate
@@ -671,11 +685,34 @@ __device__ __forceinline__ float exact24(const float* __restrict__ q, const floa
 // window on bit N - 1 - j; a bit reversal then gives the row-major masks of
 // the generic pass (candidate j on bit j).  w: LDS record of the window's
 // top-left candidate.
-template <int R, int SP, int CAP>
-__device__ __forceinline__ void scan16_inside(const uint32_t* q16, const uint4* __restrict__ w, int rw, float tau,
-                                              float& run, uint64_t& mask0, uint64_t& mask1) {
+// CLIP: some query's window reaches beyond the image.  It has slid inside by kx
+// columns and ky rows, so that every lane scans S x S staged candidates, and those
+// outside its own window score -inf (one select each).  Before, such waves took a
+// per-lane loop over the candidates inside the image, about half as much again as
+// the unrolled pass: the 64 x 48 pair, all of whose tiles lie at the border, took
+// 20.5 us and takes 17.8; 512 x 384 31.2 and 30.3.
+template <int R, int SP, int CAP, bool CLIP>
+__device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restrict__ w, int rw, float tau, int kx,
+                                       int ky, float& run, uint64_t& mask0, uint64_t& mask1) {
     constexpr int S = 2 * R + 1, N = S * S;
     static_assert(N <= 128 && S < 32, "mask width");
+    bool in[S];
+#pragma unroll
+    for (int dx = 0; dx < S; ++dx) in[dx] = !CLIP || (uint32_t)(dx + kx) < (uint32_t)S;
+    // Scores of window row dy, and the least score that survives.
+    auto row = [&](int dy, float (&sc)[S]) {
+#pragma unroll
+        for (int dx = 0; dx < S; ++dx) {
+            sc[dx] = dot16(q16, w[SP * dx], w[SP * dx + CAP], w[SP * dx + 2 * CAP]);
+            if constexpr (CLIP) sc[dx] = in[dx] ? sc[dx] : -INFINITY;
+        }
+        float rm = sc[0];
+#pragma unroll
+        for (int dx = 1; dx < S; ++dx) rm = fmaxf(rm, sc[dx]);
+        const bool on = !CLIP || (uint32_t)(dy + ky) < (uint32_t)S;
+        run = on ? fmaxf(run, rm) : run;
+        return on ? run - tau : INFINITY;
+    };
     if constexpr (N <= 64) {
         // The whole mask in one word: candidate (dy, dx) at bit dy * S + dx,
         // the row-major order the survivor pass pops in (bit values 1 .. 2^(S-1)
@@ -684,14 +721,7 @@ __device__ __forceinline__ void scan16_inside(const uint32_t* q16, const uint4* 
 #pragma unroll 1
         for (int dy = 0; dy < S; ++dy, w += SP * rw) {
             float sc[S];
-#pragma unroll
-            for (int dx = 0; dx < S; ++dx)
-                sc[dx] = dot16(q16, w[SP * dx], w[SP * dx + CAP], w[SP * dx + 2 * CAP]);
-            float rm = sc[0];
-#pragma unroll
-            for (int dx = 1; dx < S; ++dx) rm = fmaxf(rm, sc[dx]);
-            run = fmaxf(run, rm);
-            const float thr = run - tau;
+            const float thr = row(dy, sc);
             uint32_t rb = 0;
 #pragma unroll
             for (int dx = 0; dx < S; ++dx) rb |= sc[dx] >= thr ? (1u << dx) : 0u;
@@ -705,14 +735,7 @@ __device__ __forceinline__ void scan16_inside(const uint32_t* q16, const uint4* 
 #pragma unroll 1
     for (int dy = 0; dy < S; ++dy, w += SP * rw) {
         float sc[S];
-#pragma unroll
-        for (int dx = 0; dx < S; ++dx)
-            sc[dx] = dot16(q16, w[SP * dx], w[SP * dx + CAP], w[SP * dx + 2 * CAP]);
-        float rm = sc[0];
-#pragma unroll
-        for (int dx = 1; dx < S; ++dx) rm = fmaxf(rm, sc[dx]);
-        run = fmaxf(run, rm);
-        const float thr = run - tau;
+        const float thr = row(dy, sc);
         uint32_t rb = 0;
 #pragma unroll
         for (int dx = 0; dx < S; ++dx) rb = rb + rb + (sc[dx] >= thr ? 1u : 0u);
@@ -827,10 +850,10 @@ __device__ __forceinline__ void f16_scan_band(const EdgeArgs& A, const Query16& 
 // holds every candidate inside the image.  dnorm: bound on |d| over the
 // region, dl1: bound on |d|_1.
 template <int CAP>
-__device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query16& Q, int mx0, int my0, int sp,
+__device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query16& Q, int mx0, int my0, int lev,
                                                  const uint4* __restrict__ sd, int rx0, int ry0, int rw, float dnorm,
                                                  float dl1) {
-    const int H = A.H, W = A.W, r = A.r, side = 2 * r + 1;
+    const int H = A.H, W = A.W, r = A.r, side = 2 * r + 1, sp = 1 << lev;
     const float tau = f16_tau(Q, dnorm, dl1);
 
     // Pass 1: fp16 scores in row-major window order over the candidates
@@ -839,20 +862,22 @@ __device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query1
     const uint4* c0 = sd + (my0 - ry0) * rw + (mx0 - rx0);
     float run = dot16(Q.q16, c0[0], c0[CAP], c0[2 * CAP]);
     uint64_t mask0 = 0, mask1 = 0;
-    const int reach = r * sp;
-    // Wave-uniform choice: the unrolled scan when every active lane's window
-    // lies inside the image, the bounded loop otherwise.
-    const bool whole = mx0 - reach >= 0 && mx0 + reach <= W - 1 && my0 - reach >= 0 && my0 + reach <= H - 1;
-    const uint4* w = sd + (my0 - reach - ry0) * rw + (mx0 - reach - rx0);
-    const bool all_whole = __all(whole) != 0;
-    if (all_whole && sp == 1 && r == 3) {
-        scan16_inside<3, 1, CAP>(Q.q16, w, rw, tau, run, mask0, mask1);
-    } else if (all_whole && sp == 1 && r == 2) {
-        scan16_inside<2, 1, CAP>(Q.q16, w, rw, tau, run, mask0, mask1);
-    } else if (all_whole && sp == 1 && r == 4) {
-        scan16_inside<4, 1, CAP>(Q.q16, w, rw, tau, run, mask0, mask1);
-    } else if (all_whole && sp == 2 && r == 3) {
-        scan16_inside<3, 2, CAP>(Q.q16, w, rw, tau, run, mask0, mask1);
+    const int reach = r << lev;
+    int kx = 0, ky = 0;
+    if (slides(r, lev, H, W)) {
+        // The unrolled scan; windows that reach beyond the image slid inside it.
+        kx = slide_steps(mx0, reach, lev, W);
+        ky = slide_steps(my0, reach, lev, H);
+        const uint4* w = sd + (my0 + sp * ky - reach - ry0) * rw + (mx0 + sp * kx - reach - rx0);
+        const bool clip = __any((kx | ky) != 0) != 0;  // the same for every lane of the wave
+        auto scan = [&](auto R, auto SP) {
+            if (clip) scan16<decltype(R)::value, decltype(SP)::value, CAP, true>(Q.q16, w, rw, tau, kx, ky, run, mask0, mask1);
+            else scan16<decltype(R)::value, decltype(SP)::value, CAP, false>(Q.q16, w, rw, tau, 0, 0, run, mask0, mask1);
+        };
+        if (lev > 0) scan(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
+        else if (r == 3) scan(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
+        else if (r == 2) scan(std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{});
+        else scan(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
     } else {
         for (int dy = -r; dy <= r; ++dy) {
             const int my = my0 + sp * dy;
@@ -871,7 +896,7 @@ __device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query1
         }
     }
     // Pass 2: exact scores of the survivors.
-    return f16_rescore(A, Q, mx0, my0, sp, mask0, mask1);
+    return f16_rescore(A, Q, mx0 + sp * kx, my0 + sp * ky, sp, mask0, mask1);
 }
 
 // Stages region rows [ly, ly + rh) x columns [lx, lx + rw) of D^i_i into the
@@ -975,8 +1000,12 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, Tile
         const int sp = 1 << lev, reach = r * sp;
         int lx = INT_MAX, hx = INT_MIN, ly = INT_MAX, hy = INT_MIN;
         if (live) {
-            lx = max(cx - reach, 0); hx = min(cx + reach, W - 1);
-            ly = max(cy - reach, 0); hy = min(cy + reach, H - 1);
+            // (The window as scan16 takes it, slid inside the image.)
+            const bool sl = slides(r, lev, H, W);
+            const int wx = sl ? cx + sp * slide_steps(cx, reach, lev, W) : cx;
+            const int wy = sl ? cy + sp * slide_steps(cy, reach, lev, H) : cy;
+            lx = max(wx - reach, 0); hx = min(wx + reach, W - 1);
+            ly = max(wy - reach, 0); hy = min(wy + reach, H - 1);
         }
         block_box<NT>(lx, hx, ly, hy, S.box);  // ends with a barrier: the previous level is done with S
         const int rw = hx - lx + 1, rh = hy - ly + 1;
@@ -1037,7 +1066,7 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, Tile
             if (live) query();
             if (live) {
                 const float dnorm = sqrtf(pn2) * 1.0001f;
-                lb = use16 ? refine_f16_level<CAP>(A, Q, cx, cy, sp, S.desc, lx, ly, rw, dnorm, kSqrt24Up * dnorm)
+                lb = use16 ? refine_f16_level<CAP>(A, Q, cx, cy, lev, S.desc, lx, ly, rw, dnorm, kSqrt24Up * dnorm)
                            : refine_global_level<24>(A, Q.qd, cx, cy, sp);
             }
         }
@@ -1600,11 +1629,14 @@ static void launch_fwd_tile(const EdgeArgs& A, bool desc_regs, int mode, bool re
     const int tiles = ((A.W + TX - 1) / TX) * ((A.H + TY - 1) / TY);
     const int grid = remap ? ((tiles + kXcds - 1) / kXcds) * kXcds : tiles;
     const int rm = remap ? 1 : 0;
-    if (mode == 2 && desc_regs && A.levels > 1)
-        fwd_f16_kernel<TX, TY, true><<<grid, TX * TY, 0, s>>>(A, rm);
-    else if (mode == 2 && desc_regs)
-        fwd_f16_kernel<TX, TY, false><<<grid, TX * TY, 0, s>>>(A, rm);
-    else if (mode == 1 && desc_regs)
+    if constexpr (TX == TY) {  // the fp16 configurations have square tiles
+        if (mode == 2 && desc_regs) {
+            if (A.levels > 1) fwd_f16_kernel<TX, TY, true><<<grid, TX * TY, 0, s>>>(A, rm);
+            else fwd_f16_kernel<TX, TY, false><<<grid, TX * TY, 0, s>>>(A, rm);
+            return;
+        }
+    }
+    if (mode == 1 && desc_regs)
         fwd_lds_kernel<TX, TY><<<grid, TX * TY, 0, s>>>(A, rm);
     else if (desc_regs)
         fwd_kernel<TX, TY, 24><<<grid, TX * TY, 0, s>>>(A, rm);
@@ -1665,7 +1697,7 @@ static void launch_batched_tile(const EdgeArgs* table, int n_edges, int total_ti
             }
             return;
         }
-    } else {
+    } else if constexpr (TX == TY) {
         if (mode == 2 && desc_regs) {
             if (levels > 1)
                 batched_fwd_kernel<TX, TY, 24, 2, kRayMargin, 1, true><<<grid, TX * TY, 0, s>>>(table, n_edges,

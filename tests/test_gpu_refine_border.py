@@ -1,0 +1,44 @@
+"""The refine where windows reach beyond the image: the unrolled scan slides
+them inside.  Frames around the least size that allows it (2 r 2^l + 2^l) and
+initial pixels in the corners, every output bit against the plain scan of global
+memory (tile configuration 0), which has no windows to slide."""
+import numpy as np
+import pytest
+import torch
+
+import parity
+import synth
+from paper_2412_12392_amd import match, match_batched, params, set_launch, EdgeInput
+
+pytestmark = pytest.mark.gpu
+
+# H, W, r, levels
+CASES = [(H, W, r, 1) for r in (2, 3, 4) for H, W in ((2 * r, 2 * r + 9), (2 * r + 1, 2 * r + 1), (2 * r + 2, 40), (33, 2 * r))]
+CASES += [(13, 14, 3, 2), (14, 14, 3, 2), (14, 31, 3, 2), (40, 15, 3, 2), (27, 28, 3, 3), (37, 53, 2, 2), (37, 53, 5, 1)]
+
+
+@pytest.mark.parametrize("H,W,r,levels", CASES)
+@pytest.mark.parametrize("tile", [5, 6])
+def test_refine_windows_beyond_the_image(H, W, r, levels, tile):
+    print("refine border", H, W, r, levels, tile, flush=True)
+    t = parity.pair_tensors(synth.make_pair(H, W, 900 + H * W + r, conf=True))
+    rng = np.random.Generator(np.random.PCG64(H * W))
+    # Every query starts, and with K = 0 stays, at a pixel of the border or anywhere.
+    corner = rng.integers(0, 2, size=(H, W, 2)) * np.array([W - 1.0, H - 1.0])
+    some = rng.uniform(0, 1, size=(H, W, 2)) * np.array([W - 1.0, H - 1.0])
+    p0 = torch.from_numpy(np.where(rng.uniform(size=(H, W, 1)) < 0.5, corner, some).astype(np.float32)).cuda()
+    args = (t["Xii"], t["Xji"], t["Dii"], t["Dji"], t["Qii"], t["Qji"])
+    for init, K in ((p0, 0), (None, 10)):
+        prm = params(max_iter=K, refine_radius=r, refine_levels=levels, max_theta=10.0)
+        got = []
+        for cfg in (0, tile):
+            set_launch(tile_config=cfg)
+            try:
+                res = match(*args, init, prm, want_xhat=True)
+                out = match_batched([EdgeInput(*args, init)], prm, graph=False, want_xhat=True)[0]
+                got += [parity.result_numpy(res), parity.result_numpy(out)]
+            finally:
+                set_launch()
+        for g in got[1:]:
+            for k in ("p", "idx", "valid", "theta", "xhat"):
+                assert np.array_equal(got[0][k], g[k], equal_nan=True), (k, K)
