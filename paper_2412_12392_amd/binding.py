@@ -61,7 +61,7 @@ def _ptr(t: Optional[torch.Tensor], dtype=torch.float32, shape=None) -> int:
         raise TypeError("expected %s, got %s" % (dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("tensors must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("expected shape %s, got %s" % (tuple(shape), tuple(t.shape)))
     return t.data_ptr()
 
@@ -71,12 +71,23 @@ def _stream(stream) -> int:
     return s.cuda_stream
 
 
+def _streams(stream, device):
+    """(stream the call launches on, stream that orders its workspace): `stream`, or the current
+    one, looked up once, with the lookup on `device` left to the case that it is not the current
+    device.  Each lookup costs 2.6 us, with a device argument more; a small pair's whole call
+    took 24 us of host time with two of them."""
+    if stream is not None:
+        return stream, stream
+    s = torch.cuda.current_stream()
+    return s, s if s.device_index == device.index else torch.cuda.current_stream(device)
+
+
 _ws_cache: dict = {}
 _WS_CACHE_STREAMS = 16
 
 
-def _workspace(nbytes: int, device, stream=None) -> torch.Tensor:
-    """Device workspace of at least nbytes for one call on `stream` (torch
+def _workspace(nbytes: int, device, s) -> torch.Tensor:
+    """Device workspace of at least nbytes for one call on stream `s` (torch
     allocations are >= 256-byte aligned).
 
     Outside a graph capture, one buffer per (device, stream) is kept and grown
@@ -88,10 +99,9 @@ def _workspace(nbytes: int, device, stream=None) -> torch.Tensor:
     the graph's lifetime, and it is never cached: later eager calls cannot
     overwrite what a replay reads.
     """
-    s = torch.cuda.current_stream(device) if stream is None else stream
     if torch.cuda.is_current_stream_capturing():
         return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-    key = (torch.device(device).index, s.cuda_stream)
+    key = (device.index, s.cuda_stream)
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         with torch.cuda.stream(s):
@@ -136,9 +146,10 @@ def match(Xii, Xji, Dii, Dji, Qii=None, Qji=None, p_init=None, prm: Optional[_li
     res = out if out is not None else _alloc_outputs(H, W, Xii.device, want_theta, want_xhat)
     o = _outputs(res)
     nbytes = lib.m3s_workspace_bytes(ctypes.byref(pair), ctypes.byref(prm))
-    ws = _workspace(nbytes, Xii.device, stream)
+    run, order = _streams(stream, Xii.device)
+    ws = _workspace(nbytes, Xii.device, order)
     st = lib.m3s_match_fwd(ctypes.byref(pair), ctypes.byref(prm), ctypes.byref(o), ws.data_ptr(), ws.numel(),
-                           _stream(stream))
+                           run.cuda_stream)
     _lib.check(lib, "m3s_match_fwd", st)
     return res
 
@@ -212,9 +223,10 @@ def match_backward_batched(inputs: Sequence[BwdEdgeInput], graph: bool = True, o
     table, grads = make_bwd_edges(inputs, outs)
     n = len(inputs)
     nbytes = lib.m3s_bwd_batched_workspace_bytes(n)
-    ws = _workspace(nbytes, inputs[0].Xii.device, stream)
+    run, order = _streams(stream, inputs[0].Xii.device)
+    ws = _workspace(nbytes, inputs[0].Xii.device, order)
     flags = (_lib.M3S_BATCH_GRAPH if graph else 0) | (_lib.M3S_BWD_ACCUMULATE if accumulate else 0)
-    st = lib.m3s_match_bwd_batched(table, n, flags, ws.data_ptr(), ws.numel(), _stream(stream))
+    st = lib.m3s_match_bwd_batched(table, n, flags, ws.data_ptr(), ws.numel(), run.cuda_stream)
     _lib.check(lib, "m3s_match_bwd_batched", st)
     return grads
 
@@ -227,10 +239,8 @@ def make_edges(inputs: Sequence[EdgeInput], want_theta=True, want_xhat=False, ou
     for k, e in enumerate(inputs):
         H, W = e.Xii.shape[:2]
         res = outs[k] if outs is not None else _alloc_outputs(H, W, e.Xii.device, want_theta, want_xhat)
-        table[k].in_ = _pair(e.Xii, e.Xji, e.Dii, e.Dji, e.Qii, e.Qji, e.p_init)
-        table[k].out = _outputs(res)
-        table[k].max_iter = e.max_iter
-        table[k].refine_radius = e.refine_radius
+        table[k] = _lib.Edge(_pair(e.Xii, e.Xji, e.Dii, e.Dji, e.Qii, e.Qji, e.p_init), _outputs(res),
+                             e.max_iter, e.refine_radius)
         results.append(res)
     return table, results
 
@@ -245,9 +255,10 @@ def match_batched(inputs: Sequence[EdgeInput], prm: Optional[_lib.Params] = None
     nbytes = lib.m3s_batched_workspace_bytes(table, n, ctypes.byref(prm))
     if nbytes == 0:
         raise _lib.M3SError("m3s_batched_workspace_bytes", _lib.M3S_OK + 2, "invalid edges")
-    ws = _workspace(nbytes, inputs[0].Xii.device, stream)
+    run, order = _streams(stream, inputs[0].Xii.device)
+    ws = _workspace(nbytes, inputs[0].Xii.device, order)
     flags = (_lib.M3S_BATCH_GRAPH if graph else 0) | (_lib.M3S_BATCH_AUTOTUNE if autotune else 0)
-    st = lib.m3s_match_batched(table, n, ctypes.byref(prm), flags, ws.data_ptr(), ws.numel(), _stream(stream))
+    st = lib.m3s_match_batched(table, n, ctypes.byref(prm), flags, ws.data_ptr(), ws.numel(), run.cuda_stream)
     _lib.check(lib, "m3s_match_batched", st)
     return results
 
@@ -259,9 +270,10 @@ def match_stats(res: MatchResult, stream=None) -> torch.Tensor:
     fwd = _lib.Outputs(0, _ptr(res.idx, torch.int32, shape=(H, W)), _ptr(res.valid, torch.uint8, shape=(H, W)), 0, 0)
     counts = torch.empty(2, dtype=torch.int32, device=res.idx.device)
     nbytes = lib.m3s_stats_workspace_bytes(H, W)
-    ws = _workspace(nbytes, res.idx.device, stream)
+    run, order = _streams(stream, res.idx.device)
+    ws = _workspace(nbytes, res.idx.device, order)
     st = lib.m3s_match_stats(ctypes.byref(fwd), H, W, _ptr(counts, torch.int32), ws.data_ptr(), ws.numel(),
-                             _stream(stream))
+                             run.cuda_stream)
     _lib.check(lib, "m3s_match_stats", st)
     return counts
 
@@ -284,9 +296,10 @@ def track_pose(Xk, Xf, idx, valid, Qf, Qk, T, prm: Optional[_lib.TrackParams] = 
     prm = prm if prm is not None else track_params()
     info = torch.empty(4, dtype=torch.float32, device=Xk.device)
     nbytes = lib.m3s_track_workspace_bytes(H, W)
-    ws = _workspace(nbytes, Xk.device, stream)
+    run, order = _streams(stream, Xk.device)
+    ws = _workspace(nbytes, Xk.device, order)
     st = lib.m3s_track_pose(ctypes.byref(prob), ctypes.byref(prm), _ptr(T, shape=(3, 4)), _ptr(info), ws.data_ptr(),
-                            ws.numel(), _stream(stream))
+                            ws.numel(), run.cuda_stream)
     _lib.check(lib, "m3s_track_pose", st)
     return T, info
 
@@ -323,9 +336,10 @@ def backend_gn(Xc, Q, edges, idx, valid, T_WC, prm: Optional[_lib.BackendParams]
     prm = prm if prm is not None else backend_params()
     info = torch.empty(4, dtype=torch.float32, device=Xc.device)
     nbytes = lib.m3s_backend_workspace_bytes(N, H, W, E)
-    ws = _workspace(nbytes, Xc.device, stream)
+    run, order = _streams(stream, Xc.device)
+    ws = _workspace(nbytes, Xc.device, order)
     st = lib.m3s_backend_gn(ctypes.byref(prob), ctypes.byref(prm), _ptr(T_WC, shape=(N, 3, 4)), _ptr(info),
-                            ws.data_ptr(), ws.numel(), _stream(stream))
+                            ws.data_ptr(), ws.numel(), run.cuda_stream)
     _lib.check(lib, "m3s_backend_gn", st)
     return T_WC, info
 
@@ -387,6 +401,9 @@ class MatchFunction(torch.autograd.Function):
                     None if p_init is None else p_init.contiguous(), prm, want_theta=True, want_xhat=True)
         ctx.save_for_backward(Xii_c, Xji_c, res.p, res.valid)
         ctx.mark_non_differentiable(res.idx, res.valid, res.theta)
+        # Else the engine fills a zero tensor for idx, valid and theta (and for an unused
+        # p or xhat) on every backward: three launches whose results nothing reads.
+        ctx.set_materialize_grads(False)
         return res.p, res.xhat, res.idx, res.valid, res.theta
 
     @staticmethod
