@@ -660,97 +660,106 @@ __device__ __forceinline__ float exact24(const float* __restrict__ q, const floa
     return acc;
 }
 
-// Lattice steps (of spacing 2^lev) by which a window of the given reach around c
-// has to move to lie inside [0, size), for size >= 2 reach + 2^lev.
-__device__ __forceinline__ int slide_steps(int c, int reach, int lev, int size) {
-    const int up = (1 << lev) - 1, lo = reach - c, hi = c + reach - (size - 1);
-    return (max(lo, 0) + up >> lev) - (max(hi, 0) + up >> lev);
+// Pixels by which a window of radius r around c has to move to lie inside
+// [0, size), for size >= 2 r + 1.
+__device__ __forceinline__ int slide_by(int c, int r, int size) {
+    return max(r - c, 0) - max(c + r - (size - 1), 0);
 }
 
-// Whether scan16 covers a level, with the image large enough for its windows to
-// slide inside (the same for every lane).
-__device__ __forceinline__ bool slides(int r, int lev, int H, int W) {
-    const int least = 2 * (r << lev) + (1 << lev);
-    return ((lev == 0 && r >= 2 && r <= 4) || (lev == 1 && r == 3)) && H >= least && W >= least;
+// Whether scan16 covers a single-level refine: its radii, in an image large
+// enough for the windows to slide inside (the same for every lane).
+__device__ __forceinline__ bool slides(int r, int H, int W) {
+    return r >= 2 && r <= 4 && H >= 2 * r + 1 && W >= 2 * r + 1;
 }
 
-// Pass 1 over a window, for a radius R and a candidate spacing SP fixed at
-// compile time: the candidates of a row are unrolled (LDS addresses are the
-// row base plus immediate offsets), the row's scores are kept in registers,
-// the running maximum takes the row's maximum, and each candidate of the row
-// survives if its score is within tau of that running maximum.  A candidate
-// that survives against the final maximum survives against any earlier one,
-// so no candidate that can be the exact maximum is dropped.  The survivor
-// bits are shifted into a 128-bit word hi:lo, leaving candidate j of the
-// window on bit N - 1 - j; a bit reversal then gives the row-major masks of
-// the generic pass (candidate j on bit j).  w: LDS record of the window's
-// top-left candidate.
-// CLIP: some query's window reaches beyond the image.  It has slid inside by kx
-// columns and ky rows, so that every lane scans S x S staged candidates, and those
-// outside its own window score -inf (one select each).  Before, such waves took a
-// per-lane loop over the candidates inside the image, about half as much again as
-// the unrolled pass: the 64 x 48 pair, all of whose tiles lie at the border, took
-// 20.5 us and takes 17.8; 512 x 384 31.2 and 30.3.
-template <int R, int SP, int CAP, bool CLIP>
-__device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restrict__ w, int rw, float tau, int kx,
-                                       int ky, float& run, uint64_t& mask0, uint64_t& mask1) {
+// The same for the multi-level kernel, which does not slide.
+__device__ __forceinline__ bool scans_bands(int r) { return r >= 2 && r <= 4; }
+
+// A query's window: the pixels it has slid (0, 0: not at all) and its top-left
+// candidate in the coordinates of the staged region (or band of it).
+struct Window16 {
+    int kx, ky, x, y;
+};
+
+// Pass 1 over a window, for a radius R fixed at compile time: the candidates of
+// a row are unrolled, the row's scores are kept in registers, the running
+// maximum takes the row's maximum, and each candidate of the row survives if
+// its score is within tau of that running maximum.  A candidate that survives
+// against the final maximum survives against any earlier one, so no candidate
+// that can be the exact maximum is dropped.  Survivors: candidate j of the
+// window on bit j of mask1:mask0, the row-major order in which they are
+// rescored (the row is the same for every lane, so its place is scalar).
+// CLIP: some query's window reaches beyond the image, and candidates outside
+// score -inf (one select each).
+// Single level: such windows have slid inside by kx columns and ky rows, so that
+// every lane scans S x S staged candidates at immediate offsets from the row's
+// address.  A per-lane loop over the candidates inside costs such waves about
+// half as much again: the 64 x 48 pair, all of whose tiles lie at the border,
+// took 20.5 us and takes 17.8; 512 x 384 31.2 and 30.3.
+// MULTI: candidates 2^lev apart, and only the rows among the `rows` staged, the
+// others being outside the image or in another band; columns outside read the
+// region's nearest one.  (Sliding would enlarge a coarse level's region.)  The
+// per-lane loops that radii and levels other than r = 3, 2^l <= 2 took before
+// cost about twice the instructions per candidate: at 512 x 384 three levels took
+// 80 us at r = 3 and 121 at r = 4, now 69 and 90; two levels of r = 4 74, now 58.
+template <int R, int CAP, bool CLIP, bool MULTI>
+__device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restrict__ sd, const Window16& win, int rw,
+                                       int lev, int rows, float tau, float& run, uint64_t& mask0, uint64_t& mask1) {
     constexpr int S = 2 * R + 1, N = S * S;
     static_assert(N <= 128 && S < 32, "mask width");
+    const int sp = MULTI ? 1 << lev : 1;
     bool in[S];
+    int col[S];
 #pragma unroll
-    for (int dx = 0; dx < S; ++dx) in[dx] = !CLIP || (uint32_t)(dx + kx) < (uint32_t)S;
-    // Scores of window row dy, and the least score that survives.
-    auto row = [&](int dy, float (&sc)[S]) {
+    for (int dx = 0; dx < S; ++dx) {
+        col[dx] = win.x + sp * dx;
+        in[dx] = !CLIP || (MULTI ? (uint32_t)col[dx] < (uint32_t)rw : (uint32_t)(dx + win.kx) < (uint32_t)S);
+        if (MULTI && CLIP) col[dx] = min(max(col[dx], 0), rw - 1);
+    }
+    int y = win.y;
+#pragma unroll 1
+    for (int dy = 0; dy < S; ++dy, y += sp) {
+        if (MULTI && (uint32_t)y >= (uint32_t)rows) continue;
+        float sc[S];
 #pragma unroll
         for (int dx = 0; dx < S; ++dx) {
-            sc[dx] = dot16(q16, w[SP * dx], w[SP * dx + CAP], w[SP * dx + 2 * CAP]);
+            const uint4* c = MULTI ? sd + (y * rw + col[dx]) : sd + (y * rw + win.x) + dx;
+            sc[dx] = dot16(q16, c[0], c[CAP], c[2 * CAP]);
             if constexpr (CLIP) sc[dx] = in[dx] ? sc[dx] : -INFINITY;
         }
         float rm = sc[0];
 #pragma unroll
         for (int dx = 1; dx < S; ++dx) rm = fmaxf(rm, sc[dx]);
-        const bool on = !CLIP || (uint32_t)(dy + ky) < (uint32_t)S;
+        const bool on = !CLIP || MULTI || (uint32_t)(dy + win.ky) < (uint32_t)S;
         run = on ? fmaxf(run, rm) : run;
-        return on ? run - tau : INFINITY;
-    };
-    if constexpr (N <= 64) {
-        // The whole mask in one word: candidate (dy, dx) at bit dy * S + dx,
-        // the row-major order the survivor pass pops in (bit values 1 .. 2^(S-1)
-        // are inline constants).
-        uint64_t m = 0;
-#pragma unroll 1
-        for (int dy = 0; dy < S; ++dy, w += SP * rw) {
-            float sc[S];
-            const float thr = row(dy, sc);
-            uint32_t rb = 0;
-#pragma unroll
-            for (int dx = 0; dx < S; ++dx) rb |= sc[dx] >= thr ? (1u << dx) : 0u;
-            m |= (uint64_t)rb << (dy * S);
-        }
-        mask0 = m;
-        mask1 = 0;
-        return;
-    }
-    uint64_t lo = 0, hi = 0;
-#pragma unroll 1
-    for (int dy = 0; dy < S; ++dy, w += SP * rw) {
-        float sc[S];
-        const float thr = row(dy, sc);
+        const float thr = on ? run - tau : INFINITY;
         uint32_t rb = 0;
 #pragma unroll
-        for (int dx = 0; dx < S; ++dx) rb = rb + rb + (sc[dx] >= thr ? 1u : 0u);
-        hi = (hi << S) | (lo >> (64 - S));
-        lo = (lo << S) | rb;
+        for (int dx = 0; dx < S; ++dx) rb |= sc[dx] >= thr ? (1u << dx) : 0u;
+        const int bit = dy * S;
+        if (N <= 64 || bit < 64) mask0 |= (uint64_t)rb << bit;
+        if constexpr (N > 64) {
+            if (bit >= 64) mask1 |= (uint64_t)rb << (bit - 64);
+            else if (bit + S > 64) mask1 |= (uint64_t)(rb >> (64 - bit));
+        }
     }
-    const uint64_t rhi = __builtin_bitreverse64(lo), rlo = __builtin_bitreverse64(hi);
-    constexpr int sh = 128 - N;  // forward mask = (rhi:rlo) >> sh
-    if constexpr (sh >= 64) {
-        mask0 = rhi >> (sh - 64);
-        mask1 = 0;
-    } else {
-        mask0 = (rlo >> sh) | (rhi << (64 - sh));
-        mask1 = rhi >> sh;
-    }
+}
+
+// scan16 at the radius r of 2, 3 or 4, in its clipped form where some lane of
+// the wave needs it.
+template <int CAP, bool MULTI>
+__device__ __forceinline__ void scan16_r(const uint32_t* q16, const uint4* __restrict__ sd, const Window16& win, int r,
+                                         int rw, int lev, int rows, float tau, float& run, uint64_t& mask0,
+                                         uint64_t& mask1) {
+    const bool out = MULTI ? win.x < 0 || win.x + (2 * r << lev) >= rw : (win.kx | win.ky) != 0;
+    const bool clip = __any(out) != 0;
+    auto scan = [&](auto R) {
+        if (clip) scan16<decltype(R)::value, CAP, true, MULTI>(q16, sd, win, rw, lev, rows, tau, run, mask0, mask1);
+        else scan16<decltype(R)::value, CAP, false, MULTI>(q16, sd, win, rw, lev, rows, tau, run, mask0, mask1);
+    };
+    if (r == 3) scan(std::integral_constant<int, 3>{});
+    else if (r == 2) scan(std::integral_constant<int, 2>{});
+    else scan(std::integral_constant<int, 4>{});
 }
 
 // A query descriptor for the fp16 pre-filter: fp32 elements (exact rescoring),
@@ -787,6 +796,26 @@ __device__ __forceinline__ float f16_tau(const Query16& Q, float dnorm, float dl
     const float eps16 = (2.f * kU16 + kU16 * kU16 + kU32x24) * qn * dnorm + kFlush16 * (Q.ql1 + dl1);
     const float eps32 = kU32x24 * qn * dnorm;
     return 2.f * (eps16 + eps32) * 1.0001f + 1e-30f;
+}
+
+// Lower bound on the fp16 score of reference pixel m (scaled units), from its
+// exact score: seeds the running maximum of a window that is scanned in bands,
+// so that the rows above the best one leave no survivors (three levels of r = 4
+// at 512 x 384 94 -> 90 us, of r = 3 no change).
+__device__ __forceinline__ float f16_floor(const EdgeArgs& A, const Query16& Q, long m) {
+    const float4* s = reinterpret_cast<const float4*>(A.Dii + 24 * m);
+    float acc = 0.f, d2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const float4 v = s[k];
+        acc = fmaf(Q.qd.q[4 * k], v.x, acc);
+        acc = fmaf(Q.qd.q[4 * k + 1], v.y, acc);
+        acc = fmaf(Q.qd.q[4 * k + 2], v.z, acc);
+        acc = fmaf(Q.qd.q[4 * k + 3], v.w, acc);
+        d2 += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+    const float dnorm = sqrtf(d2) * 1.0001f;
+    return acc * (kScale16 * kScale16) - f16_tau(Q, dnorm, kSqrt24Up * dnorm);
 }
 
 // Pass 2 of the fp16 refine: exact scores of the survivors (candidate k of the
@@ -846,13 +875,13 @@ __device__ __forceinline__ void f16_scan_band(const EdgeArgs& A, const Query16& 
 }
 
 // One level of the exact first-maximum refine with the fp16 pre-filter: the
-// (2r+1)^2 grid of spacing sp around (mx0, my0), over a staged region that
-// holds every candidate inside the image.  dnorm: bound on |d| over the
-// region, dl1: bound on |d|_1.
-template <int CAP>
+// (2r+1)^2 grid of spacing 2^lev around (mx0, my0), over a staged region of rw x
+// rh pixels that holds every candidate inside the image.  dnorm: bound on |d|
+// over the region, dl1: bound on |d|_1.
+template <int CAP, bool MULTI>
 __device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query16& Q, int mx0, int my0, int lev,
-                                                 const uint4* __restrict__ sd, int rx0, int ry0, int rw, float dnorm,
-                                                 float dl1) {
+                                                 const uint4* __restrict__ sd, int rx0, int ry0, int rw, int rh,
+                                                 float dnorm, float dl1) {
     const int H = A.H, W = A.W, r = A.r, side = 2 * r + 1, sp = 1 << lev;
     const float tau = f16_tau(Q, dnorm, dl1);
 
@@ -862,22 +891,15 @@ __device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query1
     const uint4* c0 = sd + (my0 - ry0) * rw + (mx0 - rx0);
     float run = dot16(Q.q16, c0[0], c0[CAP], c0[2 * CAP]);
     uint64_t mask0 = 0, mask1 = 0;
-    const int reach = r << lev;
-    int kx = 0, ky = 0;
-    if (slides(r, lev, H, W)) {
-        // The unrolled scan; windows that reach beyond the image slid inside it.
-        kx = slide_steps(mx0, reach, lev, W);
-        ky = slide_steps(my0, reach, lev, H);
-        const uint4* w = sd + (my0 + sp * ky - reach - ry0) * rw + (mx0 + sp * kx - reach - rx0);
-        const bool clip = __any((kx | ky) != 0) != 0;  // the same for every lane of the wave
-        auto scan = [&](auto R, auto SP) {
-            if (clip) scan16<decltype(R)::value, decltype(SP)::value, CAP, true>(Q.q16, w, rw, tau, kx, ky, run, mask0, mask1);
-            else scan16<decltype(R)::value, decltype(SP)::value, CAP, false>(Q.q16, w, rw, tau, 0, 0, run, mask0, mask1);
-        };
-        if (lev > 0) scan(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
-        else if (r == 3) scan(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
-        else if (r == 2) scan(std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{});
-        else scan(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{});
+    Window16 win{0, 0, mx0 - (r << lev) - rx0, my0 - (r << lev) - ry0};
+    if (MULTI ? scans_bands(r) : slides(r, H, W)) {
+        if (!MULTI) {
+            win.kx = slide_by(mx0, r, W);
+            win.ky = slide_by(my0, r, H);
+            win.x += win.kx;
+            win.y += win.ky;
+        }
+        scan16_r<CAP, MULTI>(Q.q16, sd, win, r, rw, lev, rh, tau, run, mask0, mask1);
     } else {
         for (int dy = -r; dy <= r; ++dy) {
             const int my = my0 + sp * dy;
@@ -896,7 +918,7 @@ __device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query1
         }
     }
     // Pass 2: exact scores of the survivors.
-    return f16_rescore(A, Q, mx0 + sp * kx, my0 + sp * ky, sp, mask0, mask1);
+    return f16_rescore(A, Q, mx0 + win.kx, my0 + win.ky, sp, mask0, mask1);
 }
 
 // Stages region rows [ly, ly + rh) x columns [lx, lx + rw) of D^i_i into the
@@ -1000,10 +1022,9 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, Tile
         const int sp = 1 << lev, reach = r * sp;
         int lx = INT_MAX, hx = INT_MIN, ly = INT_MAX, hy = INT_MIN;
         if (live) {
-            // (The window as scan16 takes it, slid inside the image.)
-            const bool sl = slides(r, lev, H, W);
-            const int wx = sl ? cx + sp * slide_steps(cx, reach, lev, W) : cx;
-            const int wy = sl ? cy + sp * slide_steps(cy, reach, lev, H) : cy;
+            // (The window as scan16 takes it: of a single level, slid inside the image.)
+            const bool sl = !MULTI && slides(r, H, W);
+            const int wx = sl ? cx + slide_by(cx, r, W) : cx, wy = sl ? cy + slide_by(cy, r, H) : cy;
             lx = max(wx - reach, 0); hx = min(wx + reach, W - 1);
             ly = max(wy - reach, 0); hy = min(wy + reach, H - 1);
         }
@@ -1046,10 +1067,17 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, Tile
                     break;
                 }
                 if (live) query();
+                if (live && b0 == 0) run = f16_floor(A, Q, (long)cy * W + cx);
                 if (live) {
                     const float dnorm = sqrtf(pn2) * 1.0001f;
-                    f16_scan_band<CAP>(A, Q, cx, cy, sp, S.desc, lx, ly + b0, rw, ly + b0 + nr - 1,
-                                       f16_tau(Q, dnorm, kSqrt24Up * dnorm), run, mask0, mask1);
+                    const float tau = f16_tau(Q, dnorm, kSqrt24Up * dnorm);
+                    if (scans_bands(r)) {
+                        const Window16 win{0, 0, cx - reach - lx, cy - reach - (ly + b0)};
+                        scan16_r<CAP, MULTI>(Q.q16, S.desc, win, r, rw, lev, nr, tau, run, mask0, mask1);
+                    } else {
+                        f16_scan_band<CAP>(A, Q, cx, cy, sp, S.desc, lx, ly + b0, rw, ly + b0 + nr - 1, tau, run, mask0,
+                                           mask1);
+                    }
                 }
             }
             if (!ok16 && tid == 0) count_path(kPathRefineGlobal);
@@ -1059,14 +1087,14 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, Tile
         } else {
             bool use16 = any && rw * rh <= CAP && r <= 5;
             float pn2 = 0.f;  // largest |d|^2 over the region's pixels
-            if (use16) pn2 = stage_region16<NT, CAP, 2>(A, S.desc, lx, ly, rw, rh);
+            if (use16) pn2 = stage_region16<NT, CAP, MULTI ? 1 : 2>(A, S.desc, lx, ly, rw, rh);
             pn2 = block_max16<NT>(pn2, S.stat);
             use16 = use16 && pn2 <= (kF16Max / kScale16) * (kF16Max / kScale16);
             if (any && !use16 && tid == 0) count_path(kPathRefineGlobal);
             if (live) query();
             if (live) {
                 const float dnorm = sqrtf(pn2) * 1.0001f;
-                lb = use16 ? refine_f16_level<CAP>(A, Q, cx, cy, lev, S.desc, lx, ly, rw, dnorm, kSqrt24Up * dnorm)
+                lb = use16 ? refine_f16_level<CAP, MULTI>(A, Q, cx, cy, lev, S.desc, lx, ly, rw, rh, dnorm, kSqrt24Up * dnorm)
                            : refine_global_level<24>(A, Q.qd, cx, cy, sp);
             }
         }

@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
 # H, W, r, levels
 CASES = [(H, W, r, 1) for r in (2, 3, 4) for H, W in ((2 * r, 2 * r + 9), (2 * r + 1, 2 * r + 1), (2 * r + 2, 40), (33, 2 * r))]
 CASES += [(13, 14, 3, 2), (14, 14, 3, 2), (14, 31, 3, 2), (40, 15, 3, 2), (27, 28, 3, 3), (37, 53, 2, 2), (37, 53, 5, 1)]
+# Coarse levels whose regions are staged in bands of rows, and radii whose mask takes two words.
+CASES += [(45, 60, 4, 2), (45, 60, 4, 3), (31, 36, 4, 3), (60, 90, 3, 3), (60, 90, 2, 4), (70, 96, 3, 4), (35, 120, 4, 4)]
 
 
 @pytest.mark.parametrize("H,W,r,levels", CASES)
