@@ -120,11 +120,10 @@ __device__ __forceinline__ bool edge_in_range(int ei, int ej, int N) {
     return ei >= 0 && ei < N && ej >= 0 && ej < N;
 }
 
-// T_ij of edge e in fp32 from the fp64 world poses (zero for an edge out of
-// range); pose(k, j) is element j of keyframe k's pose.
+// T_ij of edge e = (ei, ej) in fp32 from the fp64 world poses (zero for an edge
+// out of range); pose(k, j) is element j of keyframe k's pose.
 template <class Pose>
-__device__ __forceinline__ void write_relative_pose(const BackendArgs& A, int e, Pose pose) {
-    const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
+__device__ __forceinline__ void write_relative_pose(const BackendArgs& A, int e, int ei, int ej, Pose pose) {
     double Wi[12], Wj[12], Ti[12], Tij[12];
     if (edge_in_range(ei, ej, A.N)) {
         for (int k = 0; k < 12; ++k) Wi[k] = pose(ei, k);
@@ -224,39 +223,44 @@ __global__ void __launch_bounds__(kThreads) backend_accum_kernel(BackendArgs A) 
 }
 
 // One workgroup per edge: fixed-order fp64 sum of the edge's partials; then
-// (iterations only) A = Ad(T_WC[i]^-1), A^T H_e A and A^T g_e.
-__global__ void __launch_bounds__(kThreads) backend_edge_kernel(BackendArgs A, int final_pass) {
+// (iterations only) A = Ad(T_WC[i]^-1), A^T H_e A and A^T g_e.  Bound by the
+// latency of its chain, so a fifth wave forms A while the other four sum, and
+// the product takes two short steps (15, 65 and 198 edges: 5.0 -> 4.3, 6.2 -> 5.0
+// and 5.4 -> 4.8 us).
+constexpr int kEdgeThreads = kThreads + 64;
+__global__ void __launch_bounds__(kEdgeThreads) backend_edge_kernel(BackendArgs A, int final_pass) {
     __shared__ double sys[kStride];
     __shared__ SumLds<kThreads> part;
-    __shared__ double Ad[49];
+    __shared__ double Ad[49], HA[49];
     if (!final_pass && A.state[0]) return;
-    const int e = blockIdx.x;
-    sum_partials<kThreads>(A.partials + (size_t)e * A.blocks_per_edge * kMomentStride, A.blocks_per_edge, part, sys);
-    if (threadIdx.x < kVals) A.edge_sys[(size_t)e * kStride + threadIdx.x] = sys[threadIdx.x];
-    if (final_pass) return;
+    const int e = blockIdx.x, tid = threadIdx.x;
     const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
-    if (!edge_in_range(ei, ej, A.N)) return;
-    if (threadIdx.x == 0) {
+    const bool in_range = edge_in_range(ei, ej, A.N);
+    if (tid == kThreads && !final_pass && in_range) {
         double Ti[12];
         sim3_inverse(A.T64 + 12 * ei, Ti);
         sim3_adjoint(Ti, Ad);
     }
-    __syncthreads();
+    sum_partials<kThreads>(A.partials + (size_t)e * A.blocks_per_edge * kMomentStride, A.blocks_per_edge, part, sys);
+    if (tid < kVals) A.edge_sys[(size_t)e * kStride + tid] = sys[tid];
+    if (final_pass || !in_range) return;
     double* out = A.edge_blk + (size_t)e * kBlk;
-    if (threadIdx.x < 49) {
-        const int a = threadIdx.x / 7, b = threadIdx.x % 7;
+    const int a = tid / 7, b = tid % 7;
+    if (tid < 49) {
+        double hk = 0.0;
+        for (int l = 0; l < 7; ++l) hk += sys[upper_index(a < l ? a : l, a < l ? l : a)] * Ad[7 * l + b];
+        HA[tid] = hk;
+    } else if (tid >= 64 && tid < 71) {
+        const int c = tid - 64;
         double s = 0.0;
-        for (int k = 0; k < 7; ++k) {
-            double hk = 0.0;
-            for (int l = 0; l < 7; ++l) hk += sys[upper_index(k < l ? k : l, k < l ? l : k)] * Ad[7 * l + b];
-            s += Ad[7 * k + a] * hk;
-        }
-        out[threadIdx.x] = s;
-    } else if (threadIdx.x >= 64 && threadIdx.x < 71) {
-        const int a = threadIdx.x - 64;
+        for (int k = 0; k < 7; ++k) s += Ad[7 * k + c] * sys[28 + k];
+        out[49 + c] = s;
+    }
+    __syncthreads();
+    if (tid < 49) {
         double s = 0.0;
-        for (int k = 0; k < 7; ++k) s += Ad[7 * k + a] * sys[28 + k];
-        out[49 + a] = s;
+        for (int k = 0; k < 7; ++k) s += Ad[7 * k + a] * HA[7 * k + b];
+        out[tid] = s;
     }
 }
 
@@ -360,23 +364,50 @@ __device__ __forceinline__ void trailing_tile(const BackendArgs& A, PanelPtr P, 
             }
 }
 
+// What the end of a solve reads from memory, read before the substitution that
+// precedes it: lane k's pose T_WC[k] and its edge of the first NT.
+struct StepIn {
+    double T[12];
+    int ei, ej;
+};
+__device__ __forceinline__ StepIn read_step(const BackendArgs& A) {
+    StepIn in;
+    const int k = min((int)threadIdx.x, A.N - 1), e = min((int)threadIdx.x, A.E - 1);
+    for (int j = 0; j < 12; ++j) in.T[j] = A.T64[12 * k + j];
+    in.ei = A.edges[2 * e];
+    in.ej = A.edges[2 * e + 1];
+    return in;
+}
+
 // The end of a solve: pose updates T_WC[k] <- Exp(tau_k) o T_WC[k] for
 // keyframes 1..N-1 from the solution x (LDS; keyframe k's step at
 // 7 pos(k - 1)), the relative pose of every edge
 // at the new poses (for the next accumulation), and the step norm, which ends
-// the loop below step_tol.  All NT lanes of the workgroup call this.
+// the loop below step_tol.  All NT lanes of the workgroup call this; the poses
+// pass between them in Tl (12 N doubles of LDS that x does not overlap), not
+// through memory.  (With the lists' single round trip: the solve of 8, 32 and 96
+// keyframes 16.9 -> 16.3, 34.6 -> 33.4 and 66.5 -> 65.1 us.)
 template <int NT, class Pos>
-__device__ __forceinline__ void apply_step(const BackendArgs& A, const double* x, double* red, Pos pos) {
+__device__ __forceinline__ void apply_step(const BackendArgs& A, const StepIn& in, const double* x, double* Tl,
+                                           double* red, Pos pos) {
+    static_assert(NT >= M3S_MAX_KEYFRAMES, "one lane per keyframe");
     const int tid = threadIdx.x;
-    for (int k = 1 + tid; k < A.N; k += NT) {
-        double E[12], Tn[12];
-        sim3_exp(x + 7 * pos(k - 1), E);
-        sim3_mul(E, A.T64 + 12 * k, Tn);
-        for (int j = 0; j < 12; ++j) A.T64[12 * k + j] = Tn[j];
+    if (tid < A.N) {
+        double Tn[12];
+        if (tid > 0) {
+            double E[12];
+            sim3_exp(x + 7 * pos(tid - 1), E);
+            sim3_mul(E, in.T, Tn);
+            for (int j = 0; j < 12; ++j) A.T64[12 * tid + j] = Tn[j];
+        } else {
+            for (int j = 0; j < 12; ++j) Tn[j] = in.T[j];
+        }
+        for (int j = 0; j < 12; ++j) Tl[12 * tid + j] = Tn[j];
     }
     __syncthreads();
-    for (int e = tid; e < A.E; e += NT)
-        write_relative_pose(A, e, [&](int k, int j) { return A.T64[12 * k + j]; });
+    auto pose = [&](int k, int j) { return Tl[12 * k + j]; };
+    if (tid < A.E) write_relative_pose(A, tid, in.ei, in.ej, pose);
+    for (int e = tid + NT; e < A.E; e += NT) write_relative_pose(A, e, A.edges[2 * e], A.edges[2 * e + 1], pose);
     double sq = 0.0;
     for (int k = tid; k < A.n; k += NT) sq += x[k] * x[k];
     for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
@@ -671,7 +702,10 @@ __device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
         __syncthreads();
     }
 
-    apply_step<kSolveThreads>(A, x, S.red, [](int k) { return k; });
+    static_assert(12 * M3S_MAX_KEYFRAMES <= kPanelRows * kPanelStride, "poses in the panel's LDS");
+    const StepIn step = read_step(A);
+    __syncthreads();
+    apply_step<kSolveThreads>(A, step, x, panel, S.red, [](int k) { return k; });
 }
 
 // ---------------------------------------------------------------- block-sparse solve
@@ -869,7 +903,7 @@ __global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs 
     if (blockIdx.x > 0) {
         const int t = ((int)blockIdx.x - 1) * kPatThreads + tid;
         if (t < 12 * A.N) A.T64[t] = (double)T_in[t];
-        if (t < A.E) write_relative_pose(A, t, [&](int k, int j) { return (double)T_in[12 * k + j]; });
+        if (t < A.E) write_relative_pose(A, t, A.edges[2 * t], A.edges[2 * t + 1], [&](int k, int j) { return (double)T_in[12 * k + j]; });
         return;
     }
     if (tid < 4 && tid != 2) A.state[tid] = 0;
@@ -1049,7 +1083,7 @@ struct SparseLds {
     double Lb[LDS ? kLdsBlocks * 49 : 1];
     double xs[kMaxDim];                        // right-hand side, then y, then the solution, by position
     double red[kSolveThreads / 64];
-    uint32_t upd[kUpdates];
+    alignas(8) uint32_t upd[kUpdates];
     uint32_t elist[kEntries];
     int32_t estart[kBlocks + 1];
     uint16_t ustart[kBlocks + 2];
@@ -1058,6 +1092,48 @@ struct SparseLds {
     uint8_t si[kBlocks], sj[kBlocks];
     int bad;
 };
+
+// Copies the pattern's lists to LDS, as many entries of each as the mode can
+// hold (what lies past the pattern's own is not used): with the lengths not
+// awaited, this is one round trip to memory instead of four.
+template <bool LDS>
+__device__ __forceinline__ void read_lists(const BackendArgs& A, SparseLds<LDS>& S) {
+    const PatternBuf& P = *A.pat;
+    const int tid = threadIdx.x, nb = A.N - 1;
+    constexpr int kB = SparseLds<LDS>::kBlocks, kU = SparseLds<LDS>::kUpdates, kE = SparseLds<LDS>::kEntries;
+    static_assert(kSolveThreads > M3S_MAX_KEYFRAMES && kU % kSolveThreads == 0 && kE % kSolveThreads == 0, "whole steps");
+    uint32_t u[LDS ? kU / kSolveThreads : 1], l[LDS ? kE / kSolveThreads : 1];
+    if constexpr (LDS) {
+#pragma unroll
+        for (int j = 0; j < kU / kSolveThreads; ++j) u[j] = P.upd[tid + j * kSolveThreads];
+#pragma unroll
+        for (int j = 0; j < kE / kSolveThreads; ++j) l[j] = A.elist[min(tid + j * kSolveThreads, 3 * A.E - 1)];
+    }
+    for (int i = tid; i < kB; i += kSolveThreads) {
+        S.si[i] = P.si[i];
+        S.sj[i] = P.sj[i];
+    }
+    for (int i = tid; i <= kB; i += kSolveThreads) {
+        S.ustart[i] = P.ustart[i];
+        S.estart[i] = P.estart[i];
+    }
+    if (tid <= nb) {
+        S.colstart[tid] = P.colstart[tid];
+        if (tid < nb) S.pos[tid] = P.pos[tid];
+        S.lvl[tid] = P.lvl[tid];
+    }
+    if constexpr (LDS) {
+#pragma unroll
+        for (int j = 0; j < kU / kSolveThreads; ++j) S.upd[tid + j * kSolveThreads] = u[j];
+#pragma unroll
+        for (int j = 0; j < kE / kSolveThreads; ++j) S.elist[tid + j * kSolveThreads] = l[j];
+    } else {
+        for (int i = tid; i < P.nupd; i += kSolveThreads) S.upd[i] = P.upd[i];
+        for (int i = tid; i < min(3 * A.E, kE); i += kSolveThreads) S.elist[i] = A.elist[i];
+    }
+    if (tid == 0) S.bad = 0;
+    __syncthreads();
+}
 
 // One workgroup: the block-sparse Cholesky over the pattern, left looking and
 // level by level, the forward substitution folded in, the backward substitution
@@ -1071,27 +1147,8 @@ struct SparseLds {
 // LDS: the blocks are in LDS (Lb = S.Lb), else in the workspace.
 template <bool LDS>
 __device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS>& S, double* __restrict__ Lb) {
-    const PatternBuf& P = *A.pat;
     const int nb = A.N - 1, tid = threadIdx.x;
-    const int nblk = P.nblk, nlev = P.nlev, nupd = P.nupd;
-    const int nent = P.estart[nblk];
-    for (int i = tid; i < nblk; i += kSolveThreads) {
-        S.si[i] = P.si[i];
-        S.sj[i] = P.sj[i];
-    }
-    for (int i = tid; i <= nblk; i += kSolveThreads) {
-        S.ustart[i] = P.ustart[i];
-        S.estart[i] = P.estart[i];
-    }
-    for (int i = tid; i <= nb; i += kSolveThreads) {
-        S.colstart[i] = P.colstart[i];
-        if (i < nb) S.pos[i] = P.pos[i];
-        if (i <= nlev) S.lvl[i] = P.lvl[i];
-    }
-    for (int i = tid; i < nupd; i += kSolveThreads) S.upd[i] = P.upd[i];
-    for (int i = tid; i < min(nent, (int)S.kEntries); i += kSolveThreads) S.elist[i] = A.elist[i];
-    if (tid == 0) S.bad = 0;
-    __syncthreads();
+    const int nblk = A.pat->nblk, nlev = A.pat->nlev;
     // The system's blocks, gathered from the edges' blocks in edge order: one
     // lane per entry and one wave per block, kQ blocks a step with the reads of
     // each one's first kE edges (two per block and four per diagonal in a
@@ -1275,6 +1332,7 @@ __device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS
             return;
         }
     }
+    const StepIn step = read_step(A);
     // Backward substitution x_z = L_zz^-T (y_z - sum_x L_xz^T x_x): sixteen
     // lanes per column, lane 8 h + c summing component c over every other block.
     for (int lv = nlev - 1; lv >= 0; --lv) {
@@ -1305,7 +1363,10 @@ __device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS
         }
         __syncthreads();
     }
-    apply_step<kSolveThreads>(A, S.xs, S.red, [&](int k) { return (int)S.pos[k]; });
+    // (The blocks, or in global mode the products, are done with.)
+    double* Tl = LDS ? S.Lb : reinterpret_cast<double*>(S.upd);
+    static_assert(12 * M3S_MAX_KEYFRAMES * 8 <= (LDS ? sizeof(S.Lb) : sizeof(S.upd)), "poses in LDS");
+    apply_step<kSolveThreads>(A, step, S.xs, Tl, S.red, [&](int k) { return (int)S.pos[k]; });
 }
 
 // One launch per iteration, N workgroups.  Sparse: workgroup 0 solves and the
@@ -1318,6 +1379,8 @@ __global__ void __launch_bounds__(kSolveThreads) backend_solve_kernel(BackendArg
     static_assert(sizeof(AssembleLds) <= kBytes && kBytes <= 163328, "LDS of a CU");
     __shared__ __align__(16) char lds[kBytes];
     __shared__ int last;
+    // (The lists of the usual mode are on their way while the state is read.)
+    if (blockIdx.x == 0) read_lists<true>(A, *reinterpret_cast<SparseLds<true>*>(lds));
     if (A.state[0]) return;
     const int mode = A.state[2];
     if (mode != kSolveDense) {
@@ -1326,10 +1389,14 @@ __global__ void __launch_bounds__(kSolveThreads) backend_solve_kernel(BackendArg
             SparseLds<true>& S = *reinterpret_cast<SparseLds<true>*>(lds);
             sparse_solve<true>(A, S, S.Lb);
         } else {
-            sparse_solve<false>(A, *reinterpret_cast<SparseLds<false>*>(lds), A.M);
+            SparseLds<false>& S = *reinterpret_cast<SparseLds<false>*>(lds);
+            __syncthreads();
+            read_lists<false>(A, S);
+            sparse_solve<false>(A, S, A.M);
         }
         return;
     }
+    __syncthreads();
     assemble_row(A, (int)blockIdx.x, *reinterpret_cast<AssembleLds*>(lds));
     __threadfence();
     __syncthreads();
@@ -1453,7 +1520,7 @@ hipError_t launch_backend(int N, int HW, int E, const float* Xc, const float* Q,
         else backend_accum_kernel<false><<<grid, kThreads, 0, s>>>(A);
         timer_end(s);
         timer_begin("backend_edge", s);
-        backend_edge_kernel<<<E, kThreads, 0, s>>>(A, final_pass);
+        backend_edge_kernel<<<E, kEdgeThreads, 0, s>>>(A, final_pass);
         timer_end(s);
         if (final_pass) break;
         timer_begin("backend_solve", s);

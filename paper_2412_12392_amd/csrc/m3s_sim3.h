@@ -207,10 +207,12 @@ template <int NT>
 __device__ void sum_partials(const float* __restrict__ parts, int nparts, SumLds<NT>& S, double* out) {
     constexpr int G = NT / kMomentStride;
     const int t = threadIdx.x, g = t / kMomentStride, v = t % kMomentStride;
-    double acc = 0.0;
+    if (t < NT) {  // threads beyond NT only join the barriers
+        double acc = 0.0;
 #pragma unroll 8
-    for (int b = g; b < nparts; b += G) acc += (double)parts[(size_t)b * kMomentStride + v];
-    S.part[t] = acc;
+        for (int b = g; b < nparts; b += G) acc += (double)parts[(size_t)b * kMomentStride + v];
+        S.part[t] = acc;
+    }
     __syncthreads();
     if (t < kMomentStride) {
         double s = 0.0;
