@@ -1087,6 +1087,7 @@ struct SparseLds {
     uint32_t elist[kEntries];
     int32_t estart[kBlocks + 1];
     uint16_t ustart[kBlocks + 2];
+    uint16_t off[kBlocks];                     // slots of the blocks off the diagonal
     uint16_t colstart[M3S_MAX_KEYFRAMES + 2], lvl[M3S_MAX_KEYFRAMES + 2];
     uint8_t pos[M3S_MAX_KEYFRAMES];
     uint8_t si[kBlocks], sj[kBlocks];
@@ -1109,9 +1110,15 @@ __device__ __forceinline__ void read_lists(const BackendArgs& A, SparseLds<LDS>&
 #pragma unroll
         for (int j = 0; j < kE / kSolveThreads; ++j) l[j] = A.elist[min(tid + j * kSolveThreads, 3 * A.E - 1)];
     }
+    const int nblk = P.nblk;
     for (int i = tid; i < kB; i += kSolveThreads) {
-        S.si[i] = P.si[i];
-        S.sj[i] = P.sj[i];
+        const uint8_t si = P.si[i], sj = P.sj[i];
+        S.si[i] = si;
+        S.sj[i] = sj;
+        // A column's diagonal block comes first, so slot i is
+        // the (i - sj - 1)-th other one.  (No pattern, so any value, in dense mode.)
+        const int j = i - sj - 1;
+        if (i < nblk && si != sj && j >= 0) S.off[j] = (uint16_t)i;
     }
     for (int i = tid; i <= kB; i += kSolveThreads) {
         S.ustart[i] = P.ustart[i];
@@ -1135,6 +1142,80 @@ __device__ __forceinline__ void read_lists(const BackendArgs& A, SparseLds<LDS>&
     __syncthreads();
 }
 
+// The blocks of the reduced system, each the sum of its edges' blocks in edge
+// order, to Lb: one lane per entry and one wave per block.  A step of a wave
+// takes QD diagonal blocks, of which the reads of each one's first four edges
+// (a sequence's) are issued together without branches between them, and QO
+// others with two (both directions of a pair); they come from memory that other
+// XCDs wrote.  With four reads for every block, eight blocks a step and the
+// right-hand side after them the gather took 3.3, 6.4 and 14.2 us for 8, 32 and
+// 96 keyframes, now 2.2, 4.3 and 11.1; steps of 4 + 8 blocks the same, of 6 + 12
+// and 12 + 24 slower (96 keyframes 1,177 and 1,462 us a call, not 1,172).
+template <bool LDS, int QD, int QO>
+__device__ __forceinline__ void gather_blocks(const BackendArgs& A, SparseLds<LDS>& S, double* __restrict__ Lb, int nb,
+                                              int nblk) {
+    constexpr int kD = 4, kO = 2, kWaves = kSolveThreads / 64;
+    const int tid = threadIdx.x, wave = tid >> 6, en = min(tid & 63, 48), et = 7 * (en % 7) + en / 7;
+    const int noff = nblk - nb;
+    auto read = [&](int l, double& t) {
+        const uint32_t f = S.elist[min(l, (int)S.kEntries - 1)];
+        // Past the block's edges (or beyond the listed ones): some edge's block, not used.
+        const uint32_t e = min(f & kEdgeMask, (uint32_t)(A.E - 1));
+        t = A.edge_blk[(size_t)e * kBlk + ((f & kEdgeTransposed) ? et : en)];
+    };
+    auto sum = [&](const double* t, int most, int l0, int l1) {
+        double v = 0.0;
+        const int n0 = min(l0 + most, min(l1, (int)S.kEntries));
+#pragma unroll
+        for (int j = 0; j < kD; ++j)
+            if (j < most) v += l0 + j < n0 ? t[j] : 0.0;
+        for (int l = max(n0, l0); l < l1; ++l) {
+            const uint32_t f = l < S.kEntries ? S.elist[l] : A.elist[l];
+            v += A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + ((f & kEdgeTransposed) ? et : en)];
+        }
+        return v;
+    };
+    const bool lane = (tid & 63) < 49;
+    for (int d0 = wave, o0 = wave; d0 < nb || o0 < noff; d0 += kWaves * QD, o0 += kWaves * QO) {
+        double td[QD][kD], to[QO][kD];
+        int sd[QD], so[QO], l0[QD + QO], l1[QD + QO];
+#pragma unroll
+        for (int i = 0; i < QD; ++i) sd[i] = S.colstart[min(d0 + i * kWaves, nb - 1)];
+#pragma unroll
+        for (int i = 0; i < QO; ++i) so[i] = min((int)S.off[max(min(o0 + i * kWaves, noff - 1), 0)], nblk - 1);
+#pragma unroll
+        for (int i = 0; i < QD; ++i) {
+            l0[i] = S.estart[sd[i]];
+            l1[i] = S.estart[sd[i] + 1];
+        }
+#pragma unroll
+        for (int i = 0; i < QO; ++i) {
+            l0[QD + i] = S.estart[so[i]];
+            l1[QD + i] = S.estart[so[i] + 1];
+        }
+#pragma unroll
+        for (int i = 0; i < QD; ++i)
+#pragma unroll
+            for (int j = 0; j < kD; ++j) read(l0[i] + j, td[i][j]);
+#pragma unroll
+        for (int i = 0; i < QO; ++i)
+#pragma unroll
+            for (int j = 0; j < kO; ++j) read(l0[QD + i] + j, to[i][j]);
+#pragma unroll
+        for (int i = 0; i < QD; ++i) {
+            if (d0 + i * kWaves >= nb) break;
+            const double v = sum(td[i], kD, l0[i], l1[i]);
+            if (lane) Lb[49 * sd[i] + en] = v;
+        }
+#pragma unroll
+        for (int i = 0; i < QO; ++i) {
+            if (o0 + i * kWaves >= noff) break;
+            const double v = sum(to[i], kO, l0[QD + i], l1[QD + i]);
+            if (lane) Lb[49 * so[i] + en] = -v;
+        }
+    }
+}
+
 // One workgroup: the block-sparse Cholesky over the pattern, left looking and
 // level by level, the forward substitution folded in, the backward substitution
 // (levels in reverse), and the pose updates.  Per level:
@@ -1149,59 +1230,33 @@ template <bool LDS>
 __device__ __forceinline__ void sparse_solve(const BackendArgs& A, SparseLds<LDS>& S, double* __restrict__ Lb) {
     const int nb = A.N - 1, tid = threadIdx.x;
     const int nblk = A.pat->nblk, nlev = A.pat->nlev;
-    // The system's blocks, gathered from the edges' blocks in edge order: one
-    // lane per entry and one wave per block, kQ blocks a step with the reads of
-    // each one's first kE edges (two per block and four per diagonal in a
-    // sequence) issued together, without branches between them: they come from
-    // memory that other XCDs wrote.  (Entry by entry with branches: 9.5 us for 89
-    // blocks and 25 us for 286; this 6.6 and 14.6 us; with the indices in scalar
-    // registers 7.4 and 17.2 us.)
-    constexpr int kQ = 8, kE = 4;
-    const int wave = tid >> 6, en = min(tid & 63, 48), et = 7 * (en % 7) + en / 7;
-    for (int sb = wave * kQ; sb < nblk; sb += kQ * (kSolveThreads / 64)) {
-        double t[kQ][kE];
-        uint32_t f[kQ][kE];
-        int l0[kQ], l1[kQ];
+    // The right-hand side -g (g_i -= A^T g_e, g_j += A^T g_e): the reads of each
+    // entry's first kR edges, summed below.
+    constexpr int kR = 4, kRounds = (kMaxDim + kSolveThreads - 1) / kSolveThreads;
+    double g[kRounds][kR];
+    auto rhs_entry = [&](int l, int a) {
+        return A.edge_blk[(size_t)min(S.elist[min(l, (int)S.kEntries - 1)] & kEdgeMask, (uint32_t)(A.E - 1)) * kBlk + 49 + a];
+    };
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            const int s = min(sb + i, nblk - 1);
-            l0[i] = S.estart[s];
-            l1[i] = sb + i < nblk ? S.estart[s + 1] : l0[i];
-        }
+    for (int r = 0; r < kRounds; ++r) {
+        const int q = min(tid + r * kSolveThreads, 7 * nb - 1), l0 = S.estart[S.colstart[q / 7]];
+        if (r * kSolveThreads < 7 * nb)
 #pragma unroll
-        for (int i = 0; i < kQ; ++i)
-#pragma unroll
-            for (int j = 0; j < kE; ++j) f[i][j] = S.elist[min(l0[i] + j, (int)S.kEntries - 1)];
-        // Past the block's edges (or beyond the listed ones): some edge's block, not used.
-#pragma unroll
-        for (int i = 0; i < kQ; ++i)
-#pragma unroll
-            for (int j = 0; j < kE; ++j) {
-                const uint32_t e = min(f[i][j] & kEdgeMask, (uint32_t)(A.E - 1));
-                t[i][j] = A.edge_blk[(size_t)e * kBlk + ((f[i][j] & kEdgeTransposed) ? et : en)];
-            }
-#pragma unroll
-        for (int i = 0; i < kQ; ++i) {
-            double v = 0.0;
-            const int n0 = min(l0[i] + kE, min(l1[i], (int)S.kEntries));
-#pragma unroll
-            for (int j = 0; j < kE; ++j) v += l0[i] + j < n0 ? t[i][j] : 0.0;
-            for (int l = max(n0, l0[i]); l < l1[i]; ++l) {
-                const uint32_t g = l < S.kEntries ? S.elist[l] : A.elist[l];
-                v += A.edge_blk[(size_t)(g & kEdgeMask) * kBlk + ((g & kEdgeTransposed) ? et : en)];
-            }
-            const int s = min(sb + i, nblk - 1);
-            if ((tid & 63) < 49 && sb + i < nblk) Lb[49 * s + en] = S.si[s] == S.sj[s] ? v : -v;
-        }
+            for (int j = 0; j < kR; ++j) g[r][j] = rhs_entry(l0 + j, q % 7);
     }
-    // Right-hand side -g: g_i -= A^T g_e, g_j += A^T g_e.
-    for (int q = tid; q < 7 * nb; q += kSolveThreads) {
-        const int k = q / 7, a = q - 7 * k, s = S.colstart[k];
+    gather_blocks<LDS, 2, 4>(A, S, Lb, nb, nblk);
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const int q = tid + r * kSolveThreads;
+        if (q >= 7 * nb) break;
+        const int s = S.colstart[q / 7], l0 = S.estart[s], l1 = S.estart[s + 1];
         double v = 0.0;
-#pragma unroll 4
-        for (int l = S.estart[s]; l < S.estart[s + 1]; ++l) {
+        for (int l = l0; l < l1; ++l) {
+            const int j = l - l0;
             const uint32_t f = l < S.kEntries ? S.elist[l] : A.elist[l];
-            const double t = A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + 49 + a];
+            double t;
+            if (j < kR && l < S.kEntries) t = j == 0 ? g[r][0] : j == 1 ? g[r][1] : j == 2 ? g[r][2] : g[r][3];
+            else t = A.edge_blk[(size_t)(f & kEdgeMask) * kBlk + 49 + q % 7];
             v += (f & kEdgeOwnI) ? t : -t;
         }
         S.xs[q] = v;
