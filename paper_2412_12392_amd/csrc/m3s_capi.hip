@@ -164,9 +164,25 @@ EdgeArgs make_edge(const m3s_pair* A, const m3s_outputs* O, const m3s_params* P,
 // -1 means the library's own choice.
 thread_local m3s_launch_config g_override = {-1, -1, -1, -1, -1};
 
-// Tile configuration of the single-pair launch and of an untuned batched launch.
+// Tile configuration of an untuned batched launch.
 int chosen_tile_config() {
     return g_override.tile_config >= 0 ? g_override.tile_config : m3s::kDefaultTileConfig;
+}
+
+// Tile configuration of the single-pair launch.  A small frame is bound by the
+// latency of one tile, which 8 x 8 tiles of one wave shorten (no barrier across
+// waves, a smaller region, and one wave's stragglers hold up nobody else), as
+// long as all of them are resident at once: six a CU by LDS, or three with the
+// bands of two levels.  At r = 3, us with 16 x 16 and with 8 x 8 tiles, prep
+// included: 64 x 48 20.8 and 18.3, 160 x 120 21.2 and 19.6, 320 x 240 (4.7 tiles a
+// CU) 25.2 and 24.7, 512 x 384 (12) 31.8 and 46.9; two levels at 256 x 192 (3)
+// 30.8 and 30.4, at 320 x 240 36.8 and 55.3.  Three levels fill the smaller tiles'
+// regions: 224 x 160 43.3 and 46.8.
+int pair_tile_config(const m3s_pair* A, const m3s_params* P, int cus) {
+    if (g_override.tile_config >= 0) return g_override.tile_config;
+    const int64_t tiles = ((int64_t)A->W + 7) / 8 * ((A->H + 7) / 8);
+    const int per_cu = P->refine_levels == 1 ? 6 : P->refine_levels == 2 ? 3 : 0;
+    return desc_in_regs(A) && tiles <= (int64_t)per_cu * cus ? m3s::kSmallTileConfig : m3s::kDefaultTileConfig;
 }
 
 // Tile-to-XCD band mapping of the single-pair launch (on unless overridden).
@@ -627,7 +643,7 @@ m3s_status m3s_match_fwd(const m3s_pair* pair, const m3s_params* params, const m
     EdgeArgs A = make_edge(pair, out, P, P->max_iter, P->refine_radius, rays);
     hipError_t e = m3s::launch_prep(pair->Xii, rays, pair->H, pair->W, st);
     if (e != hipSuccess) return hip_fail(e, "prep launch");
-    e = m3s::launch_fwd(A, chosen_tile_config(), desc_in_regs(pair), chosen_xcd_remap(), st);
+    e = m3s::launch_fwd(A, pair_tile_config(pair, P, info.cus), desc_in_regs(pair), chosen_xcd_remap(), st);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
     g_last_error.clear();
     return M3S_OK;
@@ -654,7 +670,7 @@ m3s_status m3s_match_fwd_noalloc(const m3s_pair* pair, const m3s_params* params,
     EdgeArgs A = make_edge(pair, out, P, P->max_iter, P->refine_radius, rays);
     g_timer_suppressed = true;
     hipError_t e = m3s::launch_prep(pair->Xii, rays, pair->H, pair->W, st);
-    if (e == hipSuccess) e = m3s::launch_fwd(A, chosen_tile_config(), desc_in_regs(pair), chosen_xcd_remap(), st);
+    if (e == hipSuccess) e = m3s::launch_fwd(A, pair_tile_config(pair, P, info.cus), desc_in_regs(pair), chosen_xcd_remap(), st);
     g_timer_suppressed = false;
     if (e != hipSuccess) return hip_fail(e, "forward launch");
     g_last_error.clear();

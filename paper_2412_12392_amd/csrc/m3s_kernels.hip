@@ -601,10 +601,13 @@ constexpr int kRegionPx16 = 844;          // 844 px x 48 B = 39.6 KiB: four work
 constexpr int kRegionPx16Multi = 1088;    // the multi-level kernel: 51 KiB, three workgroups per CU
 constexpr int kRegionPx16Small = 256;     // 8 x 8 tiles: 12 KiB, twelve one-wave workgroups per CU
 
-// Region capacity (pixels) of a tile shape's fp16 LDS buffers.
-template <int TX, int TY, bool MULTI>
+constexpr int kRegionPx16Pair = 512;      // 8 x 8 tiles of one pair: 24 KiB, six workgroups per CU
+
+// Region capacity (pixels) of a tile shape's fp16 LDS buffers (PAIR: of the kernel
+// for one pair, whose 8 x 8 tiles serve small frames, which leave LDS to spare).
+template <int TX, int TY, bool MULTI, bool PAIR>
 constexpr int f16_cap() {
-    return MULTI ? kRegionPx16Multi : (TX * TY <= 64 ? kRegionPx16Small : kRegionPx16);
+    return MULTI ? kRegionPx16Multi : (TX * TY <= 64 ? (PAIR ? kRegionPx16Pair : kRegionPx16Small) : kRegionPx16);
 }
 constexpr float kF16Max = 60000.f;        // larger scaled magnitudes fall back to the exact scan
 constexpr float kScale16 = 256.f;         // 2^8, applied to both operands before the conversion
@@ -1000,9 +1003,10 @@ constexpr int kMaxBands = 6;
 // exceeds 5, or whose region holds a value too large for fp16 is scanned
 // exactly from global memory instead (the whole tile at that level).
 template <int TX, int TY, bool EARLY, int MARGIN = kRayMargin, int UNROLL = 1, bool MULTI = false>
-__device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, TileLds16<f16_cap<TX, TY, MULTI>()>& S) {
+__device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty,
+                                         TileLds16<f16_cap<TX, TY, MULTI, EARLY>()>& S) {
     constexpr int NT = TX * TY;
-    constexpr int CAP = f16_cap<TX, TY, MULTI>();
+    constexpr int CAP = f16_cap<TX, TY, MULTI, EARLY>();
     const int tid = threadIdx.x;
     const int x = tx * TX + tid % TX, y = ty * TY + tid / TX;
     const bool inside = x < A.W && y < A.H;
@@ -1115,9 +1119,9 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty, Tile
 // Four workgroups of 256 lanes fit a CU by LDS; keep the registers within that too.
 // The multi-level refine keeps more state per lane: three waves per SIMD.
 template <int TX, int TY, bool MULTI>
-__global__ void __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(MULTI ? 3 : 4)))
+__global__ void __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(TX * TY <= 64 ? 2 : MULTI ? 3 : 4)))
 fwd_f16_kernel(EdgeArgs A, int remap) {
-    __shared__ TileLds16<f16_cap<TX, TY, MULTI>()> S;
+    __shared__ TileLds16<f16_cap<TX, TY, MULTI, true>()> S;
     const int tiles_x = (A.W + TX - 1) / TX, tiles = tiles_x * ((A.H + TY - 1) / TY);
     const int t = tile_of_block(blockIdx.x, tiles, remap != 0);
     if (t < 0) return;
@@ -1202,7 +1206,7 @@ batched_fwd_kernel(const EdgeArgs* __restrict__ E, int n_edges, int total_tiles,
     __shared__ int s_tile;
     __shared__ typename std::conditional<
         MODE == 1, TileLds,
-        typename std::conditional<MODE == 2, TileLds16<f16_cap<TX, TY, MULTI>()>, int>::type>::type S;
+        typename std::conditional<MODE == 2, TileLds16<f16_cap<TX, TY, MULTI, false>()>, int>::type>::type S;
     int e = 0;
     for (;;) {
         if (threadIdx.x == 0) s_tile = atomicAdd(counter, 1);

@@ -44,3 +44,22 @@ def test_refine_windows_beyond_the_image(H, W, r, levels, tile):
         for g in got[1:]:
             for k in ("p", "idx", "valid", "theta", "xhat"):
                 assert np.array_equal(got[0][k], g[k], equal_nan=True), (k, K)
+
+
+@pytest.mark.parametrize("H,W,r,levels", [(256, 384, 3, 1), (256, 392, 4, 1), (8, 12288, 2, 1), (192, 256, 4, 2),
+                                          (192, 264, 3, 2), (8, 9, 3, 2), (96, 128, 3, 3)])
+def test_small_frame_tiles(H, W, r, levels):
+    """The library's own choice of tiles, at the sizes where it changes (256
+    CUs: 1,536 and 768 tiles of 8 x 8), against the scan of global memory."""
+    print("small frame", H, W, r, levels, flush=True)
+    t = parity.pair_tensors(synth.make_pair(H, W, 70 + H + W, conf=True))
+    args = (t["Xii"], t["Xji"], t["Dii"], t["Dji"], t["Qii"], t["Qji"], None)
+    prm = params(refine_radius=r, refine_levels=levels, max_theta=10.0)
+    got = parity.result_numpy(match(*args, prm, want_xhat=True))
+    set_launch(tile_config=0)
+    try:
+        ref = parity.result_numpy(match(*args, prm, want_xhat=True))
+    finally:
+        set_launch()
+    for k in ("p", "idx", "valid", "theta", "xhat"):
+        assert np.array_equal(ref[k], got[k], equal_nan=True), k
