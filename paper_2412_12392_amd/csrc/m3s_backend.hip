@@ -720,9 +720,9 @@ __device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
 // costs the latency of one column.  Eliminated one column at a time in keyframe
 // order, a 31-column system (a 32-keyframe sequence with 3 closures) took 31
 // steps of about 2.3 us and its factor had 115 blocks: 101 us; here it is 6
-// levels, 89 blocks and 35 us.  A 96-keyframe sequence with 8 closures had
+// levels, 89 blocks and 31 us.  A 96-keyframe sequence with 8 closures had
 // 791 blocks, more than LDS holds, and took the dense solve, 3,578 us; here it
-// is 9 levels, 288 blocks and 66 us.
+// is 9 levels, 288 blocks and 62 us.
 
 constexpr int kPatThreads = 512;
 
