@@ -114,6 +114,13 @@ __device__ __forceinline__ void count_path(int k) { atomicAdd(&g_path_counts[k],
 
 // Descriptor dot product of the query (in registers for a compile-time D)
 // with reference pixel m; the products are accumulated in index order.
+// A scan of global memory is bound by the L1: a pixel's loads hit the line that
+// the first of them brought only if no other wave's loads come in between.  So
+// they are issued back to back: none waits for an earlier one's data, and none
+// overwrites the address (which costs a wait state before it, enough for another
+// wave's loads).  16 edges of 512 x 384 at r = 6 in one launch, 4 workgroups a CU:
+// 2,490 us, with the last load over its own address 3,150, and, refining from
+// global memory alone (tile configuration 0) with the loads in two groups, 3,570.
 template <int DT>
 struct QueryDesc {
     float q[DT];
@@ -127,14 +134,18 @@ struct QueryDesc {
     }
     __device__ __forceinline__ float dot(const float* __restrict__ Di, long m, int) const {
         const float4* s = reinterpret_cast<const float4*>(Di + (long)DT * m);
+        float4 v[DT / 4];
+#pragma unroll
+        for (int k = 0; k < DT / 4; ++k) v[k] = s[k];
+        __builtin_amdgcn_sched_barrier(0x7);  // the ALU may cross, memory accesses may not
+        asm volatile("" : : "v"(s));          // the address outlives the loads
         float acc = 0.f;
 #pragma unroll
         for (int k = 0; k < DT / 4; ++k) {
-            float4 v = s[k];
-            acc = fmaf(q[4 * k], v.x, acc);
-            acc = fmaf(q[4 * k + 1], v.y, acc);
-            acc = fmaf(q[4 * k + 2], v.z, acc);
-            acc = fmaf(q[4 * k + 3], v.w, acc);
+            acc = fmaf(q[4 * k], v[k].x, acc);
+            acc = fmaf(q[4 * k + 1], v[k].y, acc);
+            acc = fmaf(q[4 * k + 2], v[k].z, acc);
+            acc = fmaf(q[4 * k + 3], v[k].w, acc);
         }
         return acc;
     }
