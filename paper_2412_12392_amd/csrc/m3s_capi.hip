@@ -197,6 +197,7 @@ struct Plan {
     size_t off_table = 0, off_prep = 0, off_rays = 0, total_bytes = 0;
     bool desc_regs = true;
     int levels = 1;
+    int radius = 0;                            // as launch_batched takes it
     std::string signature;
 };
 
@@ -328,6 +329,8 @@ m3s_status plan_batched(const m3s_edge* edges, int32_t n, const m3s_params* P, i
         prep += m3s::prep_tiles(E.in.H, E.in.W);
         if (tiles > INT32_MAX / 2 || prep > INT32_MAX / 2) return fail(M3S_ERR_SHAPE, "batch too large");
         if (!desc_in_regs(&E.in)) plan->desc_regs = false;
+        const int rc = r >= 2 && r <= 4 ? r : 0;
+        plan->radius = k == 0 || plan->radius == rc ? rc : m3s::kAnyRadius;
         plan->table.push_back(A);
         snprintf(buf, sizeof buf, "%d,%d,%d,%d,%d,%d,%d;", order[k], E.in.H, E.in.W, E.in.D, K, r,
                  (E.in.Qii ? 1 : 0) | (E.in.p_init ? 2 : 0) | (E.out.theta ? 4 : 0) | (E.out.xhat ? 8 : 0));
@@ -402,7 +405,7 @@ hipError_t run_batched(const Plan& plan, char* ws, const Launch& L, hipStream_t 
     return m3s::launch_batched(reinterpret_cast<const EdgeArgs*>(ws + plan.off_table),
                                reinterpret_cast<const int32_t*>(ws + plan.off_prep), (int)plan.table.size(),
                                plan.total_prep, plan.total_tiles, reinterpret_cast<int32_t*>(ws), L.tile,
-                               std::max(1, std::min(L.grid, plan.total_tiles)), L.margin, L.unroll, plan.levels,
+                               std::max(1, std::min(L.grid, plan.total_tiles)), L.margin, L.unroll, plan.levels, plan.radius,
                                plan.desc_regs, s);
 }
 

@@ -42,9 +42,12 @@ hipError_t launch_fwd(const EdgeArgs& A, int tile_config, bool desc_regs, bool x
 // Ray-window margins and LM unroll factors of the persistent fp16 kernel
 // (tile configuration 5); other configurations use the defaults.
 constexpr int kMarginMin = 1, kMarginMax = 3, kDefaultMargin = 2, kUnrollMax = 2;
+// radius: the edges' common refine radius where it is 2, 3 or 4, 0 where every
+// edge has another, kAnyRadius otherwise (which multi-level kernel runs).
+constexpr int kAnyRadius = -1;
 hipError_t launch_batched(const EdgeArgs* table, const int32_t* prep_begin, int n_edges, int total_prep_blocks,
                           int total_tiles, int32_t* counter, int tile_config, int grid, int margin, int unroll,
-                          int levels, bool desc_regs, hipStream_t s);
+                          int levels, int radius, bool desc_regs, hipStream_t s);
 // Device copy of `bytes` (a multiple of 4, both pointers 4-byte aligned)
 // from pinned host memory, by a kernel on stream s.
 hipError_t launch_host_copy(void* dst, const void* pinned_src, size_t bytes, hipStream_t s);

@@ -686,8 +686,16 @@ __device__ __forceinline__ bool slides(int r, int H, int W) {
     return r >= 2 && r <= 4 && H >= 2 * r + 1 && W >= 2 * r + 1;
 }
 
-// The same for the multi-level kernel, which does not slide.
-__device__ __forceinline__ bool scans_bands(int r) { return r >= 2 && r <= 4; }
+// The radii of a multi-level kernel: 2, 3 or 4 alone, all others, or any.  The
+// fewer forms of the scan a kernel holds, the fewer registers it keeps, so the
+// launch takes the kernel of its radius; only a batch of edges of different radii
+// takes the one for any.  16 edges of 512 x 384, two levels: r = 0 430 us, with the
+// kernel for any 442, r = 3 644 and 653, r = 5 1,200 and 1,263.
+constexpr int kOtherRadii = 0;
+
+// Whether scan16 covers a level of the multi-level kernel, which does not slide.
+template <int RT>
+__device__ __forceinline__ bool scans_bands(int r) { return RT == kAnyRadius ? r >= 2 && r <= 4 : RT != kOtherRadii; }
 
 // A query's window: the pixels it has slid (0, 0: not at all) and its top-left
 // candidate in the coordinates of the staged region (or band of it).
@@ -714,14 +722,17 @@ struct Window16 {
 // others being outside the image or in another band; columns outside read the
 // region's nearest one.  (Sliding would enlarge a coarse level's region.)  The
 // per-lane loops that radii and levels other than r = 3, 2^l <= 2 took before
-// cost about twice the instructions per candidate: at 512 x 384 three levels took
-// 80 us at r = 3 and 121 at r = 4, now 69 and 90; two levels of r = 4 74, now 58.
-template <int R, int CAP, bool CLIP, bool MULTI>
+// cost about twice the instructions per candidate: at 512 x 384, with the prep,
+// three levels took 84 us at r = 3 and 126 at r = 4, now 70 and 91; two levels of
+// r = 4 78, now 59.
+// SP: the spacing where it is fixed at compile time (columns at immediate
+// offsets, a tenth of the instructions less than with their own addresses), or 0.
+template <int R, int CAP, bool CLIP, bool MULTI, int SP>
 __device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restrict__ sd, const Window16& win, int rw,
                                        int lev, int rows, float tau, float& run, uint64_t& mask0, uint64_t& mask1) {
     constexpr int S = 2 * R + 1, N = S * S;
     static_assert(N <= 128 && S < 32, "mask width");
-    const int sp = MULTI ? 1 << lev : 1;
+    const int sp = SP ? SP : 1 << lev;
     bool in[S];
     int col[S];
 #pragma unroll
@@ -737,7 +748,7 @@ __device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restr
         float sc[S];
 #pragma unroll
         for (int dx = 0; dx < S; ++dx) {
-            const uint4* c = MULTI ? sd + (y * rw + col[dx]) : sd + (y * rw + win.x) + dx;
+            const uint4* c = SP && !(MULTI && CLIP) ? sd + (y * rw + win.x) + SP * dx : sd + (y * rw + col[dx]);
             sc[dx] = dot16(q16, c[0], c[CAP], c[2 * CAP]);
             if constexpr (CLIP) sc[dx] = in[dx] ? sc[dx] : -INFINITY;
         }
@@ -759,21 +770,38 @@ __device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restr
     }
 }
 
-// scan16 at the radius r of 2, 3 or 4, in its clipped form where some lane of
-// the wave needs it.
-template <int CAP, bool MULTI>
+// scan16 at the radius r of 2, 3 or 4 (RT where that is one of them), in its
+// clipped form where some lane of the wave needs it.
+template <int CAP, bool MULTI, int RT>
 __device__ __forceinline__ void scan16_r(const uint32_t* q16, const uint4* __restrict__ sd, const Window16& win, int r,
                                          int rw, int lev, int rows, float tau, float& run, uint64_t& mask0,
                                          uint64_t& mask1) {
     const bool out = MULTI ? win.x < 0 || win.x + (2 * r << lev) >= rw : (win.kx | win.ky) != 0;
     const bool clip = __any(out) != 0;
-    auto scan = [&](auto R) {
-        if (clip) scan16<decltype(R)::value, CAP, true, MULTI>(q16, sd, win, rw, lev, rows, tau, run, mask0, mask1);
-        else scan16<decltype(R)::value, CAP, false, MULTI>(q16, sd, win, rw, lev, rows, tau, run, mask0, mask1);
+    auto form = [&](auto R, auto C, auto SP) {
+        scan16<decltype(R)::value, CAP, decltype(C)::value, MULTI, decltype(SP)::value>(q16, sd, win, rw, lev, rows, tau,
+                                                                                      run, mask0, mask1);
     };
-    if (r == 3) scan(std::integral_constant<int, 3>{});
-    else if (r == 2) scan(std::integral_constant<int, 2>{});
-    else scan(std::integral_constant<int, 4>{});
+    auto scan = [&](auto R) {
+        std::integral_constant<int, 0> any;
+        std::integral_constant<int, 1> one;
+        std::integral_constant<int, 2> two;
+        if constexpr (MULTI) {
+            if (clip || lev > 1) form(R, std::true_type{}, any);
+            else if (lev == 1) form(R, std::false_type{}, two);
+            else form(R, std::false_type{}, one);
+        } else {
+            if (clip) form(R, std::true_type{}, one);
+            else form(R, std::false_type{}, one);
+        }
+    };
+    if constexpr (RT >= 2) {
+        scan(std::integral_constant<int, RT>{});
+    } else {
+        if (r == 3) scan(std::integral_constant<int, 3>{});
+        else if (r == 2) scan(std::integral_constant<int, 2>{});
+        else scan(std::integral_constant<int, 4>{});
+    }
 }
 
 // A query descriptor for the fp16 pre-filter: fp32 elements (exact rescoring),
@@ -888,15 +916,15 @@ __device__ __forceinline__ void f16_scan_band(const EdgeArgs& A, const Query16& 
     }
 }
 
-// One level of the exact first-maximum refine with the fp16 pre-filter: the
-// (2r+1)^2 grid of spacing 2^lev around (mx0, my0), over a staged region of rw x
-// rh pixels that holds every candidate inside the image.  dnorm: bound on |d|
-// over the region, dl1: bound on |d|_1.
-template <int CAP, bool MULTI>
-__device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query16& Q, int mx0, int my0, int lev,
-                                                 const uint4* __restrict__ sd, int rx0, int ry0, int rw, int rh,
-                                                 float dnorm, float dl1) {
-    const int H = A.H, W = A.W, r = A.r, side = 2 * r + 1, sp = 1 << lev;
+// The exact first-maximum refine of a single level with the fp16 pre-filter: the
+// (2r+1)^2 window around (mx0, my0), over a staged region of rw x rh pixels that
+// holds every candidate inside the image.  dnorm: bound on |d| over the region,
+// dl1: bound on |d|_1.
+template <int CAP>
+__device__ __forceinline__ long refine_f16_window(const EdgeArgs& A, const Query16& Q, int mx0, int my0,
+                                                  const uint4* __restrict__ sd, int rx0, int ry0, int rw, int rh,
+                                                  float dnorm, float dl1) {
+    const int H = A.H, W = A.W, r = A.r;
     const float tau = f16_tau(Q, dnorm, dl1);
 
     // Pass 1: fp16 scores in row-major window order over the candidates
@@ -905,34 +933,18 @@ __device__ __forceinline__ long refine_f16_level(const EdgeArgs& A, const Query1
     const uint4* c0 = sd + (my0 - ry0) * rw + (mx0 - rx0);
     float run = dot16(Q.q16, c0[0], c0[CAP], c0[2 * CAP]);
     uint64_t mask0 = 0, mask1 = 0;
-    Window16 win{0, 0, mx0 - (r << lev) - rx0, my0 - (r << lev) - ry0};
-    if (MULTI ? scans_bands(r) : slides(r, H, W)) {
-        if (!MULTI) {
-            win.kx = slide_by(mx0, r, W);
-            win.ky = slide_by(my0, r, H);
-            win.x += win.kx;
-            win.y += win.ky;
-        }
-        scan16_r<CAP, MULTI>(Q.q16, sd, win, r, rw, lev, rh, tau, run, mask0, mask1);
+    Window16 win{0, 0, mx0 - r - rx0, my0 - r - ry0};
+    if (slides(r, H, W)) {
+        win.kx = slide_by(mx0, r, W);
+        win.ky = slide_by(my0, r, H);
+        win.x += win.kx;
+        win.y += win.ky;
+        scan16_r<CAP, false, kAnyRadius>(Q.q16, sd, win, r, rw, 0, rh, tau, run, mask0, mask1);
     } else {
-        for (int dy = -r; dy <= r; ++dy) {
-            const int my = my0 + sp * dy;
-            if (my < 0 || my >= H) continue;
-            const uint4* d = sd + (my - ry0) * rw - rx0;
-            for (int dx = -r; dx <= r; ++dx) {
-                const int mx = mx0 + sp * dx;
-                if (mx < 0 || mx >= W) continue;
-                const int k = (dy + r) * side + (dx + r);
-                const float s16 = dot16(Q.q16, d[mx], d[mx + CAP], d[mx + 2 * CAP]);
-                run = __builtin_amdgcn_fmed3f(s16, run, INFINITY);
-                if (s16 >= run - tau) {
-                    if (k < 64) mask0 |= 1ull << k; else mask1 |= 1ull << (k - 64);
-                }
-            }
-        }
+        f16_scan_band<CAP>(A, Q, mx0, my0, 1, sd, rx0, ry0, rw, ry0 + rh - 1, tau, run, mask0, mask1);
     }
     // Pass 2: exact scores of the survivors.
-    return f16_rescore(A, Q, mx0 + win.kx, my0 + win.ky, sp, mask0, mask1);
+    return f16_rescore(A, Q, mx0 + win.kx, my0 + win.ky, 1, mask0, mask1);
 }
 
 // Stages region rows [ly, ly + rh) x columns [lx, lx + rw) of D^i_i into the
@@ -1013,7 +1025,7 @@ constexpr int kMaxBands = 6;
 // kMaxBands).  A level whose region does not fit (in bands), whose radius
 // exceeds 5, or whose region holds a value too large for fp16 is scanned
 // exactly from global memory instead (the whole tile at that level).
-template <int TX, int TY, bool EARLY, int MARGIN = kRayMargin, int UNROLL = 1, bool MULTI = false>
+template <int TX, int TY, bool EARLY, int MARGIN = kRayMargin, int UNROLL = 1, bool MULTI = false, int RT = kAnyRadius>
 __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty,
                                          TileLds16<f16_cap<TX, TY, MULTI, EARLY>()>& S) {
     constexpr int NT = TX * TY;
@@ -1024,7 +1036,7 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty,
     QState q;
     tile_lm<NT, EARLY, MARGIN, UNROLL>(A, x, y, inside, q, S.rays, (int)(sizeof(S.rays) / kRecBytes), S.box, tx * TX, min(tx * TX + TX, A.W) - 1, ty * TY,
                 min(ty * TY + TY, A.H) - 1);
-    const int r = A.r, W = A.W, H = A.H;
+    const int r = RT >= 2 ? RT : A.r, W = A.W, H = A.H;
     const long n = (long)y * W + x;
     long bi = -1;
     bool live = q.good;   // takes part in the level below
@@ -1062,18 +1074,19 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty,
             }
         };
         long lb = -1;
-        // Rows per band when the multi-level kernel stages a region that
-        // exceeds LDS band by band (0: not banded).
-        int band = 0;
         if constexpr (MULTI) {
-            if (any && r <= 5 && rw * rh > CAP && rw <= CAP && rh <= kMaxBands * (CAP / rw)) band = CAP / rw;
-        }
-        if (band > 0) {
-            if (tid == 0) count_path(kPathRefineBands);
+            // Rows staged at a time: all, or as many as LDS holds (0: the region
+            // takes too many bands, or the radius is above 5).  One loop for both
+            // cases: with the scan inlined for each of them the kernel spilt 21
+            // vector registers, and 16 edges of 512 x 384 at two levels of r = 3
+            // took 743 us, now 644 (r = 0 538, now 430).
+            const bool whole = rw * rh <= CAP;
+            const int band = any && r <= 5 && (whole || (rw <= CAP && rh <= kMaxBands * (CAP / rw))) ? (whole ? rh : CAP / rw) : 0;
+            if (band > 0 && !whole && tid == 0) count_path(kPathRefineBands);
             float pn2 = 0.f, run = -INFINITY;
             uint64_t mask0 = 0, mask1 = 0;
-            bool ok16 = true;
-            for (int b0 = 0; b0 < rh; b0 += band) {
+            bool ok16 = band > 0;
+            for (int b0 = 0; ok16 && b0 < rh; b0 += band) {
                 const int nr = min(band, rh - b0);
                 if (b0 > 0) __syncthreads();  // every lane is done with the previous band
                 pn2 = fmaxf(pn2, block_max16<NT>(stage_region16<NT, CAP, 1>(A, S.desc, lx, ly + b0, rw, nr), S.stat));
@@ -1082,34 +1095,39 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty,
                     break;
                 }
                 if (live) query();
-                if (live && b0 == 0) run = f16_floor(A, Q, (long)cy * W + cx);
                 if (live) {
+                    if (whole) {
+                        const uint4* c = S.desc + (cy - ly) * rw + (cx - lx);
+                        run = dot16(Q.q16, c[0], c[CAP], c[2 * CAP]);
+                    } else if (b0 == 0) {
+                        run = f16_floor(A, Q, (long)cy * W + cx);
+                    }
                     const float dnorm = sqrtf(pn2) * 1.0001f;
                     const float tau = f16_tau(Q, dnorm, kSqrt24Up * dnorm);
-                    if (scans_bands(r)) {
+                    if (scans_bands<RT>(r)) {
                         const Window16 win{0, 0, cx - reach - lx, cy - reach - (ly + b0)};
-                        scan16_r<CAP, MULTI>(Q.q16, S.desc, win, r, rw, lev, nr, tau, run, mask0, mask1);
+                        scan16_r<CAP, MULTI, RT>(Q.q16, S.desc, win, r, rw, lev, nr, tau, run, mask0, mask1);
                     } else {
                         f16_scan_band<CAP>(A, Q, cx, cy, sp, S.desc, lx, ly + b0, rw, ly + b0 + nr - 1, tau, run, mask0,
                                            mask1);
                     }
                 }
             }
-            if (!ok16 && tid == 0) count_path(kPathRefineGlobal);
+            if (any && !ok16 && tid == 0) count_path(kPathRefineGlobal);
             if (live) query();
             if (live)
                 lb = ok16 ? f16_rescore(A, Q, cx, cy, sp, mask0, mask1) : refine_global_level<24>(A, Q.qd, cx, cy, sp);
         } else {
             bool use16 = any && rw * rh <= CAP && r <= 5;
             float pn2 = 0.f;  // largest |d|^2 over the region's pixels
-            if (use16) pn2 = stage_region16<NT, CAP, MULTI ? 1 : 2>(A, S.desc, lx, ly, rw, rh);
+            if (use16) pn2 = stage_region16<NT, CAP, 2>(A, S.desc, lx, ly, rw, rh);
             pn2 = block_max16<NT>(pn2, S.stat);
             use16 = use16 && pn2 <= (kF16Max / kScale16) * (kF16Max / kScale16);
             if (any && !use16 && tid == 0) count_path(kPathRefineGlobal);
             if (live) query();
             if (live) {
                 const float dnorm = sqrtf(pn2) * 1.0001f;
-                lb = use16 ? refine_f16_level<CAP, MULTI>(A, Q, cx, cy, lev, S.desc, lx, ly, rw, rh, dnorm, kSqrt24Up * dnorm)
+                lb = use16 ? refine_f16_window<CAP>(A, Q, cx, cy, S.desc, lx, ly, rw, rh, dnorm, kSqrt24Up * dnorm)
                            : refine_global_level<24>(A, Q.qd, cx, cy, sp);
             }
         }
@@ -1129,14 +1147,14 @@ __device__ __forceinline__ void tile_f16(const EdgeArgs& A, int tx, int ty,
 
 // Four workgroups of 256 lanes fit a CU by LDS; keep the registers within that too.
 // The multi-level refine keeps more state per lane: three waves per SIMD.
-template <int TX, int TY, bool MULTI>
+template <int TX, int TY, bool MULTI, int RT = kAnyRadius>
 __global__ void __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(TX * TY <= 64 ? 2 : MULTI ? 3 : 4)))
 fwd_f16_kernel(EdgeArgs A, int remap) {
     __shared__ TileLds16<f16_cap<TX, TY, MULTI, true>()> S;
     const int tiles_x = (A.W + TX - 1) / TX, tiles = tiles_x * ((A.H + TY - 1) / TY);
     const int t = tile_of_block(blockIdx.x, tiles, remap != 0);
     if (t < 0) return;
-    tile_f16<TX, TY, true, kRayMargin, 1, MULTI>(A, t % tiles_x, t / tiles_x, S);
+    tile_f16<TX, TY, true, kRayMargin, 1, MULTI, RT>(A, t % tiles_x, t / tiles_x, S);
 }
 
 template <int TX, int TY>
@@ -1210,7 +1228,8 @@ __global__ void __launch_bounds__(256) batched_prep_kernel(const EdgeArgs* __res
 // tile).  LDS tiles need D = 24 and 16-byte aligned descriptors on every edge.
 // MODE 0: refine from global memory; 1: fp32 region in LDS; 2: fp16 pre-filter
 // with ray-window margin MARGIN and LM unroll UNROLL.
-template <int TX, int TY, int DT, int MODE, int MARGIN = kRayMargin, int UNROLL = 1, bool MULTI = false>
+template <int TX, int TY, int DT, int MODE, int MARGIN = kRayMargin, int UNROLL = 1, bool MULTI = false,
+          int RT = kAnyRadius>
 __global__ void __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(MODE == 2 ? (MULTI ? 3 : 4) : 1)))
 batched_fwd_kernel(const EdgeArgs* __restrict__ E, int n_edges, int total_tiles,
                                                                int32_t* __restrict__ counter) {
@@ -1236,7 +1255,7 @@ batched_fwd_kernel(const EdgeArgs* __restrict__ E, int n_edges, int total_tiles,
         if constexpr (MODE == 1) {
             tile_lds<TX, TY>(A, tx, ty, S);
         } else if constexpr (MODE == 2) {
-            tile_f16<TX, TY, false, MARGIN, UNROLL, MULTI>(A, tx, ty, S);
+            tile_f16<TX, TY, false, MARGIN, UNROLL, MULTI, RT>(A, tx, ty, S);
         } else {
             int x = tx * TX + (int)(threadIdx.x % TX);
             int y = ty * TY + (int)(threadIdx.x / TX);
@@ -1667,6 +1686,25 @@ hipError_t launch_prep(const float* Xii, float4* rays, int H, int W, hipStream_t
     return hipGetLastError();
 }
 
+// Calls f with the radii of the multi-level kernel for radius r (MIXED: or for edges
+// of several, kAnyRadius).
+template <bool MIXED, class F>
+static void with_radius(int r, F f) {
+    switch (r) {
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        default:
+            if constexpr (MIXED) {
+                if (r == kAnyRadius) {
+                    f(std::integral_constant<int, kAnyRadius>{});
+                    break;
+                }
+            }
+            f(std::integral_constant<int, kOtherRadii>{});
+    }
+}
+
 template <int TX, int TY>
 static void launch_fwd_tile(const EdgeArgs& A, bool desc_regs, int mode, bool remap, hipStream_t s) {
     const int tiles = ((A.W + TX - 1) / TX) * ((A.H + TY - 1) / TY);
@@ -1674,8 +1712,12 @@ static void launch_fwd_tile(const EdgeArgs& A, bool desc_regs, int mode, bool re
     const int rm = remap ? 1 : 0;
     if constexpr (TX == TY) {  // the fp16 configurations have square tiles
         if (mode == 2 && desc_regs) {
-            if (A.levels > 1) fwd_f16_kernel<TX, TY, true><<<grid, TX * TY, 0, s>>>(A, rm);
-            else fwd_f16_kernel<TX, TY, false><<<grid, TX * TY, 0, s>>>(A, rm);
+            if (A.levels > 1)
+                with_radius<false>(A.r, [&](auto R) {
+                    fwd_f16_kernel<TX, TY, true, decltype(R)::value><<<grid, TX * TY, 0, s>>>(A, rm);
+                });
+            else
+                fwd_f16_kernel<TX, TY, false><<<grid, TX * TY, 0, s>>>(A, rm);
             return;
         }
     }
@@ -1721,13 +1763,18 @@ static void launch_batched_f16(const EdgeArgs* table, int n_edges, int total_til
 
 template <int TX, int TY>
 static void launch_batched_tile(const EdgeArgs* table, int n_edges, int total_tiles, int32_t* counter, int grid,
-                                bool desc_regs, int mode, int margin, int unroll, int levels, hipStream_t s) {
-    if constexpr (TX == 16 && TY == 16) {
+                                bool desc_regs, int mode, int margin, int unroll, int levels, int radius,
+                                hipStream_t s) {
+    if constexpr (TX == TY) {
         if (mode == 2 && desc_regs && levels > 1) {
-            batched_fwd_kernel<TX, TY, 24, 2, kRayMargin, 1, true><<<grid, TX * TY, 0, s>>>(table, n_edges, total_tiles,
-                                                                                        counter);
+            with_radius<true>(radius, [&](auto R) {
+                batched_fwd_kernel<TX, TY, 24, 2, kRayMargin, 1, true, decltype(R)::value>
+                    <<<grid, TX * TY, 0, s>>>(table, n_edges, total_tiles, counter);
+            });
             return;
         }
+    }
+    if constexpr (TX == 16 && TY == 16) {
         if (mode == 2 && desc_regs) {
             const int v = 2 * (margin - 1) + (unroll - 1);
             switch (v) {
@@ -1742,11 +1789,7 @@ static void launch_batched_tile(const EdgeArgs* table, int n_edges, int total_ti
         }
     } else if constexpr (TX == TY) {
         if (mode == 2 && desc_regs) {
-            if (levels > 1)
-                batched_fwd_kernel<TX, TY, 24, 2, kRayMargin, 1, true><<<grid, TX * TY, 0, s>>>(table, n_edges,
-                                                                                            total_tiles, counter);
-            else
-                batched_fwd_kernel<TX, TY, 24, 2><<<grid, TX * TY, 0, s>>>(table, n_edges, total_tiles, counter);
+            batched_fwd_kernel<TX, TY, 24, 2><<<grid, TX * TY, 0, s>>>(table, n_edges, total_tiles, counter);
             return;
         }
     }
@@ -1760,19 +1803,19 @@ static void launch_batched_tile(const EdgeArgs* table, int n_edges, int total_ti
 
 hipError_t launch_batched(const EdgeArgs* table, const int32_t* prep_begin, int n_edges, int total_prep_blocks,
                           int total_tiles, int32_t* counter, int tile_config, int grid, int margin, int unroll,
-                          int levels, bool desc_regs, hipStream_t s) {
+                          int levels, int radius, bool desc_regs, hipStream_t s) {
     timer_begin("batched_prep", s);
     batched_prep_kernel<<<total_prep_blocks, 256, 0, s>>>(table, prep_begin, n_edges, counter);
     timer_end(s);
     timer_begin("batched_fwd", s);
     switch (tile_config) {
-        case 1: launch_batched_tile<16, 16>(table, n_edges, total_tiles, counter, grid, desc_regs, 0, margin, unroll, levels, s); break;
-        case 2: launch_batched_tile<64, 4>(table, n_edges, total_tiles, counter, grid, desc_regs, 0, margin, unroll, levels, s); break;
-        case 3: launch_batched_tile<16, 16>(table, n_edges, total_tiles, counter, grid, desc_regs, 1, margin, unroll, levels, s); break;
-        case 4: launch_batched_tile<32, 8>(table, n_edges, total_tiles, counter, grid, desc_regs, 1, margin, unroll, levels, s); break;
-        case 5: launch_batched_tile<16, 16>(table, n_edges, total_tiles, counter, grid, desc_regs, 2, margin, unroll, levels, s); break;
-        case 6: launch_batched_tile<8, 8>(table, n_edges, total_tiles, counter, grid, desc_regs, 2, margin, unroll, levels, s); break;
-        default: launch_batched_tile<32, 8>(table, n_edges, total_tiles, counter, grid, desc_regs, 0, margin, unroll, levels, s); break;
+        case 1: launch_batched_tile<16, 16>(table, n_edges, total_tiles, counter, grid, desc_regs, 0, margin, unroll, levels, radius, s); break;
+        case 2: launch_batched_tile<64, 4>(table, n_edges, total_tiles, counter, grid, desc_regs, 0, margin, unroll, levels, radius, s); break;
+        case 3: launch_batched_tile<16, 16>(table, n_edges, total_tiles, counter, grid, desc_regs, 1, margin, unroll, levels, radius, s); break;
+        case 4: launch_batched_tile<32, 8>(table, n_edges, total_tiles, counter, grid, desc_regs, 1, margin, unroll, levels, radius, s); break;
+        case 5: launch_batched_tile<16, 16>(table, n_edges, total_tiles, counter, grid, desc_regs, 2, margin, unroll, levels, radius, s); break;
+        case 6: launch_batched_tile<8, 8>(table, n_edges, total_tiles, counter, grid, desc_regs, 2, margin, unroll, levels, radius, s); break;
+        default: launch_batched_tile<32, 8>(table, n_edges, total_tiles, counter, grid, desc_regs, 0, margin, unroll, levels, radius, s); break;
     }
     timer_end(s);
     return hipGetLastError();
