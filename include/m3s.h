@@ -268,7 +268,7 @@ typedef struct {
 /* Fills *params with q_min 1.5, sigma_ray 0.003, sigma_dist 0.1, Huber 1.345, 10 iterations.  NULL is ignored. */
 void m3s_default_track_params(m3s_track_params *params);
 
-/* Workspace bytes m3s_track_pose needs for an H x W keyframe (0 on invalid shapes). */
+/* Workspace bytes m3s_track_pose needs for an H x W keyframe (0 on invalid shapes); never less for more pixels. */
 size_t m3s_track_workspace_bytes(int32_t H, int32_t W);
 
 /*
@@ -356,7 +356,7 @@ typedef struct {
 /* Fills *params with the tracking defaults, 10 iterations and step_tol 0.  NULL is ignored. */
 void m3s_default_backend_params(m3s_backend_params *params);
 
-/* Workspace bytes m3s_backend_gn needs (0 on invalid sizes). */
+/* Workspace bytes m3s_backend_gn needs (0 on invalid sizes); never less for a larger N, H * W or E. */
 size_t m3s_backend_workspace_bytes(int32_t N, int32_t H, int32_t W, int32_t E);
 
 /*

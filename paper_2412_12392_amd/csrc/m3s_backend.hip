@@ -39,6 +39,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "m3s.h"
@@ -1500,9 +1501,25 @@ struct BackendLayout {
 
 int padded_dim(int N) { return (7 * (N - 1) + kTile - 1) / kTile * kTile; }
 
+// Workgroups of one edge with `per` matches a lane.
+int accum_blocks(int HW, int per) {
+    const int b = (HW + kThreads * per - 1) / (kThreads * per);
+    return b < 1 ? 1 : (b > 1024 ? 1024 : b);
+}
+
+// Rows of partials: enough for every problem with fewer edges or smaller frames as
+// well, so that a workspace kept for a program's largest graph serves them all.
+// (The split into more, shorter workgroups is taken below kAccumBlocks workgroups
+// and at most doubles them.)
+size_t partial_rows(int HW, int E) {
+    const size_t most = (size_t)accum_blocks(HW, kMatchesMost) * E, split = (size_t)accum_blocks(HW, kGroup) * E;
+    const size_t cap = 2 * (size_t)kAccumBlocks;
+    static_assert(kMatchesMost == 2 * kGroup, "one halving");
+    return std::max(most, std::min(split, cap));
+}
+
 BackendLayout backend_layout(int N, int HW, int E) {
     auto al = [](size_t v) { return (v + 255) / 256 * 256; };
-    const int bpe = backend_blocks_per_edge(HW, E);
     const size_t np = padded_dim(N);
     BackendLayout L;
     size_t o = 0;
@@ -1510,7 +1527,7 @@ BackendLayout backend_layout(int N, int HW, int E) {
     L.Trel = o;     o = al(o + sizeof(float) * 12 * E);
     L.edge_sys = o; o = al(o + sizeof(double) * kStride * E);
     L.edge_blk = o; o = al(o + sizeof(double) * kBlk * E);
-    L.partials = o; o = al(o + sizeof(float) * kMomentStride * (size_t)bpe * E);
+    L.partials = o; o = al(o + sizeof(float) * kMomentStride * partial_rows(HW, E));
     L.state = o;    o = al(o + sizeof(int32_t) * 4);
     L.stat = o;     o = al(o + sizeof(double) * 2);
     L.M = o;        o = al(o + sizeof(double) * np * np);
@@ -1529,11 +1546,8 @@ BackendLayout backend_layout(int N, int HW, int E) {
 // a lane, 1,127 with 16 and 1,085 with 8; for 15 edges at 160 x 120 the accumulation
 // takes 18.4 us with 16 (75 workgroups) and 6.9 with 4 (285).
 int backend_blocks_per_edge(int HW, int E) {
-    int m = kMatchesMost;
-    auto blocks = [&](int per) { return (HW + kThreads * per - 1) / (kThreads * per); };
-    while (m > kGroup && (int64_t)blocks(m) * E < kAccumBlocks) m /= 2;
-    const int b = blocks(m);
-    return b < 1 ? 1 : (b > 1024 ? 1024 : b);
+    const int most = accum_blocks(HW, kMatchesMost);
+    return (int64_t)most * E < kAccumBlocks ? accum_blocks(HW, kGroup) : most;
 }
 
 size_t backend_workspace_bytes(int N, int HW, int E) { return backend_layout(N, HW, E).total; }

@@ -324,9 +324,10 @@ __global__ void __launch_bounds__(256) fuse_kernel(int N, int first, const float
 // sums all rows.  10-iteration solve at 320 x 240: 78.6 us with 512 x 1, 86 with
 // 256 x 2, 84.8 with 1024 x 1; tracked frame at 512 x 384: 183 us with 256 x 4 or
 // 512 x 2, 196 with 512 x 4, 189 with 1024 x 1.
+constexpr int kSmallMatches = 256 * 512;
 struct TrackShape { int threads, per; };
 static TrackShape track_shape(int N) {
-    if (N <= 256 * 512) return {512, 1};
+    if (N <= kSmallMatches) return {512, 1};
     return {256, 4};
 }
 
@@ -337,7 +338,13 @@ int track_blocks(int N) {
     return nb < 1 ? 1 : (nb > kMaxBlocks ? kMaxBlocks : nb);
 }
 
-size_t track_workspace_bytes(int N) { return kOffPart + 2 * (size_t)track_blocks(N) * kMomentStride * sizeof(float); }
+// Enough for every smaller frame as well (which may have more workgroups), so that
+// a workspace kept for a program's largest frame serves them all.
+size_t track_workspace_bytes(int N) {
+    int nb = track_blocks(N);
+    if (N > kSmallMatches && nb < track_blocks(kSmallMatches)) nb = track_blocks(kSmallMatches);
+    return kOffPart + 2 * (size_t)nb * kMomentStride * sizeof(float);
+}
 
 hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* idx, const uint8_t* valid,
                         const float* Qf, const float* Qk, float q_min, float sigma_ray, float sigma_dist, float huber,
