@@ -25,9 +25,9 @@ typedef uint16_t u16_any __attribute__((aligned(1)));
 // Number of normal-equation values of a match set: the upper triangle of the 7x7
 // J^T W J (28, rows of 7, 6, ..., 1), J^T W r (7), robust cost, match count.
 constexpr int kPoseVals = 28 + 7 + 2;
-// What the matches are summed into: 30 moments that determine those values
-// (accumulate_match), kept in rows of 32 floats.
-constexpr int kMoments = 30;
+// What the matches are summed into: the 28 of those values that are neither zero
+// nor the negative of another (accumulate_match), kept in rows of 32 floats.
+constexpr int kMoments = 28;
 constexpr int kMomentStride = 32;
 
 __device__ __forceinline__ constexpr int upper_index(int a, int b) { return a * 7 - a * (a - 1) / 2 + (b - a); }
@@ -98,16 +98,19 @@ __device__ __forceinline__ void norm_of(float n2, float& id, float& d) {
 //   H_vv = ar I + (wd - ar) u u^T   H_vw = -ar [x]_x   H_vs = wd d u
 //   H_ww = wr P                     H_ws = 0           H_ss = wd d^2
 //   g_v  = wr P e / d + wd rd u     g_w = wr u x e     g_s  = wd rd d
-// so 30 moments hold all of it, and expand_moments forms the 37 values once
-// the sums are in fp64:
-//   0 ar   1-6 (wd - ar) u u^T (upper)   7-9 ar x   10-12 wd d u   13 wr
-//   14-19 wr u u^T (upper)   20 wd d^2   21-27 g   28 robust cost   29 count
-// A pose solve is bound by vector issue here (its operands come from L2): the
-// 37 sums with correctly rounded roots took about 240 instructions a match and
-// 89 us for 65 edges at 512 x 384, this about 140 and 68 us.
+// Each of its entries but the mirrored ones of H_vw is a sum of its own over the
+// matches, the diagonals of P from the other two squares (P_00 = u1^2 + u2^2):
+//   0-5 H_vv (upper)   6-8 ar x   9-11 H_vs   12-17 H_ww (upper)   18 H_ss
+//   19-25 g   26 robust cost   27 count
+// (H_ww as the difference of two totals, wr I - wr u u^T, would need two sums
+// fewer, but in a view of a few degrees, where u u^T is nearly I for one axis,
+// that leaves the roll's entry with 1e-5 of it in error, from 3e-8.)
+// A pose solve is bound by vector issue here (its operands come from L2): all 37
+// values with correctly rounded roots took about 240 instructions a match and
+// 89 us for 65 edges at 512 x 384, this about 145 and 60 us (two totals 59).
 // Adds nothing for a point at the origin or non-finite.  A pass sums either the
-// system (COST = false: moments 0 .. 27) or the cost and the count (moments 28
-// and 29), never both: the solves read the latter at the final pose only.
+// system (COST = false: moments 0 .. 25) or the cost and the count (moments 26
+// and 27), never both: the solves read the latter at the final pose only.
 template <bool COST>
 __device__ __forceinline__ void accumulate_match(const float* T, float X0, float X1, float X2, float Y0, float Y1,
                                                  float Y2, float q, const RobustWeights& rw, float* m) {
@@ -135,59 +138,55 @@ __device__ __forceinline__ void accumulate_match(const float* T, float X0, float
     const float a_dist = fabsf(rd) * __builtin_amdgcn_sqrtf(qd);
     if constexpr (COST) {
         const float c_ray = fminf(a_ray, rw.huber), c_dist = fminf(a_dist, rw.huber);
-        m[28] = fmaf(c_ray, fmaf(-0.5f, c_ray, a_ray), fmaf(c_dist, fmaf(-0.5f, c_dist, a_dist), m[28]));
-        m[29] += 1.f;
+        m[26] = fmaf(c_ray, fmaf(-0.5f, c_ray, a_ray), fmaf(c_dist, fmaf(-0.5f, c_dist, a_dist), m[26]));
+        m[27] += 1.f;
         return;
     }
     const float wr = qr * fminf(1.f, rw.huber * __builtin_amdgcn_rcpf(a_ray));
     const float wd = qd * fminf(1.f, rw.huber * __builtin_amdgcn_rcpf(a_dist));
     const float wri = wr * id, ar = wri * id, cv = wd - ar, wdd = wd * d, wdr = wd * rd;
-    m[0] += ar;
-    const float cu0 = cv * u0, cu1 = cv * u1, cu2 = cv * u2;
-    m[1] = fmaf(cu0, u0, m[1]);
-    m[2] = fmaf(cu0, u1, m[2]);
-    m[3] = fmaf(cu0, u2, m[3]);
-    m[4] = fmaf(cu1, u1, m[4]);
-    m[5] = fmaf(cu1, u2, m[5]);
-    m[6] = fmaf(cu2, u2, m[6]);
-    m[7] = fmaf(ar, x0, m[7]);
-    m[8] = fmaf(ar, x1, m[8]);
-    m[9] = fmaf(ar, x2, m[9]);
-    m[10] = fmaf(wdd, u0, m[10]);
-    m[11] = fmaf(wdd, u1, m[11]);
-    m[12] = fmaf(wdd, u2, m[12]);
-    m[13] += wr;
+    const float s0 = u0 * u0, s1 = u1 * u1, s2 = u2 * u2;
+    const float p0 = s1 + s2, p1 = s0 + s2, p2 = s0 + s1;  // diagonal of P
+    const float cu0 = cv * u0, cu1 = cv * u1;
+    m[0] = fmaf(ar, p0, fmaf(wd, s0, m[0]));
+    m[1] = fmaf(cu0, u1, m[1]);
+    m[2] = fmaf(cu0, u2, m[2]);
+    m[3] = fmaf(ar, p1, fmaf(wd, s1, m[3]));
+    m[4] = fmaf(cu1, u2, m[4]);
+    m[5] = fmaf(ar, p2, fmaf(wd, s2, m[5]));
+    m[6] = fmaf(ar, x0, m[6]);
+    m[7] = fmaf(ar, x1, m[7]);
+    m[8] = fmaf(ar, x2, m[8]);
+    m[9] = fmaf(wdd, u0, m[9]);
+    m[10] = fmaf(wdd, u1, m[10]);
+    m[11] = fmaf(wdd, u2, m[11]);
     const float wu0 = wr * u0, wu1 = wr * u1, wu2 = wr * u2;
-    m[14] = fmaf(wu0, u0, m[14]);
-    m[15] = fmaf(wu0, u1, m[15]);
-    m[16] = fmaf(wu0, u2, m[16]);
-    m[17] = fmaf(wu1, u1, m[17]);
-    m[18] = fmaf(wu1, u2, m[18]);
-    m[19] = fmaf(wu2, u2, m[19]);
-    m[20] = fmaf(wdd, d, m[20]);
+    m[12] = fmaf(wr, p0, m[12]);
+    m[13] = fmaf(-wu0, u1, m[13]);
+    m[14] = fmaf(-wu0, u2, m[14]);
+    m[15] = fmaf(wr, p1, m[15]);
+    m[16] = fmaf(-wu1, u2, m[16]);
+    m[17] = fmaf(wr, p2, m[17]);
+    m[18] = fmaf(wdd, d, m[18]);
     const float ue = fmaf(u0, e0, fmaf(u1, e1, u2 * e2));
-    m[21] = fmaf(wri, fmaf(-u0, ue, e0), fmaf(wdr, u0, m[21]));
-    m[22] = fmaf(wri, fmaf(-u1, ue, e1), fmaf(wdr, u1, m[22]));
-    m[23] = fmaf(wri, fmaf(-u2, ue, e2), fmaf(wdr, u2, m[23]));
-    m[24] = fmaf(wu1, e2, fmaf(-wu2, e1, m[24]));
-    m[25] = fmaf(wu2, e0, fmaf(-wu0, e2, m[25]));
-    m[26] = fmaf(wu0, e1, fmaf(-wu1, e0, m[26]));
-    m[27] = fmaf(wdr, d, m[27]);
+    m[19] = fmaf(wri, fmaf(-u0, ue, e0), fmaf(wdr, u0, m[19]));
+    m[20] = fmaf(wri, fmaf(-u1, ue, e1), fmaf(wdr, u1, m[20]));
+    m[21] = fmaf(wri, fmaf(-u2, ue, e2), fmaf(wdr, u2, m[21]));
+    m[22] = fmaf(wu1, e2, fmaf(-wu2, e1, m[22]));
+    m[23] = fmaf(wu2, e0, fmaf(-wu0, e2, m[23]));
+    m[24] = fmaf(wu0, e1, fmaf(-wu1, e0, m[24]));
+    m[25] = fmaf(wdr, d, m[25]);
 }
 
 // Value v of the normal equations (kPoseVals) from the summed moments.
 __device__ __forceinline__ double pose_value(const double* m, int v) {
-    // Per value: moment of a (or -1), moment of b (or -1), a + sign b.
-    constexpr int8_t kA[kPoseVals] = {0, 2, 3, -1, 9, -1, 10,  0, 5, -1, -1, 7, 11,  0, 8, -1, -1, 12,
-                                      13, -1, -1, -1,  13, -1, -1,  13, -1,  20,
-                                      21, 22, 23, 24, 25, 26, 27, 28, 29};
-    constexpr int8_t kB[kPoseVals] = {1, -1, -1, -1, -1, 8, -1,  4, -1, 9, -1, -1, -1,  6, -1, 7, -1, -1,
-                                      14, 15, 16, -1,  17, 18, -1,  19, -1,  -1,
-                                      -1, -1, -1, -1, -1, -1, -1, -1, -1};
-    // H_vv adds its second moment; H_vw and H_ww subtract it.
-    const bool plus = v == upper_index(0, 0) || v == upper_index(1, 1) || v == upper_index(2, 2);
-    const double a = kA[v] >= 0 ? m[kA[v]] : 0.0, b = kB[v] >= 0 ? m[kB[v]] : 0.0;
-    return plus ? a + b : a - b;
+    // Per value its moment (or -1 for a zero), and whether it enters negated (H_vw = -ar [x]_x).
+    constexpr int8_t kOf[kPoseVals] = {0, 1, 2, -1, 8, 7, 9,  3, 4, 8, -1, 6, 10,  5, 7, 6, -1, 11,
+                                       12, 13, 14, -1,  15, 16, -1,  17, -1,  18,
+                                       19, 20, 21, 22, 23, 24, 25, 26, 27};
+    const bool minus = v == upper_index(0, 5) || v == upper_index(1, 3) || v == upper_index(2, 4);
+    const double a = kOf[v] >= 0 ? m[kOf[v]] : 0.0;
+    return minus ? -a : a;
 }
 
 // Fixed-order fp64 sum of nparts fp32 rows of kMoments values (kMomentStride
