@@ -150,14 +150,14 @@ __device__ __forceinline__ void accumulate_match(const float* T, float X0, float
     }
     const float u0 = x0 * id, u1 = x1 * id, u2 = x2 * id;
     const float e0 = fmaf(-Y0, idy, u0), e1 = fmaf(-Y1, idy, u1), e2 = fmaf(-Y2, idy, u2), rd = d - dy;
-    // Whitened norms a, Huber weights min(1, width / a), and Huber costs
-    // c (a - c / 2) with c = min(a, width).
+    // Whitened norms a, Huber weights min(1, width / a), and Huber costs.
     const float qr = q * rw.w_ray, qd = q * rw.w_dist;
     const float a_ray = __builtin_amdgcn_sqrtf(fmaf(e0, e0, fmaf(e1, e1, e2 * e2)) * qr);
     const float a_dist = fabsf(rd) * __builtin_amdgcn_sqrtf(qd);
     if constexpr (COST) {
-        const float c_ray = fminf(a_ray, rw.huber), c_dist = fminf(a_dist, rw.huber);
-        m[26] = fmaf(c_ray, fmaf(-0.5f, c_ray, a_ray), fmaf(c_dist, fmaf(-0.5f, c_dist, a_dist), m[26]));
+        // (Branches, since an infinite norm costs +inf at any width, also an infinite one.)
+        auto cost = [&](float a) { return a <= rw.huber ? 0.5f * a * a : rw.huber * fmaf(-0.5f, rw.huber, a); };
+        m[26] += cost(a_ray) + cost(a_dist);
         m[27] += 1.f;
         return;
     }
