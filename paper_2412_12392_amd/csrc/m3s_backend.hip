@@ -114,6 +114,7 @@ constexpr int kMatchesMost = 8;     // matches per lane of the accumulation (amo
 constexpr int kAccumBlocks = 1536;   // workgroups of an accumulation, at least, where there are matches for them
 constexpr int kTile = 32;     // tile of the blocked Cholesky
 constexpr int kPanelRows = 416;  // panel rows kept in LDS (larger systems read the panel from memory)
+static_assert(kPanelRows <= kSolveThreads, "one thread per panel row");
 constexpr int kStageRows = 64;   // raw panel rows staged per step of the panel product
 constexpr int kPanelStride = kTile + 1;  // odd stride in doubles: rows of a wave fall in different banks
 
@@ -267,15 +268,20 @@ __global__ void __launch_bounds__(kEdgeThreads) backend_edge_kernel(BackendArgs 
 
 // Dense assembly of one block row of the reduced system (keyframe
 // p = row + 1, rows 7(p-1) .. 7(p-1)+6; row N-1 is the padding rows).  The row
-// block is summed in LDS from the edges' blocks in edge order (thread (a, b)
-// owns the entries at offset (a, b) of the diagonal block, thread 64 + (a, b)
-// those of the off-diagonal blocks, so every entry has one writer, which
-// visits the edges in order) and written out whole, zeros included, with its
-// right-hand side -g.
+// block is summed from the edges' blocks in edge order (thread (a, b) owns the
+// entry at offset (a, b) of the diagonal block, thread 64 + (a, b) those of the
+// off-diagonal blocks, in LDS, so every entry has one writer, which visits the
+// edges in order) and written out whole, zeros included, with its right-hand
+// side -g.  The workgroup first lists the row's edges, one test a lane: with two
+// waves looking at every edge in turn, a chain of one round trip an edge, the row
+// took 104 us at 741 edges, now 11.
 constexpr int kMaxNp = (kMaxDim + kTile - 1) / kTile * kTile;
+constexpr uint32_t kRowEdge = 0xffffu, kRowOwnI = 1u << 16;  // listed edge; its other keyframe from bit 17
+static_assert(M3S_MAX_EDGES <= 0x10000 && M3S_MAX_KEYFRAMES <= 1 << 15, "a listed edge in 32 bits");
 struct AssembleLds {
     double rows[7 * kMaxNp];
-    double rr[7];
+    uint32_t list[kSolveThreads];
+    int count[kSolveThreads / 64];
 };
 
 __device__ __forceinline__ void assemble_row(const BackendArgs& A, int row, AssembleLds& S) {
@@ -287,36 +293,54 @@ __device__ __forceinline__ void assemble_row(const BackendArgs& A, int row, Asse
         return;
     }
     for (int i = tid; i < 7 * np; i += kSolveThreads) S.rows[i] = 0.0;
-    if (tid < 7) S.rr[tid] = 0.0;
-    __syncthreads();
     const int P = row + 1, I = 7 * (P - 1);
-    const int a = (tid & 63) / 7, b = (tid & 63) % 7;
-    for (int e = 0; tid < 128 && e < A.E; ++e) {
+    const int lane = tid & 63, wave = tid >> 6, a = lane / 7, b = lane % 7;
+    const bool entry = lane < 49, rhs = tid >= 49 && tid < 56;
+    double own = 0.0;  // thread's entry of the diagonal block, or of the right-hand side
+    for (int e0 = 0; e0 < A.E; e0 += kSolveThreads) {
+        const int e = min(e0 + tid, A.E - 1);
         const int ei = A.edges[2 * e], ej = A.edges[2 * e + 1];
         // A self edge has T_ij = I whatever the poses: its blocks cancel.
-        if (!edge_in_range(ei, ej, A.N) || ei == ej) continue;
-        const bool own_i = ei == P;
-        if (!own_i && ej != P) continue;
-        const double* blk = A.edge_blk + (size_t)e * kBlk;
-        const int other = own_i ? ej : ei;
-        if (tid < 49) {
-            // H_ii += A^T H_e A (own_i), H_jj += A^T H_e A (own_j)
-            S.rows[a * np + I + b] += blk[7 * a + b];
-        } else if (tid >= 64 && tid < 64 + 49) {
-            // H_ij -= A^T H_e A, H_ji -= (A^T H_e A)^T; keyframe 0 holds the gauge
-            if (other > 0) S.rows[a * np + 7 * (other - 1) + b] -= own_i ? blk[7 * a + b] : blk[7 * b + a];
-        } else if (tid >= 49 && tid < 56) {
-            // right-hand side -g: g_i -= A^T g_e, g_j += A^T g_e
-            const int o = tid - 49;
-            S.rr[o] += own_i ? blk[49 + o] : -blk[49 + o];
+        const bool hit = e0 + tid < A.E && edge_in_range(ei, ej, A.N) && ei != ej && (ei == P || ej == P);
+        const uint64_t hits = __ballot(hit);
+        if (lane == 0) S.count[wave] = (int)__popcll(hits);
+        __syncthreads();
+        int at = (int)__popcll(hits & ((1ull << lane) - 1ull)), total = 0;
+        for (int w = 0; w < kSolveThreads / 64; ++w) {
+            if (w < wave) at += S.count[w];
+            total += S.count[w];
         }
+        if (hit) S.list[at] = (uint32_t)e | (ei == P ? kRowOwnI : 0u) | ((uint32_t)(ei == P ? ej : ei) << 17);
+        __syncthreads();
+        constexpr int kAhead = 4;  // reads in flight together
+        for (int l0 = 0; tid < 128 && l0 < total; l0 += kAhead) {
+            double t[kAhead];
+            uint32_t f[kAhead];
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                f[j] = S.list[min(l0 + j, total - 1)];
+                // The diagonal takes A^T H_e A from either end; H_ij -= A^T H_e A, H_ji -= (A^T H_e A)^T.
+                const bool turned = tid >= 64 && !(f[j] & kRowOwnI);
+                const int at = rhs ? 49 + (tid - 49) : entry ? (turned ? 7 * b + a : 7 * a + b) : 0;
+                t[j] = A.edge_blk[(size_t)(f[j] & kRowEdge) * kBlk + at];
+            }
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                if (l0 + j >= total) break;
+                const int other = (int)(f[j] >> 17);
+                if (tid < 64) own += rhs && !(f[j] & kRowOwnI) ? -t[j] : t[j];  // -g: g_i -= A^T g_e, g_j += A^T g_e
+                else if (entry && other > 0) S.rows[a * np + 7 * (other - 1) + b] -= t[j];  // keyframe 0 holds the gauge
+            }
+        }
+        __syncthreads();  // the list is done with
     }
+    if (tid < 49) S.rows[a * np + I + b] = own;
+    if (rhs) A.rhs[I + tid - 49] = own;
     __syncthreads();
     for (int i = tid; i < 7 * np; i += kSolveThreads) {
         const int r = i / np, c = i - r * np;
         A.M[(long)(I + r) * np + c] = S.rows[i];
     }
-    if (tid < 7) A.rhs[I + tid] = S.rr[tid];
 }
 
 // Tile (ti, tj) of M as kTile x kTile, row-major with leading dimension np.
@@ -612,9 +636,15 @@ __device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
 #pragma unroll
             for (int u = 0; u < kU; ++u) acc[u] = 0.0;
             for (int t = 0; t <= c; ++t) {
+                // (The reads together: with this many registers the scheduler would
+                // otherwise wait for each, 3 us a tile column.)
                 const double dv = Dinv[c][t];
+                double sv[kU];
 #pragma unroll
-                for (int u = 0; u < kU; ++u) acc[u] += stage[(tid / kTile + u * (kSolveThreads / kTile)) * kPanelStride + t] * dv;
+                for (int u = 0; u < kU; ++u) sv[u] = stage[(tid / kTile + u * (kSolveThreads / kTile)) * kPanelStride + t];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < kU; ++u) acc[u] += sv[u] * dv;
             }
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
@@ -642,12 +672,15 @@ __device__ __forceinline__ void dense_solve(const BackendArgs& A, DenseLds& S) {
                     trailing_tile(A, (const double*)(A.M + (long)R0 * np + k * kTile), np, R0, ti, tj, lane, &D[0][0]);
             }
             // b_i -= L_ik y_k, one thread per panel row.
-            for (int rr = tid; rr < m; rr += kSolveThreads) {
+            auto minus_ly = [&](const double* row, double* b) {
                 double sacc = 0.0;
-                for (int t = 0; t < kTile; ++t)
-                    sacc += (in_lds ? panel[rr * kPanelStride + t] : A.M[(long)(R0 + rr) * np + k * kTile + t]) *
-                            x[k * kTile + t];
-                x[R0 + rr] -= sacc;
+                for (int t = 0; t < kTile; ++t) sacc += row[t] * x[k * kTile + t];
+                *b -= sacc;
+            };
+            if (in_lds) {
+                if (tid < m) minus_ly(panel + tid * kPanelStride, x + R0 + tid);
+            } else {
+                for (int rr = tid; rr < m; rr += kSolveThreads) minus_ly(A.M + (long)(R0 + rr) * np + k * kTile, x + R0 + rr);
             }
         }
         __syncthreads();
