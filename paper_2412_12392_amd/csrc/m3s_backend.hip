@@ -69,6 +69,18 @@ constexpr int kLdsUpdates = 3072;
 constexpr int kMaxUpdates = 8192;
 // How the call's systems are solved (state[2]).
 enum { kSolveLds = 0, kSolveGlobal = 1, kSolveDense = 2 };
+// Whether a factor that exceeds LDS is solved faster as a dense system.  In the
+// workspace a solve takes about 3.9 us a level and 0.092 us a block product (33
+// keyframes, all joined: 32 levels, 5,456 products 581 us; 64 with 120 random
+// closures: 30, 3,288 420; 128, each joined to its 8 neighbours: 68, 4,368 725),
+// the dense one 2.9 us times the square of its tile columns (33 keyframes: 7
+// columns, 150 us; 39: 9, 269; 64: 14, 620), and above kPanelRows, where its panel
+// leaves LDS, 1.4 ms and more (128: 28, 9.1 ms), which no factor within the limits
+// takes.
+__device__ __forceinline__ bool dense_is_faster(int np, int nlev, int nupd) {
+    const int nt = np / 32;
+    return nt <= 14 && 390 * nlev + 9 * nupd > 294 * nt * nt + 210 * nt + 1200;  // in 10 ns
+}
 struct PatternBuf {
     int32_t nblk, nlev, nupd, pad;
     uint8_t perm[M3S_MAX_KEYFRAMES];          // position -> keyframe - 1
@@ -1009,7 +1021,8 @@ __global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs 
     }
     int nupd;
     int u0 = block_exclusive(usum, tmp, &nupd);
-    if (nupd > kMaxUpdates) {
+    const bool in_lds = nblk <= kLdsBlocks && nupd <= kLdsUpdates;
+    if (nupd > kMaxUpdates || (!in_lds && dense_is_faster(A.np, nlev_s, nupd))) {
         if (tid == 0) A.state[2] = kSolveDense;
         return;
     }
@@ -1103,7 +1116,7 @@ __global__ void __launch_bounds__(kPatThreads) backend_start_kernel(BackendArgs 
         P.nupd = nupd;
         P.colstart[nb] = (uint16_t)nblk;
         P.ustart[nblk] = (uint16_t)nupd;
-        A.state[2] = nblk <= kLdsBlocks && nupd <= kLdsUpdates ? kSolveLds : kSolveGlobal;
+        A.state[2] = in_lds ? kSolveLds : kSolveGlobal;
     }
 }
 

@@ -47,6 +47,8 @@ GRAPHS = [
     # More edge entries than the workspace way keeps in LDS (8,192), ids above 9 bits.
     ("workspace_3049_edges", 128, _both_ways(_chain(128), 3049), WORKSPACE),
     ("workspace_band", 64, _band(64, 8), WORKSPACE),
+    # Past LDS but faster dense.
+    ("dense_by_cost", 26, _full(26), DENSE),
     # More than 8,192 products, on both sides of the panel's limit in LDS (65 keyframes) ...
     ("dense_65", 65, _full(65), DENSE),
     ("dense_66", 66, _full(66), DENSE),
@@ -59,7 +61,7 @@ GRAPHS = [
 
 def expected_way(N, edges):
     """The library's order (level by level, each an independent set of keyframes of nearly the
-    least degree), and the blocks and products of the factor in it."""
+    least degree), the blocks and products of the factor in it, and the rule over them."""
     nb = N - 1
     near = [set() for _ in range(nb)]
     for i, j in edges:
@@ -95,7 +97,9 @@ def expected_way(N, edges):
             products += len(rows[x] & rows[z])
     if blocks <= 320 and products <= 3072:
         return LDS
-    return DENSE if blocks > 2048 or products > 8192 else WORKSPACE
+    tiles = -(-7 * nb // 32)
+    slow = tiles <= 14 and 390 * levels + 9 * products > 294 * tiles * tiles + 210 * tiles + 1200
+    return DENSE if blocks > 2048 or products > 8192 or slow else WORKSPACE
 
 
 @pytest.mark.parametrize("name,N,edges,way", GRAPHS, ids=[g[0] for g in GRAPHS])
