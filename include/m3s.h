@@ -427,7 +427,8 @@ void m3s_batched_last_config(int32_t *grid, int32_t *tile_config);
  *                (fp32); 5: 16x16 with an fp16 pre-filter (the default); 6: 8x8
  *                one-wave tiles with the fp16 pre-filter (the default of the
  *                single-pair launch for frames small enough that all their
- *                tiles are resident at once, with at most two levels);
+ *                tiles are resident at once, with at most two levels; for
+ *                wide windows only where 16x16 tiles do not serve better);
  *   grid         workgroups of the persistent batched launch (> 0);
  *   xcd_remap    0 turns off the tile-to-XCD band mapping of the single-pair launch;
  *   ray_margin   margin in pixels (1..3, default 2) of the LM ray window the

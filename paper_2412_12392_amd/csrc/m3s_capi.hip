@@ -178,11 +178,19 @@ int chosen_tile_config() {
 // CU) 25.2 and 24.7, 512 x 384 (12) 31.8 and 46.9; two levels at 256 x 192 (3)
 // 30.8 and 30.4, at 320 x 240 36.8 and 55.3.  Three levels fill the smaller tiles'
 // regions: 224 x 160 43.3 and 46.8.
+// Windows of radius 5 (two levels: 6) and more are bound by their own work, where
+// 16 x 16 tiles keep four waves a SIMD and share their reads, unless one a CU is
+// not enough.  r = 6: 128 x 96 (0.75 tiles of 8 x 8 a CU) 55.3 and 51.5, 200 x 150
+// (1.9) 56.2 and 57.7, 288 x 216 (3.8, 0.98 of 16 x 16) 59.0 and 67.8, 304 x 228 (4.3,
+// 1.1) 97.9 and 79.1; two levels of r = 6: 160 x 120 (1.2) 98.9 and 95.5, 256 x 192
+// (3) 101.3 and 104.1, but of r = 5 there 67.2 and 61.3.
 int pair_tile_config(const m3s_pair* A, const m3s_params* P, int cus) {
     if (g_override.tile_config >= 0) return g_override.tile_config;
-    const int64_t tiles = ((int64_t)A->W + 7) / 8 * ((A->H + 7) / 8);
-    const int per_cu = P->refine_levels == 1 ? 6 : P->refine_levels == 2 ? 3 : 0;
-    return desc_in_regs(A) && tiles <= (int64_t)per_cu * cus ? m3s::kSmallTileConfig : m3s::kDefaultTileConfig;
+    auto tiles = [&](int side) { return ((int64_t)A->W + side - 1) / side * ((A->H + side - 1) / side); };
+    const int levels = P->refine_levels;
+    int64_t most = (int64_t)(levels == 1 ? 6 : levels == 2 ? 3 : 0) * cus;
+    if (P->refine_radius > (levels == 1 ? 4 : 5) && tiles(16) <= cus) most = std::min(most, (int64_t)cus * 3 / 2);
+    return desc_in_regs(A) && tiles(8) <= most ? m3s::kSmallTileConfig : m3s::kDefaultTileConfig;
 }
 
 // Tile-to-XCD band mapping of the single-pair launch (on unless overridden).
