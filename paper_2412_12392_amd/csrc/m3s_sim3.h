@@ -17,10 +17,7 @@ namespace m3s {
 // 16-byte loads at a float's alignment and 4-byte loads at a byte's).
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t i4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef float f2_any __attribute__((ext_vector_type(2), aligned(4)));
-typedef int32_t i2_any __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
-typedef uint16_t u16_any __attribute__((aligned(1)));
 
 // Number of normal-equation values of a match set: the upper triangle of the 7x7
 // J^T W J (28, rows of 7, 6, ..., 1), J^T W r (7), robust cost, match count.

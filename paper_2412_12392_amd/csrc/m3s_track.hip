@@ -126,37 +126,26 @@ struct MatchGroup {
 
 template <int PER>
 __device__ __forceinline__ void load_group(const TrackArgs& A, int n0, MatchGroup<PER>& M) {
-    static_assert(PER == 1 || PER == 2 || PER == 4, "vector loads of 1, 2 or 4 pixels");
+    static_assert(PER == 1 || PER == 4, "single loads, or vector loads of 4 pixels");
     int mm[PER];
-    if (PER > 1 && n0 + PER <= A.N) {
+    bool whole = false;
+    if constexpr (PER == 4) whole = n0 + PER <= A.N;
+    if (whole) {
         const float* x = A.Xk + 3 * (long)n0;
-        float xs[3 * PER];
-        uint32_t v = 0u;
-        if constexpr (PER == 4) {
-            v = *reinterpret_cast<const u32_any*>(A.valid + n0);
-            const i4_any i = *reinterpret_cast<const i4_any*>(A.idx + n0);
-            const f4_any q = *reinterpret_cast<const f4_any*>(A.Qk + n0);
+        float xs[12];
+        const uint32_t v = *reinterpret_cast<const u32_any*>(A.valid + n0);
+        const i4_any i = *reinterpret_cast<const i4_any*>(A.idx + n0);
+        const f4_any q = *reinterpret_cast<const f4_any*>(A.Qk + n0);
 #pragma unroll
-            for (int u = 0; u < PER; ++u) { mm[u] = i[u]; M.qk[u] = q[u]; }
+        for (int k = 0; k < 3; ++k) {
+            const f4_any t = reinterpret_cast<const f4_any*>(x)[k];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const f4_any t = reinterpret_cast<const f4_any*>(x)[k];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) xs[4 * k + j] = t[j];
-            }
-        } else if constexpr (PER == 2) {
-            v = *reinterpret_cast<const u16_any*>(A.valid + n0);
-            const i2_any i = *reinterpret_cast<const i2_any*>(A.idx + n0);
-            const f2_any q = *reinterpret_cast<const f2_any*>(A.Qk + n0);
-            const f4_any xa = *reinterpret_cast<const f4_any*>(x);
-            const f2_any xb = *reinterpret_cast<const f2_any*>(x + 4);
-#pragma unroll
-            for (int u = 0; u < PER; ++u) { mm[u] = i[u]; M.qk[u] = q[u]; }
-#pragma unroll
-            for (int j = 0; j < 6; ++j) xs[j] = j < 4 ? xa[j & 3] : xb[j & 1];
+            for (int j = 0; j < 4; ++j) xs[4 * k + j] = t[j];
         }
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
+            mm[u] = i[u];
+            M.qk[u] = q[u];
             M.ok[u] = ((v >> (8 * u)) & 0xffu) != 0u;
 #pragma unroll
             for (int j = 0; j < 3; ++j) M.xk[u][j] = xs[3 * u + j];
@@ -325,15 +314,16 @@ __global__ void __launch_bounds__(256) fuse_kernel(int N, int first, const float
 // 256 x 2, 84.8 with 1024 x 1; tracked frame at 512 x 384: 183 us with 256 x 4 or
 // 512 x 2, 196 with 512 x 4, 189 with 1024 x 1.
 constexpr int kSmallMatches = 256 * 512;
-struct TrackShape { int threads, per; };
-static TrackShape track_shape(int N) {
-    if (N <= kSmallMatches) return {512, 1};
-    return {256, 4};
+
+// Calls f with the threads of a workgroup and the matches of a lane.
+template <class F>
+static auto with_track_shape(int N, F f) {
+    return N <= kSmallMatches ? f(std::integral_constant<int, 512>{}, std::integral_constant<int, 1>{})
+                              : f(std::integral_constant<int, 256>{}, std::integral_constant<int, 4>{});
 }
 
 int track_blocks(int N) {
-    const TrackShape t = track_shape(N);
-    const int per = t.threads * t.per;
+    const int per = with_track_shape(N, [](auto threads, auto per) { return threads * per; });
     const int nb = N / per + (N % per != 0);
     return nb < 1 ? 1 : (nb > kMaxBlocks ? kMaxBlocks : nb);
 }
@@ -363,13 +353,13 @@ hipError_t launch_track(int N, const float* Xk, const float* Xf, const int32_t* 
     A.info = info;
     const int nb = track_blocks(N);
     A.nb = nb;
-    const bool small = N <= 256 * 512;
     for (int it = 0; it <= iters; ++it) {
         timer_begin("track_step", s);
         auto step = [&](auto cost) {
-            constexpr bool C = decltype(cost)::value;
-            if (small) track_step_kernel<512, 1, C><<<nb, 512, 0, s>>>(A, it);
-            else track_step_kernel<256, 4, C><<<nb, 256, 0, s>>>(A, it);
+            with_track_shape(N, [&](auto threads, auto per) {
+                track_step_kernel<decltype(threads)::value, decltype(per)::value, decltype(cost)::value>
+                    <<<nb, decltype(threads)::value, 0, s>>>(A, it);
+            });
         };
         // The last launch sums the cost and the count at the final pose.
         if (it == iters) step(std::true_type{});
