@@ -726,7 +726,7 @@ struct Window16 {
 // three levels took 84 us at r = 3 and 126 at r = 4, now 70 and 91; two levels of
 // r = 4 78, now 59.
 // SP: the spacing where it is fixed at compile time (columns at immediate
-// offsets, a tenth of the instructions less than with their own addresses), or 0.
+// offsets instead of an address each), or 0.
 template <int R, int CAP, bool CLIP, bool MULTI, int SP>
 __device__ __forceinline__ void scan16(const uint32_t* q16, const uint4* __restrict__ sd, const Window16& win, int rw,
                                        int lev, int rows, float tau, float& run, uint64_t& mask0, uint64_t& mask1) {
